@@ -1145,6 +1145,227 @@ FPH_DEVINL void cheb_series_part(const Win& w, int NP, const typename Cplx<T>::t
   if ((NP - 1) & 1) __syncthreads();
 }
 
+// The series of cheb_series for one component (real or imaginary part) of
+// the block vector per lane.  A = sA D C' - cA is real, so the recurrence
+// never mixes the two parts; only the coefficients are complex.  Lane l < 32
+// of a wave holds the real part and lane l + 32 the imaginary part of the
+// same plaquette, each in LDS buffers of its own, and each lane sums
+// Re(c_m) alpha_m and Im(c_m) alpha_m apart; one exchange between the two
+// halves of the wave ends the series:
+//   re = sum cr a - sum ci b,   im = sum cr b + sum ci a.
+
+// c ? a : b by value (a conditional on two array elements may select their
+// addresses, which puts the array in private memory).
+template <typename T>
+FPH_DEVINL T sel(bool c, T a, T b) {
+  return c ? a : b;
+}
+
+template <typename T, bool TRANS, bool ROW16>
+FPH_DEVINL void r_publish(const Win& w, const T (&x)[4], T* buf, T th, T (&c)[4], int q, int Q) {
+  using T2 = typename Cplx<T>::type;
+#pragma unroll
+  for (int m = 0; m < 4; ++m) c[m] = x[m];
+  if (TRANS) plaq_rot(c, th);
+  if (!ROW16) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) buf[w.own[m]] = c[m];
+  } else {
+    const T l1 = row_ror<1>(c[1]), l3 = row_ror<1>(c[3]);    // sites (x0-1, y0), (x0-1, y0+1)
+    const T r0 = row_ror<15>(c[0]), r2 = row_ror<15>(c[2]);  // sites (x0+2, y0), (x0+2, y0+1)
+    c[0] = fma(th, l1, c[0]);
+    c[1] = fma(th, r0, c[1]);
+    c[2] = fma(th, l3, c[2]);
+    c[3] = fma(th, r2, c[3]);
+    reinterpret_cast<T2*>(buf)[q] = T2{c[0], c[1]};
+    reinterpret_cast<T2*>(buf)[Q + q] = T2{c[2], c[3]};
+  }
+}
+
+template <typename T, bool TRANS, bool ROW16>
+FPH_DEVINL void r_finish(const Win& w, const T (&c)[4], T (&y)[4], const T* buf, T th, int Q) {
+  using T2 = typename Cplx<T>::type;
+  __syncthreads();
+  if (!ROW16) {
+    const T a0 = buf[w.hm[0]], a1 = buf[w.hm[1]], a2 = buf[w.hm[2]], a3 = buf[w.hm[3]];
+    const T m0 = buf[w.cm[0]], m1 = buf[w.cm[1]], p0 = buf[w.cp[0]], p1 = buf[w.cp[1]];
+    const T b0 = buf[w.hp[0]], b1 = buf[w.hp[1]], b2 = buf[w.hp[2]], b3 = buf[w.hp[3]];
+    // x-direction pairs on the rows y0-1, y0, y0+1, y0+2, then y-direction
+    y[0] = fma(th, fma(th, a0, a1), fma(th, m0, c[0]));
+    y[1] = fma(th, fma(th, a3, a2), fma(th, p0, c[1]));
+    y[2] = fma(th, fma(th, b0, b1), fma(th, m1, c[2]));
+    y[3] = fma(th, fma(th, b3, b2), fma(th, p1, c[3]));
+  } else {
+    const T2 t = reinterpret_cast<const T2*>(buf)[Q + w.qa];  // row y0-1
+    const T2 b = reinterpret_cast<const T2*>(buf)[w.qb];      // row y0+2
+    y[0] = fma(th, t.x, c[0]);
+    y[1] = fma(th, t.y, c[1]);
+    y[2] = fma(th, b.x, c[2]);
+    y[3] = fma(th, b.y, c[3]);
+  }
+  if (!TRANS) plaq_rot(y, th);
+}
+
+template <typename T, bool TRANS, bool ROW16>
+FPH_DEVINL void cheb_series_split(const Win& w, int NP, const typename Cplx<T>::type* cf, T sA,
+                                  T cA, T (&x)[4], const T (&db)[4], T* buf0, T* buf1, T th,
+                                  bool im, int qid, int Q) {
+  using T2 = typename Cplx<T>::type;
+  T sr[4], si[4], p[4], q[4], y[4], c_[4];
+  auto accumulate = [&](const T2 c, const T (&v)[4]) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      sr[k] = fma(c.x, v[k], sr[k]);
+      si[k] = fma(c.y, v[k], si[k]);
+    }
+  };
+  const T c2 = (T)2 * cA;
+  T sdb[4], db2[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    sr[k] = si[k] = (T)0;
+    p[k] = TRANS ? db[k] * x[k] : x[k];
+    sdb[k] = sA * db[k];
+    db2[k] = (T)2 * sdb[k];
+  }
+  auto rec = [&](T (&v)[4], const T (&u)[4]) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = fma(db2[k], y[k], fma(-c2, u[k], -v[k]));
+  };
+  if (NP >= 2) r_publish<T, TRANS, ROW16>(w, p, buf0, th, c_, qid, Q);
+  accumulate(cf[0], p);
+  if (NP >= 2) {
+    T2 c = cf[1];
+    r_finish<T, TRANS, ROW16>(w, c_, y, buf0, th, Q);
+    T2 cn = cf[min(2, NP - 1)];  // one step ahead, as in cheb_series
+#pragma unroll
+    for (int k = 0; k < 4; ++k) q[k] = fma(sdb[k], y[k], -cA * p[k]);
+    if (NP > 2) r_publish<T, TRANS, ROW16>(w, q, buf1, th, c_, qid, Q);
+    accumulate(c, q);
+    for (int m = 2; m < NP; m += 2) {
+      r_finish<T, TRANS, ROW16>(w, c_, y, buf1, th, Q);
+      c = cn;
+      cn = cf[min(m + 1, NP - 1)];
+      rec(p, q);
+      if (m + 1 < NP) r_publish<T, TRANS, ROW16>(w, p, buf0, th, c_, qid, Q);
+      accumulate(c, p);
+      if (m + 1 >= NP) break;
+      r_finish<T, TRANS, ROW16>(w, c_, y, buf0, th, Q);
+      c = cn;
+      cn = cf[min(m + 2, NP - 1)];
+      rec(q, p);
+      if (m + 2 < NP) r_publish<T, TRANS, ROW16>(w, q, buf1, th, c_, qid, Q);
+      accumulate(c, q);
+    }
+    // A following series first writes buffer 0; after an odd number of
+    // exchanges the last one read buffer 0, so every thread must be past it.
+    if ((NP - 1) & 1) __syncthreads();
+  }
+  // The coefficients of A^T are conjugated: Im(c_m) changes its sign.
+  const T sgn = (TRANS == im) ? (T)-1 : (T)1;  // of the partner's sum (re, im): -, +; F^T: +, -
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    x[k] = fma(sgn, __shfl_xor(si[k], 32, 64), sr[k]);
+    if (TRANS) x[k] *= (T)1 / db[k];
+  }
+}
+
+// Values of one component's slice buffer in k_kpm_split: kpm_row_stride rows
+// with the spare entries, and in FP32 an odd multiple of 32 banks, so that
+// the halves of a wave, which read their own buffers in one pass, do not meet
+// on a bank.
+template <typename T>
+__host__ __device__ inline int kpm_split_buf(const Geom& g) {
+  const int n = 2 * kpm_row_stride(g.hL) * g.L + kWinPad;
+  return sizeof(T) == 4 ? ((n + 63) & ~63) + 32 : (n + 1) & ~1;
+}
+
+// Per-block Chebyshev apply of k_kpm for slices of up to 256 plaquettes,
+// with the real and imaginary parts on separate lanes (cheb_series_split):
+// thread t serves plaquette 32 (t / 64) + t mod 32 and the part t / 32 mod 2,
+// NT >= 2 Q.  The kernel is bound by its longest block, a chain of 2 (N_P - 1)
+// exchanges that one wave per SIMD cannot issue fast enough; splitting the
+// parts halves the instructions of each step and doubles the waves.  Longest
+// block at L = 32, Ltau = 400, FP32, 30 exchanges: 12.1 -> 9.7 us.
+template <typename T, int NT, bool ROW16>
+__global__ void __launch_bounds__(NT)
+k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
+            const int* __restrict__ np, const typename Cplx<T>::type* __restrict__ coef,
+            const T* __restrict__ dbar, T th, T c4, const typename Cplx<T>::type* __restrict__ Z,
+            typename Cplx<T>::type* __restrict__ Zo, StIO io) {
+  using T2 = typename Cplx<T>::type;
+  static_assert(NT <= kNPMax, "one coefficient per thread is loaded ahead");
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ RhsState s_sh;
+  const int nbuf = kpm_split_buf<T>(g);
+  const int lane = threadIdx.x & 63;
+  const bool im = lane >= 32;
+  T* buf0 = reinterpret_cast<T*>(smem_raw) + (im ? nbuf : 0);
+  T* buf1 = buf0 + 2 * nbuf;
+  T2* cfs = reinterpret_cast<T2*>(reinterpret_cast<T*>(smem_raw) + 4 * nbuf);
+  const int ko = blockIdx.x / nrhs;
+  const int r = blockIdx.x % nrhs;
+  const int k = (ko % 2 == 0) ? ko / 2 : H - 1 - ko / 2;
+  const int q = (threadIdx.x >> 6) * 32 + (lane & 31);
+  const bool own = q < g.Q;
+  const Win w = make_win(g, q, own);
+  const int i0 = w.x0 + w.row[1], iL = i0 + g.L;
+
+  // Solver state: as in k_kpm, one block per right-hand side reads and
+  // writes it, folding it between the two series.
+  const bool stt = io.in != nullptr && ko == H - 1;
+  StLoad<4> sl;
+  if (stt) state_issue(io, r, sl);
+  const int f = field_of(g, r);
+  info += f;
+  np += (long)f * g.Ltau;
+  coef += (long)f * H * kNPMax;
+  dbar += (long)f * g.N;
+  const int NP = np[2 * k];
+  const T sA = (T)info->s, cA = (T)info->c;
+  const T2 c_first = coef[(long)k * kNPMax + threadIdx.x];
+  T x[4], db[4];
+  {
+    const T2* Zin = Z + ((long)r * H + k) * g.N;
+    T2 z[4];
+    ld2c(Zin + i0, z[0], z[1]);
+    ld2c(Zin + iL, z[2], z[3]);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) x[m] = sel(im, z[m].y, z[m].x);
+  }
+  db[0] = c4 * dbar[i0]; db[1] = c4 * dbar[i0 + 1];
+  db[2] = c4 * dbar[iL]; db[3] = c4 * dbar[iL + 1];
+  if (stt && op != 2) {
+    state_finish<NT>(io, r, sl, &s_sh);
+    if (s_sh.done) {
+      state_end(io, r, &s_sh, P_NONE, 0.0, 0, 1, true);
+      return;
+    }
+  }
+  if ((int)threadIdx.x < NP) cfs[threadIdx.x] = c_first;
+  for (int m = threadIdx.x + NT; m < NP; m += NT) cfs[m] = coef[(long)k * kNPMax + m];
+  __syncthreads();
+  if (op != 0)
+    cheb_series_split<T, true, ROW16>(w, NP, cfs, sA, cA, x, db, buf0, buf1, th, im, q, g.Q);
+  if (op == 2 && stt) {
+    state_finish<NT>(io, r, sl, &s_sh);
+    if (s_sh.done) {
+      state_end(io, r, &s_sh, P_NONE, 0.0, 0, 1, true);
+      return;
+    }
+  }
+  if (op != 1)
+    cheb_series_split<T, false, ROW16>(w, NP, cfs, sA, cA, x, db, buf0, buf1, th, im, q, g.Q);
+  // Row y0 is stored by the real lane, row y0+1 by the imaginary one.
+  const T t0 = __shfl_xor(sel(im, x[0], x[2]), 32, 64);
+  const T t1 = __shfl_xor(sel(im, x[1], x[3]), 32, 64);
+  if (own) {
+    T2* Zout = Zo + ((long)r * H + k) * g.N + (im ? iL : i0);
+    st2c(Zout, T2{sel(im, t0, x[0]), sel(im, x[2], t0)}, T2{sel(im, t1, x[1]), sel(im, x[3], t1)});
+  }
+  if (stt) state_end(io, r, &s_sh, P_NONE, 0.0, 0, 1, true);
+}
+
 // Per-block Chebyshev apply.  op 0: F (series in A), 1: F^T (conjugate
 // series in A^T), 2: F F^T (conjugate series, then series).  Block b
 // serves frequency order b / nrhs (longest series first: k = 0, H-1, 1,
@@ -1459,15 +1680,43 @@ hipError_t pc_launch_kpm(const PcTables* pc, const Geom& g, const T* dbar, int o
   return hipGetLastError();
 }
 
+template <typename T, int NT, bool ROW16 = false>
+hipError_t pc_launch_kpm_split(const PcTables* pc, const Geom& g, const T* dbar, int op, int nrhs,
+                               const typename Cplx<T>::type* Z, typename Cplx<T>::type* Zo,
+                               StateSeq& sq, T th, T c4, hipStream_t s) {
+  using T2 = typename Cplx<T>::type;
+  const StIO io = sq.next();
+  const size_t lds = 4 * (size_t)kpm_split_buf<T>(g) * sizeof(T) + kNPMax * sizeof(T2);
+  auto kern = k_kpm_split<T, NT, ROW16>;
+  hipError_t e = allow_lds((const void*)kern, lds);
+  if (e != hipSuccess) return e;
+  const auto* cf = (const T2*)(sizeof(T) == 8 ? (const void*)pc->coef64 : (const void*)pc->coef32);
+  hipLaunchKernelGGL(kern, dim3(pc->H * nrhs), dim3(NT), lds, s, g, pc->H, nrhs, op, pc->info,
+                     pc->np, cf, dbar, th, c4, Z, Zo, io);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t pc_kpm(const PcTables* pc, const Geom& g, const T* dbar, int op, int nrhs,
                   const typename Cplx<T>::type* Z, typename Cplx<T>::type* Zo, StateSeq& sq,
                   T th, T c4, hipStream_t s) {
-  // L = 32: each plaquette row is one 16-lane row of a wave (row form).
-  if (g.hL == 16 && g.Q == 256)
+  // Split parts up to 256 plaquettes (8 waves); with 16 waves per block
+  // (L = 40) the barrier costs more than the shorter steps give (26.2
+  // against 24.2 us per FP32 F F^T at Ltau = 100, 30.7 against 28.7 in FP64).
+  // L = 32: each plaquette row is one 16-lane row of a wave (row form).  There
+  // the FP32 blocks of several right-hand sides fill the compute units, so
+  // past two blocks each, where issue and not the chain sets the time, the
+  // unsplit form needs fewer instructions (Ltau = 400: split 19.1 against
+  // 20.8 us for one right-hand side, 23.2 / 24.1 for two, 33.2 / 32.2 for
+  // four, 49.1 / 46.5 for ten); FP64 gains or ties throughout.
+  if (g.hL == 16 && g.Q == 256) {
+    if (sizeof(T) == 8 || (long)pc->H * nrhs <= 512)
+      return pc_launch_kpm_split<T, 512, true>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
     return pc_launch_kpm<T, 256, true>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
-  if (g.Q <= 64) return pc_launch_kpm<T, 64>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
-  if (g.Q <= 256) return pc_launch_kpm<T, 256>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
+  }
+  if (g.Q <= 64) return pc_launch_kpm_split<T, 128>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
+  if (g.Q <= 128) return pc_launch_kpm_split<T, 256>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
+  if (g.Q <= 256) return pc_launch_kpm_split<T, 512>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
   if (g.Q <= 512) return pc_launch_kpm<T, 512>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
   return pc_launch_kpm<T, 1024>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
 }

@@ -1,0 +1,42 @@
+"""Kernels at the edges of their dispatch rules, against the oracle."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import lattice as OL
+from oracle import precond as OP
+from paper_2203_01291_amd.solver import FermionSolver
+
+pytestmark = pytest.mark.gpu
+
+
+def _relmax(a, b):
+    return float(np.max(np.abs(a - b)) / np.max(np.abs(b)))
+
+
+def _solver(lat, max_rhs):
+    return FermionSolver(lat.L, lat.Ltau, lat.dtau, lat.t, lat.mu, lat.alpha, max_rhs=max_rhs)
+
+
+# Chebyshev blocks by plaquettes per slice: 64 and 81 (either side of one wave per part), 121 and 144
+# (128), 256 (row form, one to three right-hand sides: split and unsplit FP32), 289 (above 256);
+# Ltau = 2 has a single frequency with one or two terms.
+@pytest.mark.parametrize("L,Ltau,nrhs", [(16, 8, 1), (18, 12, 2), (22, 6, 1), (24, 4, 3), (32, 400, 1),
+                                         (32, 400, 3), (34, 4, 1), (4, 2, 1), (10, 2, 2)])
+def test_precond_block_shapes(L, Ltau, nrhs):
+    lat = OL.Lattice(L, Ltau, 0.1, 1.0, -0.1, 1.1)
+    rng = np.random.default_rng(100 * L + Ltau)
+    x = rng.standard_normal((Ltau, lat.N))
+    v = rng.standard_normal((nrhs, Ltau, lat.N))
+    a1, a2 = (0.15, 12.0) if Ltau == 400 else (1.0, 3.0)
+    pc = OP.Preconditioner(lat, x, a1, a2, C=OL.sparse_C(lat).tocsr())
+    s = _solver(lat, nrhs)
+    s.set_field(torch.from_numpy(x).cuda(), a1, a2)
+    vg = torch.from_numpy(v).cuda()
+    w = pc.apply_F(v, transpose=True)
+    refs = {"F": pc.apply_F(v), "FT": w, "FFT": pc.apply_F(w)}
+    for op, ref in refs.items():
+        # rounding of a series of a few tens of terms in each precision
+        assert _relmax(s.precond(vg, op).cpu().numpy(), ref) < 1e-12, op
+        assert _relmax(s.precond(vg.float(), op).cpu().numpy().astype(np.float64), ref) < 1e-5, op
