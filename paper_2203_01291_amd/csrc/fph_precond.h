@@ -1147,11 +1147,10 @@ FPH_DEVINL void cheb_series_part(const Win& w, int NP, const typename Cplx<T>::t
 
 // The series of cheb_series for one component (real or imaginary part) of
 // the block vector per lane.  A = sA D C' - cA is real, so the recurrence
-// never mixes the two parts; only the coefficients are complex.  Lane l < 32
-// of a wave holds the real part and lane l + 32 the imaginary part of the
-// same plaquette, each in LDS buffers of its own, and each lane sums
-// Re(c_m) alpha_m and Im(c_m) alpha_m apart; one exchange between the two
-// halves of the wave ends the series:
+// never mixes the two parts; only the coefficients are complex.  Each lane
+// holds one part of its plaquette (`im` the imaginary one), the parts in LDS
+// buffers of their own, and sums Re(c_m) alpha_m and Im(c_m) alpha_m apart;
+// one exchange with the lane of the other part (`swap`) ends the series:
 //   re = sum cr a - sum ci b,   im = sum cr b + sum ci a.
 
 // c ? a : b by value (a conditional on two array elements may select their
@@ -1182,10 +1181,23 @@ FPH_DEVINL void r_publish(const Win& w, const T (&x)[4], T* buf, T th, T (&c)[4]
   }
 }
 
-template <typename T, bool TRANS, bool ROW16>
+// Ends an exchange: a workgroup barrier, or, where one wave holds the whole
+// slice of its part, only an order for the compiler (a wave's LDS accesses
+// complete in order).
+template <bool WAVE>
+FPH_DEVINL void exchange_sync() {
+  if constexpr (WAVE) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  } else {
+    __syncthreads();
+  }
+}
+
+template <typename T, bool TRANS, bool ROW16, bool WAVE>
 FPH_DEVINL void r_finish(const Win& w, const T (&c)[4], T (&y)[4], const T* buf, T th, int Q) {
   using T2 = typename Cplx<T>::type;
-  __syncthreads();
+  exchange_sync<WAVE>();
   if (!ROW16) {
     const T a0 = buf[w.hm[0]], a1 = buf[w.hm[1]], a2 = buf[w.hm[2]], a3 = buf[w.hm[3]];
     const T m0 = buf[w.cm[0]], m1 = buf[w.cm[1]], p0 = buf[w.cp[0]], p1 = buf[w.cp[1]];
@@ -1206,10 +1218,10 @@ FPH_DEVINL void r_finish(const Win& w, const T (&c)[4], T (&y)[4], const T* buf,
   if (!TRANS) plaq_rot(y, th);
 }
 
-template <typename T, bool TRANS, bool ROW16>
+template <typename T, bool TRANS, bool ROW16, bool WAVE, class Swap>
 FPH_DEVINL void cheb_series_split(const Win& w, int NP, const typename Cplx<T>::type* cf, T sA,
                                   T cA, T (&x)[4], const T (&db)[4], T* buf0, T* buf1, T th,
-                                  bool im, int qid, int Q) {
+                                  bool im, int qid, int Q, const Swap& swap) {
   using T2 = typename Cplx<T>::type;
   T sr[4], si[4], p[4], q[4], y[4], c_[4];
   auto accumulate = [&](const T2 c, const T (&v)[4]) {
@@ -1236,21 +1248,21 @@ FPH_DEVINL void cheb_series_split(const Win& w, int NP, const typename Cplx<T>::
   accumulate(cf[0], p);
   if (NP >= 2) {
     T2 c = cf[1];
-    r_finish<T, TRANS, ROW16>(w, c_, y, buf0, th, Q);
+    r_finish<T, TRANS, ROW16, WAVE>(w, c_, y, buf0, th, Q);
     T2 cn = cf[min(2, NP - 1)];  // one step ahead, as in cheb_series
 #pragma unroll
     for (int k = 0; k < 4; ++k) q[k] = fma(sdb[k], y[k], -cA * p[k]);
     if (NP > 2) r_publish<T, TRANS, ROW16>(w, q, buf1, th, c_, qid, Q);
     accumulate(c, q);
     for (int m = 2; m < NP; m += 2) {
-      r_finish<T, TRANS, ROW16>(w, c_, y, buf1, th, Q);
+      r_finish<T, TRANS, ROW16, WAVE>(w, c_, y, buf1, th, Q);
       c = cn;
       cn = cf[min(m + 1, NP - 1)];
       rec(p, q);
       if (m + 1 < NP) r_publish<T, TRANS, ROW16>(w, p, buf0, th, c_, qid, Q);
       accumulate(c, p);
       if (m + 1 >= NP) break;
-      r_finish<T, TRANS, ROW16>(w, c_, y, buf0, th, Q);
+      r_finish<T, TRANS, ROW16, WAVE>(w, c_, y, buf0, th, Q);
       c = cn;
       cn = cf[min(m + 2, NP - 1)];
       rec(q, p);
@@ -1259,13 +1271,15 @@ FPH_DEVINL void cheb_series_split(const Win& w, int NP, const typename Cplx<T>::
     }
     // A following series first writes buffer 0; after an odd number of
     // exchanges the last one read buffer 0, so every thread must be past it.
-    if ((NP - 1) & 1) __syncthreads();
+    if (!WAVE && ((NP - 1) & 1)) __syncthreads();
   }
   // The coefficients of A^T are conjugated: Im(c_m) changes its sign.
   const T sgn = (TRANS == im) ? (T)-1 : (T)1;  // of the partner's sum (re, im): -, +; F^T: +, -
+  T o[4];
+  swap(si, o);
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    x[k] = fma(sgn, __shfl_xor(si[k], 32, 64), sr[k]);
+    x[k] = fma(sgn, o[k], sr[k]);
     if (TRANS) x[k] *= (T)1 / db[k];
   }
 }
@@ -1283,11 +1297,15 @@ __host__ __device__ inline int kpm_split_buf(const Geom& g) {
 // Per-block Chebyshev apply of k_kpm for slices of up to 256 plaquettes,
 // with the real and imaginary parts on separate lanes (cheb_series_split):
 // thread t serves plaquette 32 (t / 64) + t mod 32 and the part t / 32 mod 2,
-// NT >= 2 Q.  The kernel is bound by its longest block, a chain of 2 (N_P - 1)
+// NT >= 2 Q (kHalves).  Up to 64 plaquettes one wave holds a whole part
+// (kOneWave: both, Q <= 32; kWavePerPart) and the steps need no barrier
+// (L = 16, Ltau = 160, FP64, N_P 60: 27.0 -> 23 us; unsplit 38 us).  The kernel is bound by its longest block, a chain of 2 (N_P - 1)
 // exchanges that one wave per SIMD cannot issue fast enough; splitting the
 // parts halves the instructions of each step and doubles the waves.  Longest
 // block at L = 32, Ltau = 400, FP32, 30 exchanges: 12.1 -> 9.7 us.
-template <typename T, int NT, bool ROW16>
+enum { kHalves = 0, kOneWave = 1, kWavePerPart = 2 };
+
+template <typename T, int NT, bool ROW16, int LAY>
 __global__ void __launch_bounds__(NT)
 k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
             const int* __restrict__ np, const typename Cplx<T>::type* __restrict__ coef,
@@ -1298,18 +1316,35 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ RhsState s_sh;
   const int nbuf = kpm_split_buf<T>(g);
+  constexpr bool kWave = LAY != kHalves;
+  __shared__ T xs[LAY == kWavePerPart ? 2 * 4 * 64 : 1];
   const int lane = threadIdx.x & 63;
-  const bool im = lane >= 32;
+  const bool im = LAY == kWavePerPart ? threadIdx.x >= 64 : lane >= 32;
   T* buf0 = reinterpret_cast<T*>(smem_raw) + (im ? nbuf : 0);
   T* buf1 = buf0 + 2 * nbuf;
   T2* cfs = reinterpret_cast<T2*>(reinterpret_cast<T*>(smem_raw) + 4 * nbuf);
   const int ko = blockIdx.x / nrhs;
   const int r = blockIdx.x % nrhs;
   const int k = (ko % 2 == 0) ? ko / 2 : H - 1 - ko / 2;
-  const int q = (threadIdx.x >> 6) * 32 + (lane & 31);
+  const int q = LAY == kWavePerPart ? lane : (threadIdx.x >> 6) * 32 + (lane & 31);
   const bool own = q < g.Q;
   const Win w = make_win(g, q, own);
   const int i0 = w.x0 + w.row[1], iL = i0 + g.L;
+
+  // o = the other part's v.
+  auto swap = [&](const T (&v)[4], T (&o)[4]) {
+    if constexpr (LAY == kWavePerPart) {
+#pragma unroll
+      for (int m = 0; m < 4; ++m) xs[(im * 4 + m) * 64 + lane] = v[m];
+      __syncthreads();
+#pragma unroll
+      for (int m = 0; m < 4; ++m) o[m] = xs[((1 - im) * 4 + m) * 64 + lane];
+      __syncthreads();
+    } else {
+#pragma unroll
+      for (int m = 0; m < 4; ++m) o[m] = __shfl_xor(v[m], 32, 64);
+    }
+  };
 
   // Solver state: as in k_kpm, one block per right-hand side reads and
   // writes it, folding it between the two series.
@@ -1346,7 +1381,8 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
   for (int m = threadIdx.x + NT; m < NP; m += NT) cfs[m] = coef[(long)k * kNPMax + m];
   __syncthreads();
   if (op != 0)
-    cheb_series_split<T, true, ROW16>(w, NP, cfs, sA, cA, x, db, buf0, buf1, th, im, q, g.Q);
+    cheb_series_split<T, true, ROW16, kWave>(w, NP, cfs, sA, cA, x, db, buf0, buf1, th, im, q, g.Q,
+                                            swap);
   if (op == 2 && stt) {
     state_finish<NT>(io, r, sl, &s_sh);
     if (s_sh.done) {
@@ -1355,10 +1391,12 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
     }
   }
   if (op != 1)
-    cheb_series_split<T, false, ROW16>(w, NP, cfs, sA, cA, x, db, buf0, buf1, th, im, q, g.Q);
+    cheb_series_split<T, false, ROW16, kWave>(w, NP, cfs, sA, cA, x, db, buf0, buf1, th, im, q, g.Q,
+                                             swap);
   // Row y0 is stored by the real lane, row y0+1 by the imaginary one.
-  const T t0 = __shfl_xor(sel(im, x[0], x[2]), 32, 64);
-  const T t1 = __shfl_xor(sel(im, x[1], x[3]), 32, 64);
+  T o[4];
+  swap(x, o);
+  const T t0 = sel(im, o[2], o[0]), t1 = sel(im, o[3], o[1]);
   if (own) {
     T2* Zout = Zo + ((long)r * H + k) * g.N + (im ? iL : i0);
     st2c(Zout, T2{sel(im, t0, x[0]), sel(im, x[2], t0)}, T2{sel(im, t1, x[1]), sel(im, x[3], t1)});
@@ -1680,14 +1718,14 @@ hipError_t pc_launch_kpm(const PcTables* pc, const Geom& g, const T* dbar, int o
   return hipGetLastError();
 }
 
-template <typename T, int NT, bool ROW16 = false>
+template <typename T, int NT, bool ROW16 = false, int LAY = kHalves>
 hipError_t pc_launch_kpm_split(const PcTables* pc, const Geom& g, const T* dbar, int op, int nrhs,
                                const typename Cplx<T>::type* Z, typename Cplx<T>::type* Zo,
                                StateSeq& sq, T th, T c4, hipStream_t s) {
   using T2 = typename Cplx<T>::type;
   const StIO io = sq.next();
   const size_t lds = 4 * (size_t)kpm_split_buf<T>(g) * sizeof(T) + kNPMax * sizeof(T2);
-  auto kern = k_kpm_split<T, NT, ROW16>;
+  auto kern = k_kpm_split<T, NT, ROW16, LAY>;
   hipError_t e = allow_lds((const void*)kern, lds);
   if (e != hipSuccess) return e;
   const auto* cf = (const T2*)(sizeof(T) == 8 ? (const void*)pc->coef64 : (const void*)pc->coef32);
@@ -1714,7 +1752,11 @@ hipError_t pc_kpm(const PcTables* pc, const Geom& g, const T* dbar, int op, int 
       return pc_launch_kpm_split<T, 512, true>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
     return pc_launch_kpm<T, 256, true>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
   }
-  if (g.Q <= 64) return pc_launch_kpm_split<T, 128>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
+  if (g.Q <= 32)
+    return pc_launch_kpm_split<T, 64, false, kOneWave>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
+  if (g.Q <= 64)
+    return pc_launch_kpm_split<T, 128, false, kWavePerPart>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4,
+                                                            s);
   if (g.Q <= 128) return pc_launch_kpm_split<T, 256>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
   if (g.Q <= 256) return pc_launch_kpm_split<T, 512>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
   if (g.Q <= 512) return pc_launch_kpm<T, 512>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
