@@ -123,14 +123,19 @@ namespace {
 
 // Residual evaluations after the first that a solve may use (opts.max_outer
 // = 0), and slots between the probes of the blocking driver (opts.chunk = 0):
-// 16, or 8 above 2^20 unknowns per right-hand side.  Once a solve has
-// finished, the rest of its chunk and the chunk queued behind it still run
-// (as idle slots); a probe costs a few microseconds.  At 409 600 unknowns
-// (one or ten right-hand sides) 16 wins; at 1 638 400 the idle slots cost
-// more than the extra probes, and 8 wins.
+// an eighth of the slots enqueued so far, at least 4 and at most 16, or 8
+// above 2^20 unknowns per right-hand side.  Once a solve has finished, the
+// rest of its chunk and the chunk queued behind it still run (as idle slots,
+// about 10 us each), a probe costs about 3 us: the best chunk grows with the
+// solve.  With chunks of 16 throughout, a solve of 40 slots ran 64 (L = 16,
+// Ltau = 160, two FP64 right-hand sides: 2.76 ms per step, of which 0.9 ms
+// idle; 2.0 ms now, the Chebyshev blocks of an idle slot returning at once).
+// At 409 600 unknowns and some 1 900 slots 16 wins over 8; at 1 638 400 an
+// idle slot costs more and 8 wins.
 constexpr int kDefaultMaxOuter = 32;
 constexpr long kDefaultSlotChunk = 16;
 constexpr long kDefaultSlotChunkLarge = 8;
+constexpr long kFirstSlotChunk = 4;
 constexpr long kSlotChunkLargeAbove = 1L << 20;
 
 size_t vbytes(const fph_handle_s* h, size_t elem) { return (size_t)h->g.d * h->max_rhs * elem; }
@@ -852,11 +857,11 @@ extern "C" int pcg_solve_sync(fph_handle_t h, int32_t nrhs, const double* b_dev,
     FPH_CHECK(run.start(s));
     int* open_dev = nullptr;
     FPH_CHECK(hipHostGetDevicePointer((void**)&open_dev, h->open_pin, 0));
-    const long chunk = opts->chunk > 0 ? opts->chunk
-                       : (h->g.d > kSlotChunkLargeAbove ? kDefaultSlotChunkLarge
-                                                         : kDefaultSlotChunk);
+    const long most = h->g.d > kSlotChunkLargeAbove ? kDefaultSlotChunkLarge : kDefaultSlotChunk;
     long enq = 0;
     for (int k = 0; enq < run.total; ++k) {
+      const long chunk = opts->chunk > 0 ? opts->chunk
+                                         : std::min(most, std::max(kFirstSlotChunk, enq / 8));
       const long n = std::min(chunk, run.total - enq);
       FPH_CHECK(run.slots(n, s));
       enq += n;

@@ -711,6 +711,12 @@ k_tinv(Geom g, int H2, const typename Cplx<T>::type* __restrict__ tw,
 
 // ------------------------------------------------------------ KPM kernel
 
+// Whether the solver state says that right-hand side r has finished or is
+// paused, as one scalar load beside the block's other table loads.
+FPH_DEVINL bool state_done(const StIO& io, int r) {
+  return *(const __attribute__((address_space(4))) int*)(uintptr_t)&io.in[r].done != 0;
+}
+
 // Sites around the even plaquette with corner (x0, y0): rows y0-1, y0,
 // y0+1, y0+2 and columns x0-1, x0..x0+1, x0+2 (periodic).  The odd
 // plaquettes of P_B that cover the plaquette's four sites lie in this
@@ -1358,6 +1364,7 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
   dbar += (long)f * g.N;
   const int NP = np[2 * k];
   const T sA = (T)info->s, cA = (T)info->c;
+  const bool idle = io.in != nullptr && !stt && state_done(io, r);
   const T2 c_first = coef[(long)k * kNPMax + threadIdx.x];
   T x[4], db[4];
   {
@@ -1377,6 +1384,7 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
       return;
     }
   }
+  if (idle) return;
   if ((int)threadIdx.x < NP) cfs[threadIdx.x] = c_first;
   for (int m = threadIdx.x + NT; m < NP; m += NT) cfs[m] = coef[(long)k * kNPMax + m];
   __syncthreads();
@@ -1455,6 +1463,7 @@ k_kpm(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
   dbar += (long)f * g.N;
   const int NP = np[2 * k];
   const T sA = (T)info->s, cA = (T)info->c;
+  const bool idle = io.in != nullptr && !stt && state_done(io, r);
   const T2 c_first = coef[(long)k * kNPMax + threadIdx.x];
   T2 x[4], acc[4];
   T db[4];
@@ -1477,6 +1486,7 @@ k_kpm(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
       return;
     }
   }
+  if (idle) return;
   if ((int)threadIdx.x < NP) cfs[threadIdx.x] = c_first;
   for (int m = threadIdx.x + NT; m < NP; m += NT) cfs[m] = coef[(long)k * kNPMax + m];
   __syncthreads();
