@@ -3,14 +3,20 @@
 // Fourier transforms of this file.
 //
 // Grid: vectors are v[tau][i], i = x + L*y; a 3-D transform acts on
-// (tau, y, x) as a spatial 2-D transform per time slice followed by a
-// transform along tau per site.
-//  * Space (k_fft_xy): one workgroup per time slice holds the L x L slice in
-//    LDS and applies direct DFTs of length L along x, then along y.
-//  * Time (k_fft_t): a workgroup holds S sites x Ltau slices in LDS and
-//    applies the two-stage factorisation Ltau = P*Q (P, Q <= 64):
-//      X[k1 + P k2] = sum_q w_Q^{q k2} w_T^{q k1} sum_p x[Q p + q] w_P^{p k1}.
-//    The "twisted" variant multiplies the input by exp(-i pi tau/Ltau) first:
+// (tau, y, x) as a spatial 2-D transform per time slice (k_fft_xy) and a
+// transform along tau per site (k_fft_t).  Both are mixed-radix Stockham
+// FFTs in LDS: radices 8, 5, 4, 3 and 2 as register butterflies, larger prime
+// factors as direct sums, so 5 n log2 n operations per line instead of the
+// n (P + Q) of a two-factor direct form.
+//  * Correlations need only the real part of the last inverse transform, and
+//    for complex sequences z = a1 + i a2, w = b1 + i b2
+//      Re sum_i conj(z_i) w_{i+D} = (a1 * b1)_D + (a2 * b2)_D,
+//    so one complex pair (z, w) carries two real pairs, with no untangling:
+//    the sums over pairs run over half as many transforms.
+//  * The tau pass transforms z and w of the same sites in one workgroup,
+//    loops over the pairs of a launch and keeps sum conj(Z) W in registers:
+//    transformed grids are never written.
+//  * The "twisted" variant multiplies the input by exp(-i pi tau/Ltau) first:
 //    it is the transform, on the Ltau odd frequencies, of a sequence extended
 //    antiperiodically to 2 Ltau slices, which is how the imaginary-time
 //    antiperiodicity of G^ext (Eq. G_def-1) enters; its inverse multiplies
@@ -23,6 +29,7 @@
 #include <cstring>
 
 #include "../../include/holstein_hmc.h"
+#include "fph_common.h"
 #include "fph_internal.h"
 
 namespace {
@@ -46,193 +53,393 @@ __global__ void __launch_bounds__(256) k_meas_twiddles(int n, double2* __restric
   }
 }
 
-enum { IN_COMPLEX = 0, IN_REAL = 1, IN_PRODUCT = 2 };
-enum { OUT_COMPLEX = 0, OUT_REAL = 1 };
+// ------------------------------------------------------------- line FFT
 
-// Spatial DFT of one time slice per workgroup (grid: Ltau).  Input: complex
-// in_c, real a, or the product a*b of two real vectors (slice tau of each).
-// Output: complex, or the real part times `scale`.  Each thread computes G
-// adjacent outputs of a row (or column) at once: one LDS read of an input
-// feeds G independent multiply-add chains.
-template <bool INV, int G>
-__global__ void __launch_bounds__(256)
-k_fft_xy(int L, int N, int in_mode, const double2* __restrict__ in_c, const double* __restrict__ a,
-         const double* __restrict__ b, int out_mode, double scale, double2* __restrict__ out_c,
-         double* __restrict__ out_r, const double2* __restrict__ twL) {
-  extern __shared__ double2 sh[];
-  double2* A = sh;          // [N]
-  double2* B = sh + N;      // [N]
-  double2* tw = sh + 2 * N; // [L]
-  const long base = (long)blockIdx.x * N;
-  for (int e = threadIdx.x; e < L; e += 256) tw[e] = INV ? conjd(twL[e]) : twL[e];
-  for (int e = threadIdx.x; e < N; e += 256) {
-    double2 v;
-    if (in_mode == IN_COMPLEX) v = in_c[base + e];
-    else if (in_mode == IN_REAL) v = make_double2(a[base + e], 0.0);
-    else v = make_double2(a[base + e] * b[base + e], 0.0);
-    A[e] = v;
+constexpr int kMaxStages = 12;
+
+// Stockham plan of one length: radices (an even one first, so that the first
+// stage is a register butterfly) and, per stage, magic numbers that divide by
+// the product Ns of the earlier radices and by n / R.
+struct FftPlan {
+  int n, ns;
+  int R[kMaxStages];
+  unsigned mNs[kMaxStages], mNb[kMaxStages];
+  unsigned mn;
+};
+
+// ceil(2^32 / d): e / d = __umulhi(e, m) while e d < 2^32 (here below 2^24);
+// 0 stands for d = 1.
+unsigned magic(unsigned d) { return d <= 1 ? 0u : (unsigned)(((1ull << 32) + d - 1) / d); }
+__device__ __forceinline__ int udiv(int e, unsigned m) { return m ? (int)__umulhi((unsigned)e, m) : e; }
+
+FftPlan make_plan(int n) {
+  FftPlan p;
+  std::memset(&p, 0, sizeof(p));
+  p.n = n;
+  p.mn = magic(n);
+  int twos = 0, m = n;
+  while (m % 2 == 0) {
+    m /= 2;
+    ++twos;
   }
-  __syncthreads();
-  const int ng = L / G;  // groups of G outputs per row
-  for (int gi = threadIdx.x; gi < ng * L; gi += 256) {  // along x: B[y][kx0 + j]
-    const int y = gi / ng, kx0 = (gi - y * ng) * G;
-    double2 acc[G];
-    int m[G];
-#pragma unroll
-    for (int j = 0; j < G; ++j) {
-      acc[j] = make_double2(0.0, 0.0);
-      m[j] = 0;
+  auto add = [&](int r) { p.R[p.ns++] = r; };
+  while (twos >= 5 || twos == 3) {  // 16 is 4 * 4, not 8 * 2
+    add(8);
+    twos -= 3;
+  }
+  while (twos >= 2) {
+    add(4);
+    twos -= 2;
+  }
+  if (twos) add(2);
+  for (int r : {5, 3})
+    while (m % r == 0) {
+      add(r);
+      m /= r;
     }
-    for (int xx = 0; xx < L; ++xx) {
-      const double2 v = A[y * L + xx];
+  for (int r = 7; m > 1; r += 2)
+    while (m % r == 0) {
+      add(r);
+      m /= r;
+    }
+  int Ns = 1;
+  for (int i = 0; i < p.ns; ++i) {
+    p.mNs[i] = magic(Ns);
+    p.mNb[i] = magic(n / p.R[i]);
+    Ns *= p.R[i];
+  }
+  return p;
+}
+
+template <bool INV>
+__device__ __forceinline__ double2 mul_i(double2 a) {  // a times -i (forward) or +i
+  return INV ? make_double2(-a.y, a.x) : make_double2(a.y, -a.x);
+}
+__device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
+__device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
+
+template <bool INV>
+__device__ __forceinline__ void dft4(double2& v0, double2& v1, double2& v2, double2& v3) {
+  const double2 a = cadd(v0, v2), b = csub(v0, v2), c = cadd(v1, v3), d = mul_i<INV>(csub(v1, v3));
+  v0 = cadd(a, c);
+  v1 = cadd(b, d);
+  v2 = csub(a, c);
+  v3 = csub(b, d);
+}
+
+// In-place DFT of R values, R in {2, 3, 4, 5, 8}.
+template <int R, bool INV>
+__device__ __forceinline__ void dft(double2 (&v)[R]) {
+  if constexpr (R == 2) {
+    const double2 a = v[0];
+    v[0] = cadd(a, v[1]);
+    v[1] = csub(a, v[1]);
+  } else if constexpr (R == 3) {
+    constexpr double kS = 0.86602540378443864676;  // sin(2 pi / 3)
+    const double2 t = cadd(v[1], v[2]), d = csub(v[1], v[2]);
+    const double2 m = make_double2(fma(-0.5, t.x, v[0].x), fma(-0.5, t.y, v[0].y));
+    const double2 q = mul_i<INV>(make_double2(kS * d.x, kS * d.y));
+    v[0] = cadd(v[0], t);
+    v[1] = cadd(m, q);
+    v[2] = csub(m, q);
+  } else if constexpr (R == 4) {
+    dft4<INV>(v[0], v[1], v[2], v[3]);
+  } else if constexpr (R == 5) {
+    constexpr double c1 = 0.30901699437494742410, c2 = -0.80901699437494742410;  // cos(2 pi k / 5)
+    constexpr double s1 = 0.95105651629515357212, s2 = 0.58778525229247312917;   // sin(2 pi k / 5)
+    const double2 t1 = cadd(v[1], v[4]), d1 = csub(v[1], v[4]);
+    const double2 t2 = cadd(v[2], v[3]), d2 = csub(v[2], v[3]);
+    const double2 m1 = make_double2(fma(c2, t2.x, fma(c1, t1.x, v[0].x)), fma(c2, t2.y, fma(c1, t1.y, v[0].y)));
+    const double2 m2 = make_double2(fma(c1, t2.x, fma(c2, t1.x, v[0].x)), fma(c1, t2.y, fma(c2, t1.y, v[0].y)));
+    const double2 q1 = mul_i<INV>(make_double2(fma(s2, d2.x, s1 * d1.x), fma(s2, d2.y, s1 * d1.y)));
+    const double2 q2 = mul_i<INV>(make_double2(fma(-s1, d2.x, s2 * d1.x), fma(-s1, d2.y, s2 * d1.y)));
+    v[0] = cadd(v[0], cadd(t1, t2));
+    v[1] = cadd(m1, q1);
+    v[4] = csub(m1, q1);
+    v[2] = cadd(m2, q2);
+    v[3] = csub(m2, q2);
+  } else {
+    static_assert(R == 8, "radix");
+    constexpr double kH = 0.70710678118654752440;
+    dft4<INV>(v[0], v[2], v[4], v[6]);
+    dft4<INV>(v[1], v[3], v[5], v[7]);
+    const double2 i3 = mul_i<INV>(v[3]), i7 = mul_i<INV>(v[7]);
+    const double2 o1 = make_double2(kH * (v[3].x + i3.x), kH * (v[3].y + i3.y));
+    const double2 o2 = mul_i<INV>(v[5]);
+    const double2 o3 = make_double2(kH * (i7.x - v[7].x), kH * (i7.y - v[7].y));
+    const double2 e0 = v[0], e1 = v[2], e2 = v[4], e3 = v[6], o0 = v[1];
+    v[0] = cadd(e0, o0);
+    v[4] = csub(e0, o0);
+    v[1] = cadd(e1, o1);
+    v[5] = csub(e1, o1);
+    v[2] = cadd(e2, o2);
+    v[6] = csub(e2, o2);
+    v[3] = cadd(e3, o3);
+    v[7] = csub(e3, o3);
+  }
+}
+
+// One Stockham stage of radix R over `items` = (n / R) lines' butterflies:
+// split(e, s, j) gives item e's line s and butterfly j; ld(i, s) and
+// st(i, s, v) read and write entry i of line s; tw[m] = w_n^m (conjugated for
+// INV).  Butterfly j, k = j mod Ns: inputs j + r n/R times w^{k r n/(Ns R)},
+// outputs (j - k) R + k + r Ns.
+template <int R, bool INV, int NT, class Split, class Ld, class St>
+__device__ __forceinline__ void fft_stage(int n, int Ns, unsigned mNs, int items, const double2* tw,
+                                          const Split& split, const Ld& ld, const St& st) {
+  const int nb = n / R, ts = nb / Ns;
+  for (int e = threadIdx.x; e < items; e += NT) {
+    int s, j;
+    split(e, s, j);
+    const int k = j - udiv(j, mNs) * Ns;
+    double2 v[R];
 #pragma unroll
-      for (int j = 0; j < G; ++j) {
-        acc[j] = cfma(v, tw[m[j]], acc[j]);
-        m[j] += kx0 + j;
-        if (m[j] >= L) m[j] -= L;
+    for (int r = 0; r < R; ++r) v[r] = ld(j + r * nb, s);
+    if (Ns > 1) {
+#pragma unroll
+      for (int r = 1; r < R; ++r) v[r] = cmul(v[r], tw[k * r * ts]);
+    }
+    dft<R, INV>(v);
+    const int o = (j - k) * R + k;
+#pragma unroll
+    for (int r = 0; r < R; ++r) st(o + r * Ns, s, v[r]);
+  }
+}
+
+// The same for any radix, one output at a time by its direct sum (prime
+// factors above 5).
+template <int NT, class Split, class Ld, class St>
+__device__ __forceinline__ void fft_stage_any(int R, int n, int Ns, unsigned mNs, int items, const double2* tw,
+                                              const Split& split, const Ld& ld, const St& st) {
+  const int nb = n / R, ts = nb / Ns;
+  for (int e = threadIdx.x; e < items * R; e += NT) {
+    const int r = e / items;
+    int s, j;
+    split(e - r * items, s, j);
+    const int k = j - udiv(j, mNs) * Ns;
+    const int step = (k * ts + r * nb) % n;
+    double2 acc = make_double2(0.0, 0.0);
+    int m = 0;
+    for (int q = 0; q < R; ++q) {
+      acc = cfma(ld(j + q * nb, s), tw[m], acc);
+      m += step;
+      if (m >= n) m -= n;
+    }
+    st((j - k) * R + k + r * Ns, s, acc);
+  }
+}
+
+template <bool INV, int NT, class Split, class Ld, class St>
+__device__ __forceinline__ void fft_stage_sel(int R, int n, int Ns, unsigned mNs, int items, const double2* tw,
+                                              const Split& split, const Ld& ld, const St& st) {
+  switch (R) {
+    case 8: fft_stage<8, INV, NT>(n, Ns, mNs, items, tw, split, ld, st); break;
+    case 5: fft_stage<5, INV, NT>(n, Ns, mNs, items, tw, split, ld, st); break;
+    case 4: fft_stage<4, INV, NT>(n, Ns, mNs, items, tw, split, ld, st); break;
+    case 3: fft_stage<3, INV, NT>(n, Ns, mNs, items, tw, split, ld, st); break;
+    case 2: fft_stage<2, INV, NT>(n, Ns, mNs, items, tw, split, ld, st); break;
+    default: fft_stage_any<NT>(R, n, Ns, mNs, items, tw, split, ld, st); break;
+  }
+}
+
+// ------------------------------------------------------------ space pass
+
+// One grid of a space launch.  Input: complex `in`, or a b + i c d of real
+// vectors (b or d null: that factor is 1; c null: no imaginary part).
+// Output: complex `out`, or the real part times `scale` in `outr`.
+struct XyJob {
+  const double2* in;
+  const double *a, *b, *c, *d;
+  double2* out;
+  double* outr;
+};
+constexpr int kGrids = 8;  // grids per launch, and complex grids of workspace
+struct XyArgs {
+  XyJob job[kGrids];
+  int njob;
+  double scale;
+};
+
+// Spatial transform, one workgroup per (time slice, grid).  Stages along y
+// first (lanes along x: the first stage reads rows from memory straight into
+// its butterflies), then along x (the last stage writes rows from its
+// butterflies, lanes along its contiguous outputs).  LDS rows are L + 1 long,
+// odd, so that lanes along y do not meet on a bank.  The grids of a slice are
+// numbered next to each other on one XCD: they read the same vectors.
+// Bound by its traffic from the caches (reads of up to four real vectors and
+// one complex write per grid) and the chain of stages: 43 us for eight grids
+// of 400 x 32 x 32, 14-15 us each with direct DFTs and one grid per launch.
+template <bool INV, int NT>
+__global__ void __launch_bounds__(NT)
+k_fft_xy(int L, int N, FftPlan pl, XyArgs A, const double2* __restrict__ twL) {
+  extern __shared__ double2 sh[];
+  const int LP = L + 1;
+  double2* tw = sh;
+  double2* buf = sh + L;
+  const int nbuf = L * LP;
+  const int logical = fph::xcd_contiguous(blockIdx.x, gridDim.x);
+  const int slice = logical / A.njob;
+  const XyJob jb = A.job[logical - slice * A.njob];
+  const long base = (long)slice * N;
+  for (int e = threadIdx.x; e < L; e += NT) tw[e] = INV ? conjd(twL[e]) : twL[e];
+  const int ns = pl.ns;
+  int cur = 0;
+  for (int pass = 0; pass < 2; ++pass) {  // 0: along y, 1: along x
+    const int sn = pass ? 1 : LP, sb = pass ? LP : 1;
+    int Ns = 1;
+    for (int i = 0; i < ns; ++i) {
+      const int R = pl.R[i];
+      const bool first = pass == 0 && i == 0, last = pass == 1 && i == ns - 1;
+      const double2* src = buf + cur * nbuf;
+      double2* dst = buf + (cur ^ 1) * nbuf;
+      const unsigned mn = pl.mn, mnb = pl.mNb[i];
+      const int nb = L / R;
+      auto split = [&](int e, int& s, int& j) {
+        if (last) {
+          s = udiv(e, mnb);
+          j = e - s * nb;
+        } else {
+          j = udiv(e, mn);
+          s = e - j * L;
+        }
+      };
+      auto ld = [&](int k, int s) {
+        if (!first) return src[k * sn + s * sb];
+        const long o = base + (long)k * L + s;  // row y = k, column x = s
+        if (jb.in) return jb.in[o];
+        double re = jb.a[o], im = 0.0;
+        if (jb.b) re *= jb.b[o];
+        if (jb.c) im = jb.d ? jb.c[o] * jb.d[o] : jb.c[o];
+        return make_double2(re, im);
+      };
+      auto st = [&](int k, int s, double2 v) {
+        if (!last) {
+          dst[k * sn + s * sb] = v;
+          return;
+        }
+        const long o = base + (long)s * L + k;  // row y = s, column x = k
+        if (jb.outr) jb.outr[o] = A.scale * v.x;
+        else jb.out[o] = v;
+      };
+      if (!first || Ns > 1) __syncthreads();
+      fft_stage_sel<INV, NT>(R, L, Ns, pl.mNs[i], nb * L, tw, split, ld, st);
+      Ns *= R;
+      cur ^= 1;
+    }
+  }
+}
+
+// ------------------------------------------------------------- time pass
+
+enum { T_PLAIN = 0, T_CROSS = 1, T_PREFIX = 2 };
+constexpr int kTNT = 512;          // threads of a time workgroup
+constexpr int kTElems = 2048;      // its most elements, T * S
+constexpr int kTE = kTElems / kTNT;
+
+// T_PLAIN: out[0] = transform of z[0][0].  T_CROSS, set y = blockIdx.y: out[y]
+// += sum_p conj(Z_p) W_p, p < np.  T_PREFIX: for p < np in order out[0] +=
+// conj(run) Z_p, run += Z_p.  first: out and run start from zero.
+struct TArgs {
+  const double2* z[2][kGrids];
+  const double2* w[2][kGrids];
+  double2* out[2];
+  double2* run;
+  int np, first, twist;
+};
+
+// Transform along tau of S = 2^ls sites per workgroup (grid: N/S tiles, sets).
+// tw2[m] = exp(-i pi m / T), m < 2T.  The first stage reads its inputs from
+// memory; the sums over pairs stay in registers, one element per thread and
+// step of kTNT.  Eight grids of 400 x 32 x 32 with their products: 29 us; the
+// two-factor direct form took 17 us per grid and 5 us per product pass.
+template <bool INV, int MODE>
+__global__ void __launch_bounds__(kTNT)
+k_fft_t(int N, int ls, FftPlan pl, TArgs A, const double2* __restrict__ tw2) {
+  extern __shared__ double2 sh[];
+  const int T = pl.n, S = 1 << ls, nel = T << ls;
+  double2* tw = sh;
+  double2* buf = sh + T;
+  const int set = blockIdx.y;
+  const int site0 = fph::xcd_contiguous(blockIdx.x, gridDim.x) << ls;
+  for (int e = threadIdx.x; e < T; e += kTNT) tw[e] = INV ? conjd(tw2[2 * e]) : tw2[2 * e];
+  __syncthreads();
+  auto split = [&](int e, int& s, int& j) {
+    s = e & (S - 1);
+    j = e >> ls;
+  };
+  // Transform of `in`; returns the buffer that holds it ([tau][s]), after a barrier.
+  auto transform = [&](const double2* in) {
+    int cur = 0, Ns = 1;
+    for (int i = 0; i < pl.ns; ++i) {
+      const int R = pl.R[i];
+      const double2* src = buf + cur * nel;
+      double2* dst = buf + (cur ^ 1) * nel;
+      auto ld = [&](int k, int s) {
+        if (i > 0) return src[(k << ls) + s];
+        double2 v = in[(long)k * N + site0 + s];
+        if (!INV && A.twist) v = cmul(v, tw2[k]);
+        return v;
+      };
+      auto st = [&](int k, int s, double2 v) { dst[(k << ls) + s] = v; };
+      fft_stage_sel<INV, kTNT>(R, T, Ns, pl.mNs[i], (T / R) << ls, tw, split, ld, st);
+      __syncthreads();
+      Ns *= R;
+      cur ^= 1;
+    }
+    return (const double2*)(buf + cur * nel);
+  };
+  auto at = [&](int e) { return (long)(e >> ls) * N + site0 + (e & (S - 1)); };
+  if constexpr (MODE == T_PLAIN) {
+    const double2* x = transform(A.z[0][0]);
+    for (int e = threadIdx.x; e < nel; e += kTNT) {
+      double2 v = x[e];
+      if (INV && A.twist) v = cmul(v, conjd(tw2[e >> ls]));
+      A.out[0][at(e)] = v;
+    }
+  } else {
+    double2 acc[kTE], keep[kTE];  // keep: Z_p (T_CROSS) or the running sum (T_PREFIX)
+    double2* out = A.out[set];
+#pragma unroll
+    for (int i = 0; i < kTE; ++i) {
+      const int e = threadIdx.x + i * kTNT;
+      acc[i] = keep[i] = make_double2(0.0, 0.0);
+      if (e < nel && !A.first) {
+        acc[i] = out[at(e)];
+        if (MODE == T_PREFIX) keep[i] = A.run[at(e)];
       }
     }
+    for (int p = 0; p < A.np; ++p) {
+      const double2* x = transform(A.z[set][p]);
+      if constexpr (MODE == T_CROSS) {
 #pragma unroll
-    for (int j = 0; j < G; ++j) B[y * L + kx0 + j] = acc[j];
-  }
-  __syncthreads();
-  for (int gi = threadIdx.x; gi < ng * L; gi += 256) {  // along y: out[ky][kx0 + j]
-    const int ky = gi / ng, kx0 = (gi - ky * ng) * G;
-    double2 acc[G];
+        for (int i = 0; i < kTE; ++i) keep[i] = x[min((int)threadIdx.x + i * kTNT, nel - 1)];
+        __syncthreads();
+        x = transform(A.w[set][p]);
+      }
 #pragma unroll
-    for (int j = 0; j < G; ++j) acc[j] = make_double2(0.0, 0.0);
-    int m = 0;
-    for (int y = 0; y < L; ++y) {
-      const double2 w = tw[m];
-#pragma unroll
-      for (int j = 0; j < G; ++j) acc[j] = cfma(B[y * L + kx0 + j], w, acc[j]);
-      m += ky;
-      if (m >= L) m -= L;
+      for (int i = 0; i < kTE; ++i) {
+        const double2 v = x[min((int)threadIdx.x + i * kTNT, nel - 1)];
+        acc[i] = cfma(conjd(keep[i]), v, acc[i]);
+        if constexpr (MODE == T_PREFIX) keep[i] = cadd(keep[i], v);
+      }
+      __syncthreads();
     }
-    const long o = base + (long)ky * L + kx0;
 #pragma unroll
-    for (int j = 0; j < G; ++j) {
-      if (out_mode == OUT_COMPLEX) out_c[o + j] = acc[j];
-      else out_r[o + j] = scale * acc[j].x;
+    for (int i = 0; i < kTE; ++i) {
+      const int e = threadIdx.x + i * kTNT;
+      if (e < nel) {
+        out[at(e)] = acc[i];
+        if (MODE == T_PREFIX) A.run[at(e)] = keep[i];
+      }
     }
   }
 }
 
-// Transform along tau of S sites per workgroup (grid: N/S), Ltau = P*Q.
-// in/out complex [Ltau][N]; twist as described at the top of the file.  A
-// thread computes one output row for all S sites: one twiddle feeds S
-// independent multiply-add chains.
-template <bool INV, int S>
-__global__ void __launch_bounds__(256)
-k_fft_t(int N, int T, int P, int Q, int twist, const double2* __restrict__ in,
-        double2* __restrict__ out, const double2* __restrict__ twT) {
-  extern __shared__ double2 sh[];
-  double2* X = sh;              // [T][S]
-  double2* Y = sh + T * S;      // [T][S]
-  double2* tw = sh + 2 * T * S; // [T]
-  const int site0 = blockIdx.x * S;
-  for (int e = threadIdx.x; e < T; e += 256) tw[e] = INV ? conjd(twT[e]) : twT[e];
-  for (int e = threadIdx.x; e < T * S; e += 256) {
-    const int s = e % S, tau = e / S;
-    double2 v = in[(long)tau * N + site0 + s];
-    if (twist && !INV) {
-      double sn, cs;
-      sincospi((double)tau / T, &sn, &cs);
-      v = cmul(v, make_double2(cs, -sn));
-    }
-    X[e] = v;
-  }
-  __syncthreads();
-  // stage A: Y[q P + k1] = w_T^{q k1} sum_p X[Q p + q] w_P^{p k1},  w_P^j = tw[Q j]
-  for (int r = threadIdx.x; r < T; r += 256) {
-    const int k1 = r % P, q = r / P;
-    double2 acc[S];
-#pragma unroll
-    for (int s = 0; s < S; ++s) acc[s] = make_double2(0.0, 0.0);
-    int m = 0;
-    const int step = (Q * k1) % T;
-    for (int p = 0; p < P; ++p) {
-      const double2 w = tw[m];
-      const double2* xr = X + (Q * p + q) * S;
-#pragma unroll
-      for (int s = 0; s < S; ++s) acc[s] = cfma(xr[s], w, acc[s]);
-      m += step;
-      if (m >= T) m -= T;
-    }
-    const double2 post = tw[(q * k1) % T];
-#pragma unroll
-    for (int s = 0; s < S; ++s) Y[r * S + s] = cmul(acc[s], post);
-  }
-  __syncthreads();
-  // stage B: out[k1 + P k2] = sum_q Y[q P + k1] w_Q^{q k2},  w_Q^j = tw[P j]
-  for (int k = threadIdx.x; k < T; k += 256) {
-    const int k1 = k % P, k2 = k / P;
-    double2 acc[S];
-#pragma unroll
-    for (int s = 0; s < S; ++s) acc[s] = make_double2(0.0, 0.0);
-    int m = 0;
-    const int step = (P * k2) % T;
-    for (int q = 0; q < Q; ++q) {
-      const double2 w = tw[m];
-      const double2* yr = Y + (q * P + k1) * S;
-#pragma unroll
-      for (int s = 0; s < S; ++s) acc[s] = cfma(yr[s], w, acc[s]);
-      m += step;
-      if (m >= T) m -= T;
-    }
-    double2 tk = make_double2(1.0, 0.0);
-    if (twist && INV) {
-      double sn, cs;
-      sincospi((double)k / T, &sn, &cs);
-      tk = make_double2(cs, sn);
-    }
-#pragma unroll
-    for (int s = 0; s < S; ++s) out[(long)k * N + site0 + s] = cmul(acc[s], tk);
-  }
-}
-
-// acc += conj(A) B over n values.
-__global__ void __launch_bounds__(256)
-k_acc_cross(long n, const double2* __restrict__ A, const double2* __restrict__ B, double2* __restrict__ acc) {
-  for (long k = blockIdx.x * 256L + threadIdx.x; k < n; k += (long)gridDim.x * 256)
-    acc[k] = cfma(conjd(A[k]), B[k], acc[k]);
-}
-
-// acc += conj(S) B; S += B (running sum over earlier vectors).
-__global__ void __launch_bounds__(256)
-k_acc_prefix(long n, double2* __restrict__ S, const double2* __restrict__ B, double2* __restrict__ acc) {
-  for (long k = blockIdx.x * 256L + threadIdx.x; k < n; k += (long)gridDim.x * 256) {
-    const double2 b = B[k];
-    const double2 s = S[k];
-    acc[k] = cfma(conjd(s), b, acc[k]);
-    S[k] = make_double2(s.x + b.x, s.y + b.y);
-  }
-}
-
-__global__ void __launch_bounds__(256) k_zero2(long n, double2* __restrict__ p) {
-  for (long k = blockIdx.x * 256L + threadIdx.x; k < n; k += (long)gridDim.x * 256)
-    p[k] = make_double2(0.0, 0.0);
-}
-
-int grid_for(long n) {
-  const long b = (n + 255) / 256;
-  return (int)(b < 1 ? 1 : (b > 4096 ? 4096 : b));
-}
-
-// Ltau = P*Q with P <= Q <= 64 and P + Q smallest; false if none.
-bool factor_T(int T, int* P, int* Q) {
-  int best = -1;
-  for (int p = 1; p <= 64; ++p) {
-    if (T % p) continue;
-    const int q = T / p;
-    if (q > 64 || p > q) continue;
-    if (best < 0 || p + q < *P + *Q) {
-      *P = p;
-      *Q = q;
-      best = p;
-    }
-  }
-  return best > 0;
+// Whether Ltau = P*Q with P, Q <= 64 (the range of lattices this file takes).
+bool slices_ok(int T) {
+  for (int p = 1; p <= 64; ++p)
+    if (T % p == 0 && T / p <= 64) return T <= kTElems;
+  return false;
 }
 
 }  // namespace
@@ -241,84 +448,63 @@ struct fph_meas_s {
   fph_handle_t h;
   fph_lattice_t lat;
   int max_rhs;
-  int L, N, T, P, Q, S;
+  int L, N, T, ls;
   long d;
-  double2 *twL, *twT;
-  double2 *A, *B, *tmp, *acc, *acc2, *run;  // complex grids [Ltau][N]
-  double* bvec;                              // max_rhs real vectors
+  FftPlan pL, pT;
+  double2 *twL, *tw2;  // exp(-2 pi i m / L), exp(-i pi m / Ltau)
+  double2* grid[kGrids];  // complex grids [Ltau][N]
+  double2 *acc, *acc2, *run;
+  double* bvec;           // max_rhs real vectors
   size_t lds_xy, lds_t;
 };
 
 namespace {
 
-hipError_t launch_xy(const fph_meas_s* m, bool inv, int in_mode, const double2* in_c, const double* a,
-                     const double* b, int out_mode, double scale, double2* out_c, double* out_r,
-                     hipStream_t s) {
-  const bool g4 = (m->L % 4) == 0;
-  if (!inv && g4)
-    hipLaunchKernelGGL((k_fft_xy<false, 4>), dim3(m->T), dim3(256), m->lds_xy, s, m->L, m->N, in_mode, in_c,
-                       a, b, out_mode, scale, out_c, out_r, (const double2*)m->twL);
-  else if (!inv)
-    hipLaunchKernelGGL((k_fft_xy<false, 2>), dim3(m->T), dim3(256), m->lds_xy, s, m->L, m->N, in_mode, in_c,
-                       a, b, out_mode, scale, out_c, out_r, (const double2*)m->twL);
-  else if (g4)
-    hipLaunchKernelGGL((k_fft_xy<true, 4>), dim3(m->T), dim3(256), m->lds_xy, s, m->L, m->N, in_mode, in_c,
-                       a, b, out_mode, scale, out_c, out_r, (const double2*)m->twL);
-  else
-    hipLaunchKernelGGL((k_fft_xy<true, 2>), dim3(m->T), dim3(256), m->lds_xy, s, m->L, m->N, in_mode, in_c,
-                       a, b, out_mode, scale, out_c, out_r, (const double2*)m->twL);
-  return hipGetLastError();
-}
-
-template <bool INV>
-hipError_t launch_t_inv(const fph_meas_s* m, int twist, const double2* in, double2* out, hipStream_t s) {
-  dim3 g(m->N / m->S);
-#define FPH_T_CASE(SS)                                                                              \
-  case SS:                                                                                          \
-    hipLaunchKernelGGL((k_fft_t<INV, SS>), g, dim3(256), m->lds_t, s, m->N, m->T, m->P, m->Q, twist, \
-                       in, out, (const double2*)m->twT);                                          \
-    break;
-  switch (m->S) {
-    FPH_T_CASE(1)
-    FPH_T_CASE(2)
-    FPH_T_CASE(4)
-    FPH_T_CASE(8)
-    FPH_T_CASE(16)
-    default: return hipErrorInvalidValue;
+// Threads of a space workgroup: one radix-4 or two radix-8 butterflies each.
+hipError_t launch_xy(const fph_meas_s* m, bool inv, const XyArgs& A, hipStream_t s) {
+  const dim3 g(m->T * A.njob);
+  if (m->N <= 1024) {
+    auto k = inv ? k_fft_xy<true, 256> : k_fft_xy<false, 256>;
+    hipLaunchKernelGGL(k, g, dim3(256), m->lds_xy, s, m->L, m->N, m->pL, A, (const double2*)m->twL);
+  } else {
+    auto k = inv ? k_fft_xy<true, 512> : k_fft_xy<false, 512>;
+    hipLaunchKernelGGL(k, g, dim3(512), m->lds_xy, s, m->L, m->N, m->pL, A, (const double2*)m->twL);
   }
-#undef FPH_T_CASE
   return hipGetLastError();
 }
 
-hipError_t launch_t(const fph_meas_s* m, bool inv, int twist, const double2* in, double2* out, hipStream_t s) {
-  return inv ? launch_t_inv<true>(m, twist, in, out, s) : launch_t_inv<false>(m, twist, in, out, s);
+template <bool INV, int MODE>
+hipError_t launch_t(const fph_meas_s* m, int sets, const TArgs& A, hipStream_t s) {
+  hipLaunchKernelGGL((k_fft_t<INV, MODE>), dim3(m->N >> m->ls, sets), dim3(kTNT), m->lds_t, s, m->N, m->ls,
+                     m->pT, A, (const double2*)m->tw2);
+  return hipGetLastError();
 }
 
-// Forward 3-D transform of a real input (in_mode IN_REAL / IN_PRODUCT) into `out`.
-hipError_t fwd3(const fph_meas_s* m, int in_mode, const double* a, const double* b, int twist,
-                double2* out, hipStream_t s) {
-  hipError_t e = launch_xy(m, false, in_mode, nullptr, a, b, OUT_COMPLEX, 0.0, m->tmp, nullptr, s);
-  if (e != hipSuccess) return e;
-  return launch_t(m, false, twist, m->tmp, out, s);
+TArgs plain_t(const double2* in, double2* out, int twist) {
+  TArgs A;
+  std::memset(&A, 0, sizeof(A));
+  A.z[0][0] = in;
+  A.out[0] = out;
+  A.twist = twist;
+  return A;
+}
+
+XyArgs one_xy(const XyJob& j, double scale) {
+  XyArgs A;
+  std::memset(&A, 0, sizeof(A));
+  A.job[0] = j;
+  A.njob = 1;
+  A.scale = scale;
+  return A;
 }
 
 // Inverse 3-D transform of `in` (complex), real part times `scale` into out_r.
 hipError_t inv3(const fph_meas_s* m, const double2* in, int twist, double scale, double* out_r,
                 hipStream_t s) {
-  hipError_t e = launch_t(m, true, twist, in, m->tmp, s);
+  hipError_t e = launch_t<true, T_PLAIN>(m, 1, plain_t(in, m->grid[0], twist), s);
   if (e != hipSuccess) return e;
-  return launch_xy(m, true, IN_COMPLEX, m->tmp, nullptr, nullptr, OUT_REAL, scale, nullptr, out_r, s);
-}
-
-hipError_t zero2(const fph_meas_s* m, double2* p, hipStream_t s) {
-  hipLaunchKernelGGL(k_zero2, dim3(grid_for(m->d)), dim3(256), 0, s, m->d, p);
-  return hipGetLastError();
-}
-
-hipError_t cross(const fph_meas_s* m, double2* acc, hipStream_t s) {
-  hipLaunchKernelGGL(k_acc_cross, dim3(grid_for(m->d)), dim3(256), 0, s, m->d, (const double2*)m->A,
-                     (const double2*)m->B, acc);
-  return hipGetLastError();
+  return launch_xy(m, true, one_xy(XyJob{m->grid[0], nullptr, nullptr, nullptr, nullptr, nullptr, out_r}, scale),
+                   s);
 }
 
 }  // namespace
@@ -340,7 +526,7 @@ extern "C" {
 int fph_meas_destroy(fph_meas_t m) {
   if (m == nullptr) return FPH_E_NULL;
   (void)hipDeviceSynchronize();
-  void* ptrs[] = {m->twL, m->twT, m->A, m->B, m->tmp, m->acc, m->acc2, m->run, m->bvec};
+  void* ptrs[] = {m->twL, m->tw2, m->grid[0], m->acc, m->acc2, m->run, m->bvec};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   delete m;
@@ -353,18 +539,15 @@ int fph_meas_create(fph_meas_t* out, fph_handle_t h, void* stream) {
   fph_lattice_t lat;
   int32_t max_rhs = 0;
   MEAS_CALL(fph_get_lattice(h, &lat, &max_rhs));
-  int P = 0, Q = 0;
-  if (!factor_T(lat.Ltau, &P, &Q)) return FPH_E_LATTICE;
+  if (!slices_ok(lat.Ltau)) return FPH_E_LATTICE;
   const int N = lat.L * lat.L;
-  const size_t lds_xy = (size_t)(2 * N + lat.L) * sizeof(double2);
+  const size_t lds_xy = (size_t)(2 * lat.L * (lat.L + 1) + lat.L) * sizeof(double2);
   if (lds_xy > (size_t)kLdsMax) return FPH_E_LATTICE;
-  // sites per workgroup along tau: a power of two dividing N, within the LDS
-  // budget, and small enough to give at least 256 workgroups where possible
-  int S = 16;
-  while (S > 1 && ((size_t)(2 * S + 0) * lat.Ltau * sizeof(double2) + lat.Ltau * sizeof(double2) >
-                       (size_t)kLdsMax || N / S < 256 || N % S))
-    S /= 2;
-  const size_t lds_t = (size_t)(2 * S * lat.Ltau + lat.Ltau) * sizeof(double2);
+  // Sites per time workgroup: a power of two dividing N, at most 8 and kTElems
+  // elements, narrower while that leaves fewer than 256 tiles (not below 2).
+  int ls = 3;
+  while (ls > 0 && ((lat.Ltau << ls) > kTElems || N % (1 << ls) || (ls > 1 && (N >> ls) < 256))) --ls;
+  const size_t lds_t = (size_t)(2 * (lat.Ltau << ls) + lat.Ltau) * sizeof(double2);
   if (lds_t > (size_t)kLdsMax) return FPH_E_LATTICE;
   fph_meas_s* m = new fph_meas_s();
   std::memset(m, 0, sizeof(*m));
@@ -374,33 +557,29 @@ int fph_meas_create(fph_meas_t* out, fph_handle_t h, void* stream) {
   m->L = lat.L;
   m->N = N;
   m->T = lat.Ltau;
-  m->P = P;
-  m->Q = Q;
-  m->S = S;
+  m->ls = ls;
   m->d = (long)N * lat.Ltau;
+  m->pL = make_plan(lat.L);
+  m->pT = make_plan(lat.Ltau);
   m->lds_xy = lds_xy;
   m->lds_t = lds_t;
   hipError_t e = hipSuccess;
 #define ALLOC(ptr, bytes) \
   if (e == hipSuccess) e = hipMalloc((void**)&(ptr), (bytes));
   ALLOC(m->twL, m->L * sizeof(double2));
-  ALLOC(m->twT, m->T * sizeof(double2));
-  ALLOC(m->A, m->d * sizeof(double2));
-  ALLOC(m->B, m->d * sizeof(double2));
-  ALLOC(m->tmp, m->d * sizeof(double2));
+  ALLOC(m->tw2, 2 * m->T * sizeof(double2));
+  ALLOC(m->grid[0], kGrids * m->d * sizeof(double2));
+  for (int k = 1; k < kGrids; ++k) m->grid[k] = m->grid[0] + k * m->d;
   ALLOC(m->acc, m->d * sizeof(double2));
   ALLOC(m->acc2, m->d * sizeof(double2));
   ALLOC(m->run, m->d * sizeof(double2));
   ALLOC(m->bvec, (size_t)max_rhs * m->d * sizeof(double));
 #undef ALLOC
   {
-    const void* fns[] = {(const void*)k_fft_xy<false, 2>, (const void*)k_fft_xy<false, 4>,
-                         (const void*)k_fft_xy<true, 2>,  (const void*)k_fft_xy<true, 4>,
-                         (const void*)k_fft_t<false, 1>,  (const void*)k_fft_t<false, 2>,
-                         (const void*)k_fft_t<false, 4>,  (const void*)k_fft_t<false, 8>,
-                         (const void*)k_fft_t<false, 16>, (const void*)k_fft_t<true, 1>,
-                         (const void*)k_fft_t<true, 2>,   (const void*)k_fft_t<true, 4>,
-                         (const void*)k_fft_t<true, 8>,   (const void*)k_fft_t<true, 16>};
+    const void* fns[] = {(const void*)k_fft_xy<false, 256>,    (const void*)k_fft_xy<true, 256>,
+                         (const void*)k_fft_xy<false, 512>,    (const void*)k_fft_xy<true, 512>,
+                         (const void*)k_fft_t<false, T_PLAIN>, (const void*)k_fft_t<true, T_PLAIN>,
+                         (const void*)k_fft_t<false, T_CROSS>, (const void*)k_fft_t<false, T_PREFIX>};
     for (const void* f : fns)
       if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsMax);
   }
@@ -410,7 +589,7 @@ int fph_meas_create(fph_meas_t* out, fph_handle_t h, void* stream) {
     e = hipGetLastError();
   }
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_meas_twiddles, dim3((m->T + 255) / 256), dim3(256), 0, s, m->T, m->twT);
+    hipLaunchKernelGGL(k_meas_twiddles, dim3((2 * m->T + 255) / 256), dim3(256), 0, s, 2 * m->T, m->tw2);
     e = hipGetLastError();
   }
   if (e != hipSuccess) {
@@ -429,12 +608,14 @@ int meas_fft(fph_meas_t m, int32_t inverse, int32_t twist, const double* in_dev,
   const double2* in = (const double2*)in_dev;
   double2* out = (double2*)out_dev;
   const int tw = twist != 0;
+  const XyJob job{inverse ? m->grid[0] : in, nullptr, nullptr, nullptr, nullptr, inverse ? out : m->grid[0],
+                  nullptr};
   if (!inverse) {
-    MEAS_CHECK(launch_xy(m, false, IN_COMPLEX, in, nullptr, nullptr, OUT_COMPLEX, 0.0, m->tmp, nullptr, s));
-    MEAS_CHECK(launch_t(m, false, tw, m->tmp, out, s));
+    MEAS_CHECK(launch_xy(m, false, one_xy(job, 0.0), s));
+    MEAS_CHECK((launch_t<false, T_PLAIN>(m, 1, plain_t(m->grid[0], out, tw), s)));
   } else {
-    MEAS_CHECK(launch_t(m, true, tw, in, m->tmp, s));
-    MEAS_CHECK(launch_xy(m, true, IN_COMPLEX, m->tmp, nullptr, nullptr, OUT_COMPLEX, 0.0, out, nullptr, s));
+    MEAS_CHECK((launch_t<true, T_PLAIN>(m, 1, plain_t(in, m->grid[0], tw), s)));
+    MEAS_CHECK(launch_xy(m, true, one_xy(job, 0.0), s));
   }
   return FPH_OK;
 }
@@ -459,11 +640,27 @@ int green_average(fph_meas_t m, int32_t nvec, const double* xi_dev, const double
   if (m == nullptr || xi_dev == nullptr || gxi_dev == nullptr || out_dev == nullptr) return FPH_E_NULL;
   if (nvec < 1) return FPH_E_NRHS;
   hipStream_t s = (hipStream_t)stream;
-  MEAS_CHECK(zero2(m, m->acc, s));
-  for (int n = 0; n < nvec; ++n) {
-    MEAS_CHECK(fwd3(m, IN_REAL, xi_dev + (long)n * m->d, nullptr, 1, m->A, s));
-    MEAS_CHECK(fwd3(m, IN_REAL, gxi_dev + (long)n * m->d, nullptr, 1, m->B, s));
-    MEAS_CHECK(cross(m, m->acc, s));
+  // Two vectors per complex pair, kGrids / 2 pairs per launch.
+  const long d = m->d;
+  for (int n = 0; n < nvec;) {
+    XyArgs X;
+    TArgs A;
+    std::memset(&X, 0, sizeof(X));
+    std::memset(&A, 0, sizeof(A));
+    A.first = n == 0;
+    A.twist = 1;
+    A.out[0] = m->acc;
+    for (; n < nvec && A.np < kGrids / 2; n += 2, ++A.np) {
+      const bool two = n + 1 < nvec;
+      for (int k = 0; k < 2; ++k) {
+        const double* v = (k ? gxi_dev : xi_dev) + (long)n * d;
+        double2* g = m->grid[X.njob];
+        X.job[X.njob++] = XyJob{nullptr, v, nullptr, two ? v + d : nullptr, nullptr, g, nullptr};
+        (k ? A.w : A.z)[0][A.np] = g;
+      }
+    }
+    MEAS_CHECK(launch_xy(m, false, X, s));
+    MEAS_CHECK((launch_t<false, T_CROSS>(m, 1, A, s)));
   }
   // GA = e^{i pi dtau/Ltau} IDFT3[sum_n conj(A_n) B_n] / (nvec Ncal^2), Ncal = N Ltau
   const double ncal = (double)m->d;
@@ -482,27 +679,58 @@ int green_pair_products(fph_meas_t m, int32_t nvec, const double* xi_dev, const 
   const double npairs = 0.5 * (double)nvec * (double)(nvec - 1);
   const double scale = 1.0 / (npairs * (double)d * (double)d);
   // T1: (xi_n . xi_m) * (Gxi_n . Gxi_m);  T3: (xi_n . Gxi_m) * (xi_m . Gxi_n)
-  MEAS_CHECK(zero2(m, m->acc, s));
-  MEAS_CHECK(zero2(m, m->acc2, s));
-  for (int a = 0; a < nvec; ++a)
-    for (int b = a + 1; b < nvec; ++b) {
-      MEAS_CHECK(fwd3(m, IN_PRODUCT, xi(a), xi(b), 0, m->A, s));
-      MEAS_CHECK(fwd3(m, IN_PRODUCT, gx(a), gx(b), 0, m->B, s));
-      MEAS_CHECK(cross(m, m->acc, s));
-      MEAS_CHECK(fwd3(m, IN_PRODUCT, xi(a), gx(b), 0, m->A, s));
-      MEAS_CHECK(fwd3(m, IN_PRODUCT, xi(b), gx(a), 0, m->B, s));
-      MEAS_CHECK(cross(m, m->acc2, s));
+  // Two vector pairs per complex pair; kGrids / 4 complex pairs of each
+  // product per launch.
+  const long npair = (long)nvec * (nvec - 1) / 2;
+  int a = 0, b = 1;
+  for (long done = 0; done < npair;) {
+    XyArgs X;
+    TArgs A;
+    std::memset(&X, 0, sizeof(X));
+    std::memset(&A, 0, sizeof(A));
+    A.first = done == 0;
+    A.out[0] = m->acc;
+    A.out[1] = m->acc2;
+    for (; done < npair && A.np < kGrids / 4; ++A.np) {
+      XyJob q[4];  // Z, W of T1, then of T3
+      std::memset(q, 0, sizeof(q));
+      for (int k = 0; k < 2 && done < npair; ++k, ++done) {
+        const double* f[4][2] = {{xi(a), xi(b)}, {gx(a), gx(b)}, {xi(a), gx(b)}, {xi(b), gx(a)}};
+        for (int j = 0; j < 4; ++j) {
+          (k ? q[j].c : q[j].a) = f[j][0];
+          (k ? q[j].d : q[j].b) = f[j][1];
+        }
+        if (++b == nvec) {
+          ++a;
+          b = a + 1;
+        }
+      }
+      for (int j = 0; j < 4; ++j) {
+        q[j].out = m->grid[X.njob];
+        X.job[X.njob++] = q[j];
+        (j % 2 ? A.w : A.z)[j / 2][A.np] = q[j].out;
+      }
     }
+    MEAS_CHECK(launch_xy(m, false, X, s));
+    MEAS_CHECK((launch_t<false, T_CROSS>(m, 2, A, s)));
+  }
   MEAS_CHECK(inv3(m, m->acc, 0, scale, out_dev, s));
   MEAS_CHECK(inv3(m, m->acc2, 0, scale, out_dev + 2 * d, s));
   // T2: (xi_n . Gxi_n) * (xi_m . Gxi_m), n < m: sum_m conj(sum_{n<m} H_n) H_m
-  MEAS_CHECK(zero2(m, m->acc, s));
-  MEAS_CHECK(zero2(m, m->run, s));
-  for (int n = 0; n < nvec; ++n) {
-    MEAS_CHECK(fwd3(m, IN_PRODUCT, xi(n), gx(n), 0, m->B, s));
-    hipLaunchKernelGGL(k_acc_prefix, dim3(grid_for(d)), dim3(256), 0, s, d, m->run, (const double2*)m->B,
-                       m->acc);
-    MEAS_CHECK(hipGetLastError());
+  for (int n = 0; n < nvec;) {
+    XyArgs X;
+    TArgs A;
+    std::memset(&X, 0, sizeof(X));
+    std::memset(&A, 0, sizeof(A));
+    A.first = n == 0;
+    A.out[0] = m->acc;
+    A.run = m->run;
+    for (; n < nvec && A.np < kGrids; ++n, ++A.np) {
+      X.job[X.njob++] = XyJob{nullptr, xi(n), gx(n), nullptr, nullptr, m->grid[A.np], nullptr};
+      A.z[0][A.np] = m->grid[A.np];
+    }
+    MEAS_CHECK(launch_xy(m, false, X, s));
+    MEAS_CHECK((launch_t<false, T_PREFIX>(m, 1, A, s)));
   }
   MEAS_CHECK(inv3(m, m->acc, 0, scale, out_dev + d, s));
   return FPH_OK;

@@ -40,3 +40,38 @@ def test_precond_block_shapes(L, Ltau, nrhs):
         # rounding of a series of a few tens of terms in each precision
         assert _relmax(s.precond(vg, op).cpu().numpy(), ref) < 1e-12, op
         assert _relmax(s.precond(vg.float(), op).cpu().numpy().astype(np.float64), ref) < 1e-5, op
+
+
+# Line lengths by their factors: 4 and 8 (one stage), 14, 22, 62 and Ltau 62, 84 (prime factors above 5),
+# 18, 24, 60 (radices 3 and 5), 2 (one stage, one site tile), 128 and 400 (radices 8, 4, 5).
+@pytest.mark.parametrize("L,Ltau", [(4, 2), (8, 62), (14, 84), (22, 8), (62, 6), (18, 60), (24, 128), (10, 400)])
+def test_transform_lengths(L, Ltau):
+    from paper_2203_01291_amd.measure import GreenMeasurement
+    lat = OL.Lattice(L, Ltau, 0.1, 1.0, 0.0, 1.0)
+    rng = np.random.default_rng(L + 100 * Ltau)
+    z = rng.standard_normal((Ltau, L, L)) + 1j * rng.standard_normal((Ltau, L, L))
+    m = GreenMeasurement(_solver(lat, 1))
+    zg = torch.from_numpy(z.reshape(Ltau, -1)).cuda()
+    twist = np.exp(-1j * np.pi * np.arange(Ltau) / Ltau)[:, None, None]
+    for inverse in (False, True):
+        for tw in (False, True):
+            ref = (np.conj(twist if tw else 1.0) * np.fft.ifftn(z) * z.size if inverse
+                   else np.fft.fftn(twist * z if tw else z))
+            got = m.fft(zg, inverse=inverse, twist=tw).cpu().numpy().reshape(z.shape)
+            assert _relmax(got, ref) < 1e-13  # a few rounding errors per stage
+
+
+# Counts around the grids of a launch: an unpaired last vector or pair, several launches.
+@pytest.mark.parametrize("nvec", [1, 2, 3, 4, 9, 17])
+def test_estimator_counts(nvec):
+    from oracle import measure as OM
+    from paper_2203_01291_amd.measure import GreenMeasurement
+    lat = OL.Lattice(6, 10, 0.1, 1.0, 0.0, 1.0)
+    rng = np.random.default_rng(nvec)
+    xi = rng.choice([-1.0, 1.0], size=(nvec, lat.Ltau, lat.N))
+    gx = 0.5 * xi + 0.3 * rng.standard_normal(xi.shape)
+    m = GreenMeasurement(_solver(lat, 1))
+    a, b = torch.from_numpy(xi).cuda(), torch.from_numpy(gx).cuda()
+    assert _relmax(m.green_average(a, b).cpu().numpy(), OM.green_average_estimate(lat, xi, gx)) < 1e-12
+    if nvec > 1:
+        assert _relmax(m.pair_products(a, b).cpu().numpy(), OM.pair_products_estimate(lat, xi, gx)) < 1e-12
