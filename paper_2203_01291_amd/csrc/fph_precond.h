@@ -154,9 +154,16 @@ k_pc_bounds(int N, int Ltau, const double* __restrict__ dbar, double dtau, doubl
 
 // Chebyshev-Gauss coefficients (Eq. Cheby-Gauss, N_Q = 2 N_P) of
 // f_w(y) = 1/(1 - e^{-i phi_w} b(y)), b(y) = bmin + (y + 1) db/2, for the
-// even frequencies w = 2k.  Grid: H blocks.
+// even frequencies w = 2k.  Grid: H blocks.  Thread m sums over the N_Q
+// abscissas; up to kCoefLds orders f_w at the abscissas and the cosines
+// cos(pi j / (2 N_Q)) come from LDS, formed once per block (each term took
+// two cosines and a division before: 53 us for N_P 60, 5 us with the tables).
+constexpr int kCoefLds = 256;
+
 __global__ void __launch_bounds__(256)
 k_pc_coef(int Ltau, const PcInfo* info, const int* np, double2* coef64, float2* coef32) {
+  __shared__ double ct[4 * kCoefLds + 1];  // j = 0 .. 2 N_Q
+  __shared__ double2 fs[2 * kCoefLds];
   const int k = blockIdx.x;
   const int w = 2 * k;
   const int NP = np[w];
@@ -164,17 +171,29 @@ k_pc_coef(int Ltau, const PcInfo* info, const int* np, double2* coef64, float2* 
   const double bmin = info->bmin, db = info->bmax - info->bmin;
   const double er = cospi((2.0 * w + 1.0) / (double)Ltau);    // Re e^{-i phi}
   const double ei = -sinpi((2.0 * w + 1.0) / (double)Ltau);   // Im e^{-i phi}
+  auto f_at = [&](int n) {  // f_w at abscissa n
+    const double y = cospi((2.0 * n + 1.0) / (2.0 * NQ));
+    const double b = bmin + (y + 1.0) * 0.5 * db;
+    const double dr = 1.0 - er * b, di = -ei * b;   // 1 - e^{-i phi} b
+    const double den = dr * dr + di * di;
+    return make_double2(dr / den, -di / den);
+  };
+  const bool lds = NP <= kCoefLds;
+  if (lds) {
+    for (int j = threadIdx.x; j <= 2 * NQ; j += 256) ct[j] = cospi((double)j / (2.0 * NQ));
+    for (int n = threadIdx.x; n < NQ; n += 256) fs[n] = f_at(n);
+    __syncthreads();
+  }
   for (int m = threadIdx.x; m < NP; m += 256) {
     double sr = 0.0, si = 0.0;
+    int arg = m;  // m (2n + 1) mod 4 N_Q
     for (int n = 0; n < NQ; ++n) {
-      const double y = cospi((2.0 * n + 1.0) / (2.0 * NQ));
-      const long arg = ((long)m * (2 * n + 1)) % (4L * NQ);
-      const double cm = cospi((double)arg / (2.0 * NQ));
-      const double b = bmin + (y + 1.0) * 0.5 * db;
-      const double dr = 1.0 - er * b, di = -ei * b;   // 1 - e^{-i phi} b
-      const double den = dr * dr + di * di;
-      sr += cm * (dr / den);
-      si += cm * (-di / den);
+      const double cm = lds ? ct[min(arg, 4 * NQ - arg)] : cospi((double)arg / (2.0 * NQ));
+      const double2 f = lds ? fs[n] : f_at(n);
+      sr = fma(cm, f.x, sr);
+      si = fma(cm, f.y, si);
+      arg += 2 * m;
+      if (arg >= 4 * NQ) arg -= 4 * NQ;
     }
     const double scale = (m == 0 ? 1.0 : 2.0) / (double)NQ;
     const double2 c = make_double2(sr * scale, si * scale);
@@ -424,8 +443,8 @@ k_tfwd(Geom g, int H2, const typename Cplx<T>::type* __restrict__ tw,
       T2 a, b;
       dft_pair<false, H1 / 2>(Fl + k1 * H1, Y0 + n2 * KS + sidx, s1, H1, a, b);
       const int ia = ((n2 * H1 + k1) << lks) + sidx;
-      Y1[ia] = cmul<T2, T>(a, Wl[(n2 * k1) % H]);
-      Y1[ia + (h1 << lks)] = cmul<T2, T>(b, Wl[(n2 * (k1 + h1)) % H]);
+      Y1[ia] = cmul<T2, T>(a, Wl[n2 * k1]);
+      Y1[ia + (h1 << lks)] = cmul<T2, T>(b, Wl[n2 * (k1 + h1)]);
     }
   } else {
     for (int it = threadIdx.x; it < KS * H; it += NT) {
@@ -437,7 +456,7 @@ k_tfwd(Geom g, int H2, const typename Cplx<T>::type* __restrict__ tw,
       T2 acc = T2{(T)0, (T)0};
 #pragma unroll
       for (int n1 = 0; n1 < H1; ++n1) cmac(acc, fr[n1], yp[n1 * s1]);
-      Y1[it] = cmul<T2, T>(acc, Wl[(n2 * k1) % H]);
+      Y1[it] = cmul<T2, T>(acc, Wl[n2 * k1]);
     }
   }
   __syncthreads();
@@ -624,8 +643,8 @@ k_tinv(Geom g, int H2, const typename Cplx<T>::type* __restrict__ tw,
       T2 a, b;
       dft_pair<true, H1 / 2>(Fl + k1 * H1, Zt + n2 * KS + sidx, s1, H1, a, b);
       const int ia = ((n2 * H1 + k1) << lks) + sidx;
-      Y[ia] = cmulc<T2, T>(a, Wl[(n2 * k1) % H]);
-      Y[ia + (h1 << lks)] = cmulc<T2, T>(b, Wl[(n2 * (k1 + h1)) % H]);
+      Y[ia] = cmulc<T2, T>(a, Wl[n2 * k1]);
+      Y[ia + (h1 << lks)] = cmulc<T2, T>(b, Wl[n2 * (k1 + h1)]);
     }
   } else {
     for (int it = threadIdx.x; it < KS * H; it += NT) {
@@ -637,7 +656,7 @@ k_tinv(Geom g, int H2, const typename Cplx<T>::type* __restrict__ tw,
       T2 acc = T2{(T)0, (T)0};
 #pragma unroll
       for (int n1 = 0; n1 < H1; ++n1) cmacc(acc, fr[n1], yp[n1 * s1]);
-      Y[it] = cmulc<T2, T>(acc, Wl[(n2 * k1) % H]);
+      Y[it] = cmulc<T2, T>(acc, Wl[n2 * k1]);
     }
   }
   if (io.in != nullptr) {
@@ -975,8 +994,9 @@ FPH_DEVINL void c_finish(const Win& w, const T2 (&c)[4], T2 (&y)[4], const T2* b
 // (j - 1) mod 2, fixed per step of the unrolled loop; a series always
 // starts on buffer 0.  The two latest terms alternate between two register
 // sets, so no copies are made.
-template <typename T, bool TRANS, bool ROW16>
-FPH_DEVINL void cheb_series(const Win& w, int NP, const typename Cplx<T>::type* cf, T sA, T cA,
+// cf[m] is c_m, m < NP.
+template <typename T, bool TRANS, bool ROW16, class Coef>
+FPH_DEVINL void cheb_series(const Win& w, int NP, const Coef& cf, T sA, T cA,
                             const typename Cplx<T>::type (&x)[4], const T (&db)[4],
                             typename Cplx<T>::type* buf0, typename Cplx<T>::type* buf1, T th,
                             typename Cplx<T>::type (&acc)[4], int qid, int Q) {
