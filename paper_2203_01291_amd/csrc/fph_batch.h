@@ -34,7 +34,7 @@ struct BatchItem {
   float* u32;
   float* z;               // preconditioned direction input z = F F^T r
   float2* Zw;             // transform workspace, [H][N] complex (d floats)
-  BatchPc pc;             // the system's preconditioner tables
+  PcView<float> pc;       // the system's preconditioner tables
   int out;                // index into the statistics array
   int pad;
 };
@@ -43,6 +43,20 @@ struct BatchStat {
   int status, iters, outer, matvecs;
   double rel_resid, action;
 };
+
+// A copy of g whose sizes the compiler cannot trace to g: the index arithmetic
+// of the phases of one loop iteration then stays in it, instead of being
+// carried in registers from phase to phase (and spilled).
+FPH_DEVINL Geom opaque(Geom g) {
+  asm volatile("" : "+s"(g.L), "+s"(g.hL), "+s"(g.N), "+s"(g.Q));
+  return g;
+}
+
+// Sum of squares of four FP32 values, in FP64.
+FPH_DEVINL double sq4(const float4& v) {
+  return (double)v.x * (double)v.x + (double)v.y * (double)v.y + (double)v.z * (double)v.z +
+         (double)v.w * (double)v.w;
+}
 
 // Sum over the block, returned to every thread.
 template <int NT>
@@ -57,12 +71,14 @@ FPH_DEVINL double block_allsum(double v, double* sh, double* bcast) {
 
 // z = F F^T r for one item (fph_batch_pc.h); returns r . z in every thread.
 template <int NT>
-FPH_DEVINL double bpc_apply(const BatchItem& it, const float* r, float* z, unsigned char* lds,
+FPH_DEVINL double bpc_apply(const BatchItem& it, const Geom& g, const float* r, float* z, unsigned char* lds,
                             double* red_sh, double* bcast) {
-  float2* l = reinterpret_cast<float2*>(lds);
-  bpc_forward<NT>(it.g, it.pc, r, it.Zw, l);
-  bpc_series<NT>(it.g, it.pc, (float)it.th, it.Zw, l);
-  const double part = bpc_inverse<NT>(it.g, it.pc, it.Zw, r, z, l);
+  float2* tab = reinterpret_cast<float2*>(lds);
+  float2* l = tab + bpc_lds_tables(it.pc.H1, it.pc.H2);
+  bpc_tables<float, NT>(it.pc, tab);  // (the operator sweep uses this LDS too)
+  bpc_forward<float, NT, bpc_budget(NT)>(g, it.pc, r, it.Zw, tab, l);
+  bpc_series<float, NT, bpc_budget(NT)>(g, it.pc, (float)it.th, it.Zw, l);
+  const double part = bpc_inverse<float, NT, bpc_budget(NT)>(g, it.pc, it.Zw, r, z, tab, l);
   return block_allsum<NT>(part, red_sh, bcast);
 }
 
@@ -136,14 +152,14 @@ FPH_DEVINL void batch_solve_item(const BatchItem& it, double tol, int maxiter, d
 
   // Initial state: u = 0, r = b.
   double bb = 0.0, rr = 0.0;
-  for (long k = threadIdx.x; k < d; k += NT) {
-    const double bv = it.b[k];
-    const float rv = (float)bv;
-    it.u[k] = 0.0;
-    it.u32[k] = 0.0f;
-    it.r[k] = rv;
-    bb += bv * bv;
-    rr += (double)rv * (double)rv;
+  for (long k = 4L * threadIdx.x; k < d; k += 4L * NT) {
+    const auto bv = Vec4<double>::ld(it.b + k);
+    const float4 rv = make_float4((float)bv.x, (float)bv.y, (float)bv.z, (float)bv.w);
+    Vec4<double>::st(it.u + k, Vec4<double>::V{0.0, 0.0, 0.0, 0.0});
+    Vec4<float>::st(it.u32 + k, make_float4(0.f, 0.f, 0.f, 0.f));
+    Vec4<float>::st(it.r + k, rv);
+    bb += bv.x * bv.x + bv.y * bv.y + bv.z * bv.z + bv.w * bv.w;
+    rr += sq4(rv);
   }
   bb = block_allsum<NT>(bb, red_sh, bcast);
   rr = block_allsum<NT>(rr, red_sh, bcast);
@@ -155,7 +171,7 @@ FPH_DEVINL void batch_solve_item(const BatchItem& it, double tol, int maxiter, d
   if (bb == 0.0) status = 1;
   if (!isfinite(bb)) status = 8;
   if (status == 0 && pre) {
-    rz = bpc_apply<NT>(it, it.r, it.z, lds, red_sh, bcast);
+    rz = bpc_apply<NT>(it, opaque(g), it.r, it.z, lds, red_sh, bcast);
     if (!(rz > 0.0) || !isfinite(rz)) status = isfinite(rz) ? 4 : 8;
   }
 
@@ -166,7 +182,7 @@ FPH_DEVINL void batch_solve_item(const BatchItem& it, double tol, int maxiter, d
       InDir<float> in{zdir, pold, pnew, (float)beta, fresh};
       EpiDot<float> epi{it.Ap};
       double acc = 0.0, acc2 = 0.0;
-      mtm_sweep<float, NT, MS, 1>(g, it.E32, (float)it.th, Tch, tau0, Tc, active,
+      mtm_sweep<float, NT, MS, 1>(opaque(g), it.E32, (float)it.th, Tch, tau0, Tc, active,
                                   lane, nslot, lds4, 0, in, epi, acc, acc2, [] { return true; });
       const double pAp = block_allsum<NT>(acc, red_sh, bcast);
       matvecs += 1;
@@ -176,11 +192,15 @@ FPH_DEVINL void batch_solve_item(const BatchItem& it, double tol, int maxiter, d
       }
       const float alpha = (float)(rz / pAp);
       double acc_rr = 0.0;
-      for (long k = threadIdx.x; k < d; k += NT) {
-        const float rv = it.r[k] - alpha * it.Ap[k];
-        it.u32[k] += alpha * pnew[k];
-        it.r[k] = rv;
-        acc_rr += (double)rv * (double)rv;
+#pragma unroll 2
+      for (long k = 4L * threadIdx.x; k < d; k += 4L * NT) {
+        float4 rv = Vec4<float>::ld(it.r + k), uv = Vec4<float>::ld(it.u32 + k);
+        const float4 av = Vec4<float>::ld(it.Ap + k), pv = Vec4<float>::ld(pnew + k);
+        rv.x -= alpha * av.x; rv.y -= alpha * av.y; rv.z -= alpha * av.z; rv.w -= alpha * av.w;
+        uv.x += alpha * pv.x; uv.y += alpha * pv.y; uv.z += alpha * pv.z; uv.w += alpha * pv.w;
+        Vec4<float>::st(it.r + k, rv);
+        Vec4<float>::st(it.u32 + k, uv);
+        acc_rr += sq4(rv);
       }
       rr = block_allsum<NT>(acc_rr, red_sh, bcast);
     }
@@ -194,7 +214,7 @@ FPH_DEVINL void batch_solve_item(const BatchItem& it, double tol, int maxiter, d
       break;
     }
     if (!(rr <= tol2 || rr < delta * delta * rr_ref || iter >= maxiter)) {
-      const double rz_new = pre ? bpc_apply<NT>(it, it.r, it.z, lds, red_sh, bcast) : rr;
+      const double rz_new = pre ? bpc_apply<NT>(it, opaque(g), it.r, it.z, lds, red_sh, bcast) : rr;
       if (!(rz_new > 0.0) || !isfinite(rz_new)) {
         status = isfinite(rz_new) ? 4 : 8;
         break;
@@ -206,9 +226,12 @@ FPH_DEVINL void batch_solve_item(const BatchItem& it, double tol, int maxiter, d
 
     // FP64 residual replacement.
     const double rr_iter = rr;
-    for (long k = threadIdx.x; k < d; k += NT) {
-      it.u[k] += (double)it.u32[k];
-      it.u32[k] = 0.0f;
+    for (long k = 4L * threadIdx.x; k < d; k += 4L * NT) {
+      auto uv = Vec4<double>::ld(it.u + k);
+      const float4 c = Vec4<float>::ld(it.u32 + k);
+      uv.x += (double)c.x; uv.y += (double)c.y; uv.z += (double)c.z; uv.w += (double)c.w;
+      Vec4<double>::st(it.u + k, uv);
+      Vec4<float>::st(it.u32 + k, make_float4(0.f, 0.f, 0.f, 0.f));
     }
     __syncthreads();
     {
@@ -216,7 +239,7 @@ FPH_DEVINL void batch_solve_item(const BatchItem& it, double tol, int maxiter, d
       InPlain<double> in{it.u};
       EpiResidual<float> epi{it.b, it.r};
       double acc = 0.0, acc2 = 0.0;
-      mtm_sweep<double, NT, MS, 1>(g, it.E64, it.th, Tch, tau0, Tc, active, lane, nslot,
+      mtm_sweep<double, NT, MS, 1>(opaque(g), it.E64, it.th, Tch, tau0, Tc, active, lane, nslot,
                                    lds4, 0, in, epi, acc, acc2, [] { return true; });
       rr_true = block_allsum<NT>(acc, red_sh, bcast);
     }
@@ -231,13 +254,10 @@ FPH_DEVINL void batch_solve_item(const BatchItem& it, double tol, int maxiter, d
       break;
     }
     double acc_rr = 0.0;
-    for (long k = threadIdx.x; k < d; k += NT) {
-      const double rv = it.r[k];
-      acc_rr += rv * rv;
-    }
+    for (long k = 4L * threadIdx.x; k < d; k += 4L * NT) acc_rr += sq4(Vec4<float>::ld(it.r + k));
     rr = block_allsum<NT>(acc_rr, red_sh, bcast);
     if (rr > 100.0 * rr_iter) fresh = 1;  // replaced residual far from the iterated one
-    const double rz_new = pre ? bpc_apply<NT>(it, it.r, it.z, lds, red_sh, bcast) : rr;
+    const double rz_new = pre ? bpc_apply<NT>(it, opaque(g), it.r, it.z, lds, red_sh, bcast) : rr;
     if (!(rz_new > 0.0) || !isfinite(rz_new)) {
       status = isfinite(rz_new) ? 4 : 8;
       break;
@@ -249,7 +269,10 @@ FPH_DEVINL void batch_solve_item(const BatchItem& it, double tol, int maxiter, d
 
   // S_F = b . u in FP64.
   double act = 0.0;
-  for (long k = threadIdx.x; k < d; k += NT) act += it.b[k] * it.u[k];
+  for (long k = 4L * threadIdx.x; k < d; k += 4L * NT) {
+    const auto bv = Vec4<double>::ld(it.b + k), uv = Vec4<double>::ld(it.u + k);
+    act += bv.x * uv.x + bv.y * uv.y + bv.z * uv.z + bv.w * uv.w;
+  }
   act = block_allsum<NT>(act, red_sh, bcast);
   if (threadIdx.x == 0) {
     BatchStat st;

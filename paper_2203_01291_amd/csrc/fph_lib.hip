@@ -915,9 +915,10 @@ struct fph_batch_s {
   double2 *tw64, *W64, *F64;
   float2 *tw32, *W32, *F32;
   int nt, ms, per_cu;         // launch shape
+  bool tuned;                 // chosen by fph_batch_tune; else by batch_shape
+  long dmax;                  // unknowns of the largest item
   int num_cu;
   int qmax;
-  size_t lds_pc;              // LDS of the transforms and the series (bytes, largest system)
   hipStream_t cap;            // capture stream
   hipGraphExec_t exec;
   bool have_graph;
@@ -947,14 +948,17 @@ template <int NT, int MS>
 hipError_t batch_launch(fph_batch_s* b, const BatchRunCfg& c, hipStream_t s) {
   // LDS: four FP64 slices per chunk, chunks side by side (largest over
   // systems); with the preconditioner also the transforms and the series.
-  long sn = 0;
+  size_t lds = 0;
   for (const auto& sy : b->sys) {
     const int N = sy.lat.L * sy.lat.L, Q = N / 4;
     const int S = (Q <= NT) ? NT / Q : 1;
-    sn = std::max<long>(sn, (long)S * N);
+    lds = std::max(lds, 4 * (size_t)S * N * sizeof(double));
+    if (!c.pre) continue;
+    const int H = sy.lat.Ltau / 2, H1 = pick_h1(H), H2 = H / H1;
+    const long tf = bpc_lds_tf(H, bpc_tile_log2(N, H, bpc_budget(NT), sizeof(float2)));
+    const long se = bpc_groups(sy.lat.L, H, NT, bpc_budget(NT), sizeof(float2)) * bpc_lds_series(sy.lat.L);
+    lds = std::max(lds, (size_t)(std::max(tf, se) + bpc_lds_tables(H1, H2)) * sizeof(float2));
   }
-  size_t lds = 4 * (size_t)sn * sizeof(double);
-  if (c.pre) lds = std::max(lds, b->lds_pc);
   auto kern = k_batch_solve<NT, MS>;
   {
     hipError_t e = allow_lds((const void*)kern, lds);
@@ -1000,6 +1004,7 @@ hipError_t batch_enqueue(fph_batch_s* b, const BatchRunCfg& c, hipStream_t s) {
   if (b->nt == 256 && b->ms == 1) return batch_launch<256, 1>(b, c, s);
   if (b->nt == 128 && b->ms == 2) return batch_launch<128, 2>(b, c, s);
   if (b->nt == 512 && b->ms == 1) return batch_launch<512, 1>(b, c, s);
+  if (b->nt == 1024 && b->ms == 1) return batch_launch<1024, 1>(b, c, s);
   return hipErrorInvalidValue;
 }
 
@@ -1012,7 +1017,31 @@ __global__ void k_copy_batch_stats(int n, const BatchStat* __restrict__ in,
   out[k] = PcgStatsDev{s.status, s.iters, s.outer, s.matvecs, s.rel_resid, s.action};
 }
 
+// Launch shape of a batch that was not tuned.  An item is a chain of short
+// phases with workgroup barriers; until items queue up several deep, its own
+// time counts and more waves shorten it.  Without the preconditioner 512
+// threads win throughout (ms, 256 / 512 / 1 024 threads: 288 items of L 8-24,
+// Ltau 100: 125 / 60 / 59; 768 items: 146 / 102 / 130; 40 of L 4-6, Ltau 40:
+// 2.0 / 1.7 / 3.2; 2 560: 421 / 376 / -).  With it the transforms and series
+// feed 1 024 threads unless every item is small (288 items: 65 / 44 / 33; 768:
+// 82 / 70 / 65; 18 of up to 15 360 unknowns: 6.7 / 5.3 / 5.0; 20 of 4 000: 2.0 /
+// 1.8 / 2.2) or many items share a compute unit (2 560: 212 with 256).
+void batch_shape(fph_batch_s* b, const BatchRunCfg& c) {
+  b->ms = 1;
+  if (!c.pre || b->dmax <= 8192) {
+    b->nt = 512;
+    b->per_cu = 2;
+  } else if (b->nitems <= 4 * b->num_cu) {
+    b->nt = 1024;
+    b->per_cu = 1;
+  } else {
+    b->nt = 256;
+    b->per_cu = 2;
+  }
+}
+
 hipError_t batch_graph(fph_batch_s* b, const BatchRunCfg& c) {
+  if (!b->tuned) batch_shape(b, c);
   if (b->have_graph) {
     (void)hipGraphExecDestroy(b->exec);
     b->have_graph = false;
@@ -1038,7 +1067,7 @@ int check_batch_opts(const fph_batch_s* b, const fph_pcg_opts_t* opts) {
       !std::isfinite(opts->cheb_a2))
     return FPH_E_ARG;
   // the in-workgroup series needs one even plaquette per thread
-  if (opts->use_precond && b->nt < b->qmax) return FPH_E_ARG;
+  if (opts->use_precond && b->tuned && b->nt < b->qmax) return FPH_E_ARG;
   return FPH_OK;
 }
 
@@ -1052,7 +1081,7 @@ int fph_batch_create(fph_batch_t* out, const fph_system_t* sys, int32_t nsys) {
   if (nsys < 1) return FPH_E_ARG;
   long etot = 0, wtot = 0, ntot = 0, nptot = 0, ctot = 0, twtot = 0, ftot = 0;
   int nitems = 0, qmax = 1;
-  size_t lds_pc = 0;
+  long dmax = 0;
   for (int k = 0; k < nsys; ++k) {
     const fph_lattice_t& L = sys[k].lat;
     if (sys[k].x_dev == nullptr || sys[k].b_dev == nullptr || sys[k].u_dev == nullptr)
@@ -1074,17 +1103,17 @@ int fph_batch_create(fph_batch_t* out, const fph_system_t* sys, int32_t nsys) {
     ftot += (long)H1 * H1 + (long)H2 * H2;
     nitems += sys[k].nrhs;
     qmax = std::max(qmax, N / 4);
-    lds_pc = std::max(lds_pc, (size_t)std::max(bpc_lds_tf(H, H1, H2, bpc_tile_n(N)),
-                                               bpc_lds_series(L.L)) * sizeof(float2));
+    dmax = std::max(dmax, d);
   }
   fph_batch_s* b = new fph_batch_s();
   b->nsys = nsys;
   b->nitems = nitems;
   b->qmax = qmax;
-  b->lds_pc = lds_pc;
+  b->dmax = dmax;
   b->sys.assign(sys, sys + nsys);
   b->have_graph = false;
-  b->nt = qmax <= 256 ? 256 : 512;
+  b->tuned = false;
+  b->nt = 512;
   b->ms = 1;
   b->per_cu = 2;
   int dev = 0;
@@ -1120,7 +1149,7 @@ int fph_batch_create(fph_batch_t* out, const fph_system_t* sys, int32_t nsys) {
   }
   // Per-system offsets, twiddle tables (they depend on Ltau only), and the
   // preconditioner view of each system.
-  std::vector<BatchPc> pcs(nsys);
+  std::vector<PcView<float>> pcs(nsys);
   {
     long eo = 0, no = 0, npo = 0, co = 0, two = 0, fo = 0;
     for (int k = 0; k < nsys; ++k) {
@@ -1137,7 +1166,7 @@ int fph_batch_create(fph_batch_t* out, const fph_system_t* sys, int32_t nsys) {
                          H, H1, H2, L.Ltau, b->tw64 + two, b->W64 + two, b->F64 + fo,
                          b->tw32 + two, b->W32 + two, b->F32 + fo);
       const double ch = std::cosh(L.dtau * L.t);
-      BatchPc& pc = pcs[k];
+      PcView<float>& pc = pcs[k];
       pc.info = b->info + k;
       pc.np = b->np + npo;
       pc.coef = b->coef32 + co;
@@ -1253,6 +1282,7 @@ int fph_batch_tune(fph_batch_t b, const fph_pcg_opts_t* opts, int32_t* best, voi
     if (b->qmax <= 256) cands.push_back({256, 1, pc});
     if (!c.pre) cands.push_back({128, 2, pc});
     if (b->qmax <= 512) cands.push_back({512, 1, pc});
+    if (pc == 1) cands.push_back({1024, 1, 1});
   }
   hipEvent_t e0, e1;
   FPH_CHECK(hipEventCreate(&e0));
@@ -1261,6 +1291,7 @@ int fph_batch_tune(fph_batch_t b, const fph_pcg_opts_t* opts, int32_t* best, voi
   Cfg best_cfg = {b->nt, b->ms, b->per_cu};
   for (const Cfg& cf : cands) {
     if (cf.ms * cf.nt < b->qmax) continue;  // a slice must fit one block
+    b->tuned = true;
     b->nt = cf.nt;
     b->ms = cf.ms;
     b->per_cu = cf.per_cu;

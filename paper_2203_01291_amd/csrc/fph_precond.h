@@ -1244,8 +1244,8 @@ FPH_DEVINL void r_finish(const Win& w, const T (&c)[4], T (&y)[4], const T* buf,
   if (!TRANS) plaq_rot(y, th);
 }
 
-template <typename T, bool TRANS, bool ROW16, bool WAVE, class Swap>
-FPH_DEVINL void cheb_series_split(const Win& w, int NP, const typename Cplx<T>::type* cf, T sA,
+template <typename T, bool TRANS, bool ROW16, bool WAVE, class Coef, class Swap>
+FPH_DEVINL void cheb_series_split(const Win& w, int NP, const Coef& cf, T sA,
                                   T cA, T (&x)[4], const T (&db)[4], T* buf0, T* buf1, T th,
                                   bool im, int qid, int Q, const Swap& swap) {
   using T2 = typename Cplx<T>::type;

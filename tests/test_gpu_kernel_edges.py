@@ -75,3 +75,35 @@ def test_estimator_counts(nvec):
     assert _relmax(m.green_average(a, b).cpu().numpy(), OM.green_average_estimate(lat, xi, gx)) < 1e-12
     if nvec > 1:
         assert _relmax(m.pair_products(a, b).cpu().numpy(), OM.pair_products_estimate(lat, xi, gx)) < 1e-12
+
+
+# Batch workgroups: several frequencies side by side (ragged last round at L = 10, H = 21; more groups
+# than frequencies at L = 4), tiles of 32 to 128 sites with a ragged end, odd and even factors of
+# Ltau / 2; every shape through the tuner's candidates or the defaults, FP64 residuals from the oracle.
+@pytest.mark.parametrize("shapes", [[(4, 6, 2), (6, 8, 1)], [(10, 42, 2), (12, 40, 1), (8, 100, 1)],
+                                    [(24, 60, 1), (16, 32, 2)], [(32, 20, 1), (22, 24, 1)]])
+@pytest.mark.parametrize("tune", [False, True])
+def test_batch_workgroups(shapes, tune):
+    from paper_2203_01291_amd.solver import FermionBatch
+    systems, host = [], []
+    for n, (L, Ltau, nrhs) in enumerate(shapes):
+        lat = OL.Lattice(L, Ltau, 0.1, 1.0, 0.1, 1.0)
+        rng = np.random.default_rng(17 * n + L)
+        x = rng.standard_normal((Ltau, lat.N))
+        b = rng.standard_normal((nrhs, Ltau, lat.N))
+        systems.append((lat, torch.from_numpy(x).cuda(), torch.from_numpy(b).cuda()))
+        host.append((lat, x, b))
+    batch = FermionBatch(systems)
+    for precond in (False, True):
+        if tune:
+            batch.tune(tol=1e-11, precond=precond)
+        stats = batch.solve(tol=1e-11, precond=precond)
+        assert all(st["status"] == 1 for st in stats)
+        for (lat, x, b), u in zip(host, batch.u):
+            un = u.cpu().numpy()
+            C = OL.sparse_C(lat).tocsr()
+            res = b - OL.apply_MT(lat, x, OL.apply_M(lat, x, un, C), C)
+            for r in range(len(b)):
+                # the solver's own FP64 residual is below 1e-11 |b|
+                assert np.linalg.norm(res[r]) < 1.1e-11 * np.linalg.norm(b[r])
+
