@@ -117,9 +117,10 @@ typedef struct {
                            residual more than twice the FP32 one          */
   int32_t chunk;        /* pcg_solve_sync: solver slots (iterations or
                            residual evaluations) enqueued between two
-                           progress probes (0 -> an eighth of the slots
-                           enqueued so far, between 4 and 16, or 8 when
-                           N Ltau > 2^20); variant 2: the
+                           progress probes (0 -> 16, or 8 when
+                           N Ltau > 2^20; with the preconditioner
+                           an eighth of the slots enqueued so far
+                           up to that, at least 4); variant 2: the
                            largest number of workgroups (0 -> 128)         */
   int32_t variant;      /* 0: the standard (P)CG of pcg_solve (two
                            launches per iteration without preconditioner,
@@ -214,8 +215,10 @@ int fermion_matvec(fph_handle_t h, int32_t op, int32_t prec, int32_t nrhs,
  * FP64 residual evaluation per right-hand side; slots after a right-hand
  * side finished return at once, about 1.5 us per launch), then two final
  * kernels; set maxiter near the expected iteration count, since every slot
- * is enqueued.  Only kernel launches are enqueued (no memset or copy), so
- * the sequence can be captured into a hipGraph and replayed.  The host
+ * is enqueued.  (Small systems, N Ltau up to 2048 with the preconditioner, 4096
+ * without, 6144 without in FP32_REFINED, and up to 256 right-hand sides, run
+ * the same slots inside one launch.)  Only kernel launches are enqueued (no
+ * memset or copy), so the sequence can be captured into a hipGraph and replayed.  The host
  * thread may wait for space in the stream's queue while enqueueing a long
  * solve.  Calls on one handle must be ordered on one stream (they share
  * its workspace).  Returns FPH_OK even when a right-hand side did not
@@ -226,8 +229,8 @@ int pcg_solve(fph_handle_t h, int32_t nrhs, const double* b_dev, double* u_dev,
 
 /* The same solve for callers that want the statistics on the host:
  * stats_host (nrhs entries, may be NULL) is filled on return.  Enqueues the
- * slots of pcg_solve in chunks of opts->chunk (0 -> growing from 4 to 16, or
- * to 8 above 2^20 unknowns per right-hand side); after each chunk
+ * slots of pcg_solve in chunks of opts->chunk (0 -> 16, or 8 above 2^20
+ * unknowns per right-hand side, growing from 4 with the preconditioner); after each chunk
  * a one-wave kernel writes how many right-hand sides are still open into
  * pinned host memory, the host waits for the previous chunk's count only
  * (the GPU always has a chunk queued) and stops enqueueing once it is zero.

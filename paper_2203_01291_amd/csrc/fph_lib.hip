@@ -22,6 +22,7 @@
 #include "fph_internal.h"
 #include "fph_matvec.h"
 #include "fph_precond.h"
+#include "fph_small.h"
 #include "fph_solve.h"
 
 using namespace fph;
@@ -130,6 +131,9 @@ namespace {
 // solve.  With chunks of 16 throughout, a solve of 40 slots ran 64 (L = 16,
 // Ltau = 160, two FP64 right-hand sides: 2.76 ms per step, of which 0.9 ms
 // idle; 2.0 ms now, the Chebyshev blocks of an idle slot returning at once).
+// Without the preconditioner a slot is two short launches, and the host could
+// not keep the GPU busy from chunks of 4: there the largest from the start
+// (L = 18, Ltau = 84: 13.4 against 13.6 ms).
 // At 409 600 unknowns and some 1 900 slots 16 wins over 8; at 1 638 400 an
 // idle slot costs more and 8 wins.
 constexpr int kDefaultMaxOuter = 32;
@@ -702,6 +706,59 @@ struct SolveRun {
   }
 };
 
+// Whether a solve runs in one launch, a workgroup per right-hand side
+// (fph_small.h).  The line lies where a workgroup's time per iteration, which
+// grows with the unknowns, meets that of the two or four launches of a slot,
+// which hardly does (one right-hand side to 1e-13, launches / one workgroup, ms;
+// preconditioned FP64 L = 4, Ltau 40: 1.46 / 0.91, Ltau 100: 4.0 / 3.7, Ltau 160:
+// 8.1 / 8.9; L = 6, Ltau 60: 2.7 / 2.5; L = 10, Ltau 60: 3.0 / 4.0; plain FP64
+// L = 4, Ltau 160: 14.1 / 10.3, L = 8, Ltau 60: 8.1 / 6.3, L = 12, Ltau 40: 5.8 /
+// 6.0; plain FP32-refined L = 10, Ltau 60: 8.3 / 7.1, L = 16, Ltau 40: 5.9 / 6.9).
+// More right-hand sides than compute units would queue.
+bool small_route(const SolveRun& run) {
+  const long most = run.pre ? 2048 : run.mixed ? 6144 : 4096;
+  return run.h->g.d <= most && run.h->g.Q <= kSmallNT && run.nrhs <= 256;
+}
+
+template <typename TI>
+hipError_t small_launch(const fph_handle_s* h, int nrhs, const SolveRun& run, const SlotArgs<TI>& a, TI* uit,
+                        const TI* dbar, PcgStatsDev* stats, hipStream_t s) {
+  using T2 = typename Cplx<TI>::type;
+  const PcTables& pc = h->pc;
+  auto pick = [](void* p64, void* p32) { return (const T2*)(sizeof(TI) == 8 ? p64 : p32); };
+  SmallArgs<TI> A;
+  A.s = a;
+  A.uit = uit;
+  A.Z = reinterpret_cast<T2*>(pc.Z);
+  A.pc = PcView<TI>{pc.info,
+                    pc.np,
+                    pick(pc.coef64, pc.coef32),
+                    dbar,
+                    pick(pc.tw64, pc.tw32),
+                    pick(pc.W64, pc.W32),
+                    pick(pc.F64, pc.F32),
+                    (TI)pc.c4,
+                    pc.H,
+                    pc.H1,
+                    pc.H2};
+  A.pre = run.pre;
+  A.zero = run.zero;
+  A.total = run.total;
+  A.init = run.init;
+  const size_t lds = small_lds<TI>(h->g, pc.H1, pc.H2, run.pre);
+  auto kern = k_small_solve<TI>;
+  const hipError_t e = allow_lds((const void*)kern, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(nrhs), dim3(kSmallNT), lds, s, h->g, A, stats);
+  return hipGetLastError();
+}
+
+hipError_t small_solve(const SolveRun& run, PcgStatsDev* stats, hipStream_t s) {
+  fph_handle_s* h = run.h;
+  return run.mixed ? small_launch<float>(h, run.nrhs, run, run.a32, h->u32, h->dbar32, stats, s)
+                   : small_launch<double>(h, run.nrhs, run, run.a64, run.u, h->dbar64, stats, s);
+}
+
 // The one-launch cooperative FP32-refined solve (fph_coop.h) for one
 // right-hand side.  Workgroups own chunks of slices; the chunk length is
 // the shortest that keeps the workgroup count within the exchange's limit
@@ -833,6 +890,10 @@ extern "C" int pcg_solve(fph_handle_t h, int32_t nrhs, const double* b_dev, doub
     return FPH_OK;
   }
   SolveRun run(h, nrhs, b_dev, u_dev, opts);
+  if (small_route(run)) {
+    FPH_CHECK(small_solve(run, st, s));
+    return FPH_OK;
+  }
   FPH_CHECK(run.start(s));
   FPH_CHECK(run.slots(run.total, s));
   FPH_CHECK(run.finish(st, s));
@@ -847,13 +908,14 @@ extern "C" int pcg_solve_sync(fph_handle_t h, int32_t nrhs, const double* b_dev,
   hipStream_t s = (hipStream_t)stream;
   if (opts->variant == 2) {
     FPH_CHECK(coop_enqueue(h, b_dev, u_dev, opts, h->stats_dev, s));
+  } else if (SolveRun run(h, nrhs, b_dev, u_dev, opts); small_route(run)) {
+    FPH_CHECK(small_solve(run, h->stats_dev, s));
   } else {
     // The same launches as pcg_solve, in chunks of slots; after each chunk
     // a probe kernel writes how many right-hand sides are still open to
     // pinned host memory.  The host waits for the probe of the previous
     // chunk only (so the GPU always has a chunk queued) and stops
     // enqueueing once it reads zero; slots already queued return at once.
-    SolveRun run(h, nrhs, b_dev, u_dev, opts);
     FPH_CHECK(run.start(s));
     int* open_dev = nullptr;
     FPH_CHECK(hipHostGetDevicePointer((void**)&open_dev, h->open_pin, 0));
@@ -861,7 +923,7 @@ extern "C" int pcg_solve_sync(fph_handle_t h, int32_t nrhs, const double* b_dev,
     long enq = 0;
     for (int k = 0; enq < run.total; ++k) {
       const long chunk = opts->chunk > 0 ? opts->chunk
-                                         : std::min(most, std::max(kFirstSlotChunk, enq / 8));
+                                         : std::min(most, std::max(run.pre ? kFirstSlotChunk : most, enq / 8));
       const long n = std::min(chunk, run.total - enq);
       FPH_CHECK(run.slots(n, s));
       enq += n;

@@ -147,10 +147,7 @@ struct SolveInit {
   int pad;
 };
 
-__global__ void k_solve_init(int nrhs, SolveInit p, RhsState* st) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nrhs) return;
-  RhsState s;
+FPH_DEVINL void solve_init_state(RhsState& s, const SolveInit& p) {
   memset(&s, 0, sizeof(s));
   s.tol = p.tol;
   s.rdelta = p.rdelta;
@@ -160,8 +157,15 @@ __global__ void k_solve_init(int nrhs, SolveInit p, RhsState* st) {
   s.fresh = 1;
   s.done = 1;
   s.replace = 1;
-  s.u32z = 1;
+  s.u32z = p.refined;  // FP64: the update advances u_dev, which holds the guess
   s.pend = P_NONE;
+}
+
+__global__ void k_solve_init(int nrhs, SolveInit p, RhsState* st) {
+  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= nrhs) return;
+  RhsState s;
+  solve_init_state(s, p);
   st[r] = s;
 }
 
@@ -205,25 +209,27 @@ k_solve_final(long d, const RhsState* __restrict__ st, const double* __restrict_
   if (threadIdx.x == 0) part[(long)r * kPStride + blockIdx.x] = bs;
 }
 
-// Statistics of every right-hand side (one block each): a right-hand side
-// that did not finish within the enqueued slots reports MAXITER.
+// Statistics of a right-hand side: one that did not finish within the
+// enqueued slots reports MAXITER.
+FPH_DEVINL PcgStatsDev solve_stats(const RhsState& s, double action) {
+  PcgStatsDev o;
+  o.status = s.final_ ? s.status : (s.status | 2);
+  o.iters = s.iter;
+  o.outer_iters = s.outer;
+  o.matvecs = s.matvecs;
+  o.rel_resid = s.bb > 0.0 ? sqrt(s.rr_true / s.bb) : 0.0;
+  o.action = action;
+  return o;
+}
+
+// Statistics of every right-hand side (one block each).
 __global__ void __launch_bounds__(256)
 k_solve_stats(int nb, const RhsState* __restrict__ st, const double* __restrict__ part,
               PcgStatsDev* __restrict__ out) {
   __shared__ double red_sh[4];
   const int r = blockIdx.x;
   const double act = reduce_partials<256>(part + (long)r * kPStride, nb, red_sh);
-  if (threadIdx.x == 0) {
-    const RhsState s = st[r];
-    PcgStatsDev o;
-    o.status = s.final_ ? s.status : (s.status | 2);
-    o.iters = s.iter;
-    o.outer_iters = s.outer;
-    o.matvecs = s.matvecs;
-    o.rel_resid = s.bb > 0.0 ? sqrt(s.rr_true / s.bb) : 0.0;
-    o.action = act;
-    out[r] = o;
-  }
+  if (threadIdx.x == 0) out[r] = solve_stats(st[r], act);
 }
 
 // Number of right-hand sides not finished (one wave), stored to pinned host

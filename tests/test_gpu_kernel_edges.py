@@ -107,3 +107,55 @@ def test_batch_workgroups(shapes, tune):
                 # the solver's own FP64 residual is below 1e-11 |b|
                 assert np.linalg.norm(res[r]) < 1.1e-11 * np.linalg.norm(b[r])
 
+
+# Solves in one launch (up to 2048 unknowns preconditioned, 4096 or 6144 without) and just above:
+# fewer slices than chunks, one chunk per workgroup (L = 44), one wave per frequency (L <= 10) and
+# several frequencies per workgroup (L = 22), a field per right-hand side, zero and non-zero guesses.
+@pytest.mark.parametrize("L,Ltau", [(4, 2), (4, 40), (4, 128), (6, 56), (8, 32), (22, 4), (32, 2), (4, 130),
+                                    (44, 2), (16, 16), (16, 24), (10, 62)])
+@pytest.mark.parametrize("prec", ["f64", "f32_refined"])
+@pytest.mark.parametrize("precond", [False, True])
+def test_small_solves(L, Ltau, prec, precond):
+    lat = OL.Lattice(L, Ltau, 0.1, 1.0, 0.1, 1.0)
+    rng = np.random.default_rng(31 * L + Ltau)
+    xs = rng.standard_normal((2, Ltau, lat.N))
+    b = rng.standard_normal((4, Ltau, lat.N))
+    b[2] = 0.0
+    s = _solver(lat, 4)
+    s.set_fields(torch.from_numpy(xs).cuda(), rhs_per_field=2)
+    bg = torch.from_numpy(b).cuda()
+    u, stats = s.solve(bg, tol=1e-11, prec=prec, precond=precond)
+    C = OL.sparse_C(lat).tocsr()
+
+    def check(u, stats):
+        un = u.cpu().numpy()
+        for r in range(4):
+            assert stats[r]["status"] == 1
+            res = b[r] - OL.apply_MT(lat, xs[r // 2], OL.apply_M(lat, xs[r // 2], un[r], C), C)
+            assert np.linalg.norm(res) <= 1.1e-11 * np.linalg.norm(b[r])  # the solver's FP64 residual
+            assert stats[r]["action"] == pytest.approx(float(np.sum(b[r] * un[r])), rel=1e-12, abs=1e-12)
+
+    check(u, stats)
+    assert not u[2].any()
+    # the enqueue-only call takes the same path
+    v, st = s.solve_async(bg, tol=1e-11, prec=prec, precond=precond, maxiter=stats[0]["iters"] + 400)
+    torch.cuda.synchronize()
+    assert torch.equal(u, v)
+    # from a guess with a relative error of 1e-5 fewer iterations are left
+    guess = u * (1.0 + 1e-5 * torch.randn_like(u))
+    w, warm = s.solve(bg, u=guess, tol=1e-11, prec=prec, precond=precond)
+    check(w, warm)
+    for r in (0, 1, 3):
+        assert warm[r]["iters"] < stats[r]["iters"] or stats[r]["iters"] <= 2
+
+
+# An iteration budget that ends the solve early, inside one launch and above.
+@pytest.mark.parametrize("L,Ltau", [(4, 40), (16, 40)])
+@pytest.mark.parametrize("prec", ["f64", "f32_refined"])
+def test_small_solve_budget(L, Ltau, prec):
+    lat = OL.Lattice(L, Ltau, 0.1, 1.0, 0.1, 1.0)
+    rng = np.random.default_rng(5)
+    s = _solver(lat, 1)
+    s.set_field(torch.from_numpy(rng.standard_normal((Ltau, lat.N))).cuda())
+    _, st = s.solve(torch.from_numpy(rng.standard_normal((1, Ltau, lat.N))).cuda(), tol=1e-12, prec=prec, maxiter=7)
+    assert st[0]["status"] == 2 and st[0]["iters"] == 7
