@@ -1632,20 +1632,27 @@ size_t pc_tile_lds(const PcTables* pc, int lks) {
   return (nF + pc->H + 2 * (size_t)pc->H * ((size_t)1 << lks)) * sizeof(typename Cplx<T>::type);
 }
 
-// Tile width (log2) of the transforms, for workgroups of kTNT threads:
-// the widest tile up to 8 sites that leaves at least 256 tiles (each slice
-// row of a tile is a separate short segment, so narrow tiles cost more
-// cache lines per byte; wide ones leave CUs idle), not below 2 sites, and
-// at most 64 KB of LDS per workgroup.  (At L = 64 FP64 tiles of 4 sites
-// would make 1 024 workgroups, two rounds at the two workgroups of this
-// kernel a CU holds; 8 sites make one.)
+// Tile width (log2) of the transforms, for workgroups of kTNT threads: the
+// widest tile up to 32 sites with at least 512 tiles (two workgroups per
+// compute unit) and at most 48 KB of LDS, else up to 8 sites with at least 256
+// tiles, not below 2 sites, and at most 64 KB.  Each slice row of a tile is a separate
+// short segment, so narrow tiles cost more cache lines per byte (us per
+// preconditioned iteration with 8 / 16 / 32 sites, FP32: L = 32, Ltau 160, ten
+// right-hand sides 48.5 / 43.7 / 44.2; L = 48, Ltau 100, four 40.8 / 36.2 / 35.7;
+// L = 64, Ltau 40, four 46.9 / 36.1 / 30.7, FP64 55.0 / 42.9 / 37.7); wide ones
+// leave compute units idle (L = 64, Ltau 400, one: 47.1 / 47.7 / 57.3), and
+// long ones of more than 48 KB waste a second round (L = 32, Ltau 400, ten: F F^T
+// 48.3 / 52.3, FP64 iteration 132 / 142).
 constexpr int kTNT = 512;
 
 template <typename T>
 int pc_tile_log2(const PcTables* pc, const Geom& g, int nrhs) {
-  int lks = 3;
-  while (lks > 1 && (long)((g.N + (1 << lks) - 1) >> lks) * nrhs < 256) --lks;
-  while (lks > 0 && pc_tile_lds<T>(pc, lks) > ((size_t)64 << 10)) --lks;
+  auto tiles = [&](int lks) { return (long)((g.N + (1 << lks) - 1) >> lks) * nrhs; };
+  auto fits = [&](int lks, size_t kb) { return pc_tile_lds<T>(pc, lks) <= (kb << 10); };
+  int lks = 5;
+  while (lks > 3 && (tiles(lks) < 512 || !fits(lks, 48))) --lks;
+  while (lks > 1 && tiles(lks) < 256) --lks;
+  while (lks > 0 && !fits(lks, 64)) --lks;
   return lks;
 }
 

@@ -23,7 +23,9 @@ def _solver(lat, max_rhs):
 # (128), 256 (row form, one to three right-hand sides: split and unsplit FP32), 289 (above 256);
 # Ltau = 2 has a single frequency with one or two terms.
 @pytest.mark.parametrize("L,Ltau,nrhs", [(16, 8, 1), (18, 12, 2), (22, 6, 1), (24, 4, 3), (32, 400, 1),
-                                         (32, 400, 3), (34, 4, 1), (4, 2, 1), (10, 2, 2)])
+                                         (32, 400, 3), (34, 4, 1), (4, 2, 1), (10, 2, 2),
+                                         # transform tiles of 16 and 32 sites, ragged at the end
+                                         (30, 20, 10), (30, 20, 19), (64, 40, 4), (62, 4, 6)])
 def test_precond_block_shapes(L, Ltau, nrhs):
     lat = OL.Lattice(L, Ltau, 0.1, 1.0, -0.1, 1.1)
     rng = np.random.default_rng(100 * L + Ltau)
