@@ -645,7 +645,8 @@ int ssh_set_preconditioner(fph_ssh_t c, fph_handle_t h, double a1, double a2);
  * evaluated; the right-hand side finishes when that residual is below
  * tol |b|, after opts->max_outer evaluations (0 -> 32) or maxiter FP32
  * iterations (FPH_ST_MAXITER).  Other precisions: FPH_E_PREC.
- * opts->chunk iterations (0 -> 64) are enqueued between host checks.
+ * opts->chunk iterations (0 -> 4 to 64, as many as the convergence so far
+ * leaves to do) are enqueued between host checks.
  * stats_host (nrhs entries, may be NULL) hold the iterations, the FP64
  * evaluations after the first (outer_iters), the FP64 true relative
  * residual and S_F = b . u.  Blocks until done. */

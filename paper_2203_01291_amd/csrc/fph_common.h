@@ -197,8 +197,9 @@ struct StateSeq {
   int cur;
   int precond;
   bool active;  // false: plain operator calls without solver state
+  double* plain = nullptr;  // then: r.z partials of the inverse transform, [rhs][tile], or null
   StIO next() {
-    if (!active) return StIO{nullptr, nullptr, nullptr, nullptr, precond};
+    if (!active) return StIO{nullptr, nullptr, nullptr, plain, precond};
     StIO io{st[cur], st[cur ^ 1], part[cur], part[cur ^ 1], precond};
     cur ^= 1;
     return io;

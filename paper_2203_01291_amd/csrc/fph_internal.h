@@ -12,6 +12,12 @@ namespace fph {
 // Records hipGetErrorString(e) as the message of FPH_E_HIP and returns FPH_E_HIP.
 int record_hip_error(hipError_t e);
 
+// fph_precond_apply of F F^T that also writes partial sums of in_r . out_r,
+// part_dev[r * nparts + k], k < nparts; nparts (at most N) = precond_parts.
+int precond_parts(fph_handle_t h, int32_t prec, int32_t nrhs);
+int precond_apply_dot(fph_handle_t h, int32_t prec, int32_t nrhs, const void* in_dev, void* out_dev,
+                      double* part_dev, void* stream);
+
 // The operator an HMC context runs on (its Holstein handle or SSH context):
 // two contexts on the same one must not run side by side.
 const void* hmc_operator(fph_hmc_t c);

@@ -328,6 +328,42 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 // =================================================================== ABI
 
+namespace {
+
+// fph_precond_apply; with part, also partials of in_r . out_r.
+int precond_call(fph_handle_t h, int32_t op, int32_t prec, int32_t nrhs, const void* in_dev, void* out_dev,
+                 double* part, void* stream) {
+  if (h == nullptr || in_dev == nullptr || out_dev == nullptr) return FPH_E_NULL;
+  if (!h->have_field) return FPH_E_NOFIELD;
+  if (nrhs < 1 || nrhs > h->max_rhs || (h->nfields && nrhs > h->nfields * h->g.rpf)) return FPH_E_NRHS;
+  if (op < 0 || op > 2 || (prec != FPH_F64 && prec != FPH_F32)) return FPH_E_PREC;
+  hipStream_t s = (hipStream_t)stream;
+  hipError_t e;
+  StateSeq sq{{nullptr, nullptr}, {nullptr, nullptr}, 0, 0, false, part};
+  if (prec == FPH_F64)
+    e = pc_apply<double>(&h->pc, h->g, h->dbar64, op, nrhs, (const double*)in_dev, (double*)out_dev,
+                         part ? (const double*)in_dev : nullptr, sq, s);
+  else
+    e = pc_apply<float>(&h->pc, h->g, h->dbar32, op, nrhs, (const float*)in_dev, (float*)out_dev,
+                        part ? (const float*)in_dev : nullptr, sq, s);
+  if (e != hipSuccess) return fail_hip(e);
+  return FPH_OK;
+}
+
+}  // namespace
+
+int fph::precond_parts(fph_handle_t h, int32_t prec, int32_t nrhs) {
+  const int lks = prec == FPH_F64 ? pc_tile_log2<double>(&h->pc, h->g, nrhs)
+                                  : pc_tile_log2<float>(&h->pc, h->g, nrhs);
+  return (h->g.N + (1 << lks) - 1) >> lks;
+}
+
+int fph::precond_apply_dot(fph_handle_t h, int32_t prec, int32_t nrhs, const void* in_dev, void* out_dev,
+                           double* part_dev, void* stream) {
+  if (part_dev == nullptr) return FPH_E_NULL;
+  return precond_call(h, FPH_PC_FFT, prec, nrhs, in_dev, out_dev, part_dev, stream);
+}
+
 extern "C" {
 
 const char* fph_version(void) { return "holstein-hmc-gfx950 0.1"; }
@@ -573,21 +609,7 @@ int fermion_action_noalloc(fph_handle_t h, int32_t nrhs, const double* b_dev,
 
 int fph_precond_apply(fph_handle_t h, int32_t op, int32_t prec, int32_t nrhs, const void* in_dev,
                       void* out_dev, void* stream) {
-  if (h == nullptr || in_dev == nullptr || out_dev == nullptr) return FPH_E_NULL;
-  if (!h->have_field) return FPH_E_NOFIELD;
-  if (nrhs < 1 || nrhs > h->max_rhs || (h->nfields && nrhs > h->nfields * h->g.rpf)) return FPH_E_NRHS;
-  if (op < 0 || op > 2 || (prec != FPH_F64 && prec != FPH_F32)) return FPH_E_PREC;
-  hipStream_t s = (hipStream_t)stream;
-  hipError_t e;
-  StateSeq sq{{nullptr, nullptr}, {nullptr, nullptr}, 0, 0, false};
-  if (prec == FPH_F64)
-    e = pc_apply<double>(&h->pc, h->g, h->dbar64, op, nrhs, (const double*)in_dev,
-                         (double*)out_dev, nullptr, sq, s);
-  else
-    e = pc_apply<float>(&h->pc, h->g, h->dbar32, op, nrhs, (const float*)in_dev,
-                        (float*)out_dev, nullptr, sq, s);
-  if (e != hipSuccess) return fail_hip(e);
-  return FPH_OK;
+  return precond_call(h, op, prec, nrhs, in_dev, out_dev, nullptr, stream);
 }
 
 int fph_precond_info(fph_handle_t h, double* bounds_host, int32_t* np_host, void* stream) {

@@ -505,7 +505,8 @@ k_tfwd(Geom g, int H2, const typename Cplx<T>::type* __restrict__ tw,
 // split into tau and tau + H).  Stage 0 copies the tile Zh[k][i0..i0+KS)
 // to LDS with coalesced loads; the solver state, issued before them, is
 // folded after step 1 (it only decides whether the right-hand side is
-// skipped).  With dot != 0 also publishes rdot . out as P_RZ partials.  LDS:
+// skipped).  With dot != 0 also publishes rdot . out as P_RZ partials (without
+// solver state: into io.pout[r][tile]).  LDS:
 // (H1^2 + H2^2 + H + 2 H KS) complex values.  KI input items per thread and
 // pass: 4, or 2 where that already covers the tile in one pass (FP32 loads
 // every item slot, in range or not).
@@ -725,6 +726,9 @@ k_tinv(Geom g, int H2, const typename Cplx<T>::type* __restrict__ tw,
     double bs = 0.0;
     if (dot) bs = block_sum<NT, true>(acc_dot, red_sh);
     state_end(io, r, &s_sh, dot ? P_RZ : P_NONE, bs, tile, ntiles, tile == 0);
+  } else if (dot) {
+    const double bs = block_sum<NT, true>(acc_dot, red_sh);
+    if (threadIdx.x == 0) io.pout[(long)r * ntiles + tile] = bs;
   }
 }
 
@@ -1801,7 +1805,7 @@ hipError_t pc_kpm(const PcTables* pc, const Geom& g, const T* dbar, int op, int 
 }
 
 // out = op(in) (op: 0 F, 1 F^T, 2 F F^T).  With rdot != nullptr the inverse
-// transform also publishes rdot . out as P_RZ partials.
+// transform also publishes rdot . out as P_RZ partials, or into sq.plain.
 template <typename T>
 hipError_t pc_apply(const PcTables* pc, const Geom& g, const T* dbar, int op, int nrhs,
                     const T* in, T* out, const T* rdot, StateSeq& sq, hipStream_t s) {

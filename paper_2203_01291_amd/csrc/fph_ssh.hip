@@ -792,6 +792,20 @@ hipError_t dots(const fph_ssh_s* c, int nrhs, const T* a, const T* b, hipStream_
   return hipGetLastError();
 }
 
+// CG steps to enqueue before the next look at the states, from a residual that
+// fell from `from` to `now` in `steps` steps and stops at `goal` (squares): the
+// steps left at that rate.  A stopped right-hand side's steps still cost their
+// launches (about 30 us each at L = 20, Ltau 120, two right-hand sides), a look
+// some 20 us: fixed chunks of 64 ran 48 steps too many after 400, and half a
+// chunk at every pause of a refined solve.
+constexpr int kFirstChunk = 16, kMostChunk = 64;
+double steps_left(double from, double now, int steps, double goal) {
+  if (!(now > goal)) return 1.0;
+  const double rate = steps > 0 ? std::log(from / now) / steps : 0.0;
+  return rate > 0.0 && goal > 0.0 ? std::log(now / goal) / rate : (double)kMostChunk;
+}
+int chunk_of(double left) { return (int)std::min((double)kMostChunk, std::max(4.0, std::ceil(left))); }
+
 // FP32-refined (P)CG on M^T M (reliable updates of the residual, as the
 // Holstein solver's FP32-refined mode): FP32 CG on a correction u32 with the
 // FP32 tables.  The iteration of a right-hand side stops on the device
@@ -811,7 +825,9 @@ int solve_refined(fph_ssh_s* c, int nrhs, const double* b_dev, double* u_dev, co
   const long d = c->G.d;
   const long n = (long)nrhs * d;
   const bool pre = opts->use_precond != 0;
-  const int chunk = opts->chunk > 0 ? (opts->chunk < kMaxChunk ? opts->chunk : kMaxChunk) : 64;
+  const int fixed = std::min((int)opts->chunk, kMaxChunk);  // 0: chosen from the convergence
+  int chunk = fixed > 0 ? fixed : kFirstChunk;
+  const int nbz = pre ? fph::precond_parts(c->pc, FPH_F32, nrhs) : kXrBlocks;
   double delta = opts->ru_delta > 0.0 ? std::min(opts->ru_delta, 0.5) : (pre ? 0.1 : 0.3);
   const int max_outer = opts->max_outer > 0 ? opts->max_outer : 32;
   const double tol2 = opts->tol * opts->tol;
@@ -898,11 +914,15 @@ int solve_refined(fph_ssh_s* c, int nrhs, const double* b_dev, double* u_dev, co
   int outer = 0;
   const int matvecs0 = opts->zero_guess ? 0 : 1;
   std::vector<int> iters0(nrhs, 0);
+  std::vector<double> rr0(nrhs, 0.0), rate(nrhs, 0.0);
   for (;;) {
     bool all = true;
     for (int r = 0; r < nrhs; ++r) all = all && fin[r];
     if (all) break;
-    for (int r = 0; r < nrhs; ++r) iters0[r] = c->st_host[r].iters;
+    for (int r = 0; r < nrhs; ++r) {
+      iters0[r] = c->st_host[r].iters;
+      rr0[r] = c->st_host[r].rr;
+    }
     for (int k = 0; k < chunk; ++k) {
       const double* pq = c->part2;
       if (fused) {
@@ -913,7 +933,7 @@ int solve_refined(fph_ssh_s* c, int nrhs, const double* b_dev, double* u_dev, co
         a.st_new = sb;
         a.part_rr = c->part;
         a.part_rz = p2;
-        a.nbz = pre ? kRedBlocks : kXrBlocks;
+        a.nbz = nbz;
         a.from_state = k == 0;
         SSH_CHECK((launch_mtm_fused<float, true>(c, nrhs, pc, c->q32, s, true, c->part3, a)));
         std::swap(sa, sb);
@@ -926,12 +946,11 @@ int solve_refined(fph_ssh_s* c, int nrhs, const double* b_dev, double* u_dev, co
                          (const float*)pn, (const float*)c->q32, c->u32, c->r32, c->part);
       SSH_CHECK(hipGetLastError());
       if (pre) {
-        rc = fph_precond_apply(c->pc, FPH_PC_FFT, FPH_F32, nrhs, c->r32, c->z32, stream);
+        rc = fph::precond_apply_dot(c->pc, FPH_F32, nrhs, c->r32, c->z32, c->part2, stream);
         if (rc != FPH_OK) return rc;
-        SSH_CHECK(dots<float>(c, nrhs, c->r32, c->z32, s, c->part2));
       }
       if (!fused || k + 1 == chunk) {
-        hipLaunchKernelGGL(k_cg_scalar, dim3(nrhs), dim3(256), 0, s, 2, kXrBlocks, pre ? kRedBlocks : kXrBlocks,
+        hipLaunchKernelGGL(k_cg_scalar, dim3(nrhs), dim3(256), 0, s, 2, kXrBlocks, nbz,
                            (const double*)c->part, p2, sa);
         SSH_CHECK(hipGetLastError());
       }
@@ -940,10 +959,16 @@ int solve_refined(fph_ssh_s* c, int nrhs, const double* b_dev, double* u_dev, co
     SSH_CHECK(hipMemcpyAsync(c->st_host, sa, nrhs * sizeof(CgState), hipMemcpyDeviceToHost, s));
     SSH_CHECK(hipStreamSynchronize(s));
     bool due = false;
+    double left = 0.0;
     for (int r = 0; r < nrhs; ++r) {
       const CgState& S = c->st_host[r];
-      if (!fin[r] && (S.done || S.rr <= delta * delta * rr_ref[r])) due = true;
+      if (fin[r]) continue;
+      const double goal = std::max(S.tol2 * S.bb, S.delta2 * S.rr_ref);
+      if (S.done || S.rr <= delta * delta * rr_ref[r]) due = true;
+      left = std::max(left, steps_left(rr0[r], S.rr, S.iters - iters0[r], goal));
+      if (S.iters > iters0[r] && S.rr < rr0[r]) rate[r] = std::log(rr0[r] / S.rr) / (S.iters - iters0[r]);
     }
+    if (fixed == 0 && !due) chunk = chunk_of(left);
     if (!due) continue;
     // move the corrections into the FP64 iterate and evaluate its residual
     hipLaunchKernelGGL(k_fold_f32, dim3(grid_for(n)), dim3(256), 0, s, n, u_dev, c->u32);
@@ -998,6 +1023,15 @@ int solve_refined(fph_ssh_s* c, int nrhs, const double* b_dev, double* u_dev, co
         S.status |= std::isfinite(rz32[r]) ? FPH_ST_BREAKDOWN : FPH_ST_NONFINITE;
         S.done = fin[r] = 1;
       }
+    }
+    if (fixed == 0) {  // the next pause at the rate seen so far
+      double next = 0.0;
+      for (int r = 0; r < nrhs; ++r) {
+        const CgState& S = c->st_host[r];
+        const double goal = std::max(S.tol2 * S.bb, S.delta2 * S.rr_ref);
+        if (!fin[r]) next = std::max(next, rate[r] > 0.0 ? std::log(S.rr / goal) / rate[r] : kFirstChunk);
+      }
+      chunk = chunk_of(next);
     }
     SSH_CHECK(hipMemcpyAsync(sa, c->st_host, nrhs * sizeof(CgState), hipMemcpyHostToDevice, s));
   }
@@ -1064,7 +1098,8 @@ int fph_ssh_create(fph_ssh_t* out, const fph_lattice_t* lat, double g, int32_t m
   SSH_ALLOC(c->z, (size_t)max_rhs * d * sizeof(double));
   // partials: kRedBlocks per right-hand side from the vector kernels, Ltau from the operator
   SSH_ALLOC(c->part, (size_t)max_rhs * (lat->Ltau > kXrBlocks ? lat->Ltau : kXrBlocks) * sizeof(double));
-  SSH_ALLOC(c->part2, (size_t)max_rhs * (lat->Ltau > kRedBlocks ? lat->Ltau : kRedBlocks) * sizeof(double));
+  // (part2 also the r.z partials of the preconditioner, at most N)
+  SSH_ALLOC(c->part2, (size_t)max_rhs * std::max({(long)lat->Ltau, (long)kRedBlocks, (long)c->G.N}) * sizeof(double));
   SSH_ALLOC(c->part3, (size_t)max_rhs * (lat->Ltau > kRedBlocks ? lat->Ltau : kRedBlocks) * sizeof(double));
   SSH_ALLOC(c->st, 2 * (size_t)max_rhs * sizeof(CgState));
   SSH_ALLOC(c->hop32, 2 * d * sizeof(float2));
@@ -1189,7 +1224,9 @@ int ssh_solve(fph_ssh_t c, int32_t nrhs, const double* b_dev, double* u_dev, con
   hipStream_t s = (hipStream_t)stream;
   const long d = c->G.d;
   const long n = (long)nrhs * d;
-  const int chunk = opts->chunk > 0 ? (opts->chunk < kMaxChunk ? opts->chunk : kMaxChunk) : 64;
+  const int fixed = std::min((int)opts->chunk, kMaxChunk);  // 0: chosen from the convergence
+  int chunk = fixed > 0 ? fixed : kFirstChunk;
+  const int nbz = pre ? fph::precond_parts(c->pc, FPH_F64, nrhs) : kXrBlocks;
   double* z = pre ? c->z : c->r;  // z = F F^T r, or r itself
   const double* p2 = pre ? c->part2 : c->part;
   auto precondition = [&]() -> int {
@@ -1239,6 +1276,8 @@ int ssh_solve(fph_ssh_t c, int32_t nrhs, const double* b_dev, double* u_dev, con
   const bool fused = mtm_fusable(c);
   CgState* sa = c->st;               // the current state
   CgState* sb = c->st + c->max_rhs;  // the fused CG's next state
+  std::vector<double> rr0(bb);       // |r|^2 at the last look (at first |b|^2)
+  std::vector<int> iters0(nrhs, 0);
   for (int it = 0;;) {
     for (int k = 0; k < chunk; ++k, ++it) {
       // p = z + beta p (beta = 0 at the start, where p already holds z), formed
@@ -1253,7 +1292,7 @@ int ssh_solve(fph_ssh_t c, int32_t nrhs, const double* b_dev, double* u_dev, con
         a.st_new = sb;
         a.part_rr = c->part;
         a.part_rz = p2;
-        a.nbz = pre ? kRedBlocks : kXrBlocks;
+        a.nbz = nbz;
         a.from_state = k == 0;
         SSH_CHECK((launch_mtm_fused<double, true>(c, nrhs, pc, c->q, s, true, c->part3, a)));
         std::swap(sa, sb);
@@ -1267,12 +1306,12 @@ int ssh_solve(fph_ssh_t c, int32_t nrhs, const double* b_dev, double* u_dev, con
       hipLaunchKernelGGL(k_cg_xr<double>, dim3(kXrBlocks, nrhs), dim3(256), 0, s, d, sa, c->G.Ltau, pq,
                          (const double*)pn, (const double*)c->q, u_dev, c->r, c->part);
       SSH_CHECK(hipGetLastError());
-      rc = precondition();
-      if (rc != FPH_OK) return rc;
-      if (pre) SSH_CHECK(dots(c, nrhs, c->r, c->z, s, c->part2));
+      if (pre) {
+        rc = fph::precond_apply_dot(c->pc, FPH_F64, nrhs, c->r, c->z, c->part2, stream);
+        if (rc != FPH_OK) return rc;
+      }
       if (!fused || k + 1 == chunk) {  // the fused launch of the next step does it otherwise
-        hipLaunchKernelGGL(k_cg_scalar, dim3(nrhs), dim3(256), 0, s, 2, kXrBlocks, pre ? kRedBlocks : kXrBlocks,
-                           (const double*)c->part,
+        hipLaunchKernelGGL(k_cg_scalar, dim3(nrhs), dim3(256), 0, s, 2, kXrBlocks, nbz, (const double*)c->part,
                            p2, sa);
         SSH_CHECK(hipGetLastError());
       }
@@ -1281,8 +1320,16 @@ int ssh_solve(fph_ssh_t c, int32_t nrhs, const double* b_dev, double* u_dev, con
     SSH_CHECK(hipMemcpyAsync(c->st_host, sa, nrhs * sizeof(CgState), hipMemcpyDeviceToHost, s));
     SSH_CHECK(hipStreamSynchronize(s));
     bool all = true;
-    for (int r = 0; r < nrhs; ++r) all = all && c->st_host[r].done;
+    double left = 0.0;
+    for (int r = 0; r < nrhs; ++r) {
+      const CgState& S = c->st_host[r];
+      all = all && S.done;
+      if (!S.done) left = std::max(left, steps_left(rr0[r], S.rr, S.iters - iters0[r], S.tol2 * S.bb));
+      rr0[r] = S.rr;
+      iters0[r] = S.iters;
+    }
     if (all || it >= opts->maxiter) break;
+    if (fixed == 0) chunk = chunk_of(left);
   }
   // true residual and S_F = b . u
   SSH_CHECK(launch_apply(c, FPH_OP_MTM, nrhs, u_dev, c->r, s));
