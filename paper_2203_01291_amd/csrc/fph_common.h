@@ -212,6 +212,7 @@ struct PcInfo {
   double bmin, bmax;
   double s, c;          // A = s * Bbar - c
   int maxnp;
+  int kd64, kd32;       // blocks of F F^T applied as matrices, by precision (DenseBlocks)
   int pad;
 };
 
@@ -251,6 +252,19 @@ FPH_DEVINL double wave_sum_fixed(double v) {
   v += row_ror<2>(v);
   v += row_ror<1>(v);
   return ((readlane_d(v, 0) + readlane_d(v, 16)) + readlane_d(v, 32)) + readlane_d(v, 48);
+}
+
+// The same in the precision of the values.
+FPH_DEVINL double wave_total(double v) { return wave_sum_fixed(v); }
+FPH_DEVINL float wave_total(float v) {
+  v += row_ror<8>(v);
+  v += row_ror<4>(v);
+  v += row_ror<2>(v);
+  v += row_ror<1>(v);
+  auto at = [&](int l) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+  };
+  return ((at(0) + at(16)) + at(32)) + at(48);
 }
 
 // Sum of one double over the workgroup; result valid in thread 0.  LAST:

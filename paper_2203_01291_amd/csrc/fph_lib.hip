@@ -499,7 +499,8 @@ int fph_set_field(fph_handle_t h, const double* x_dev, double a1, double a2, voi
   hipLaunchKernelGGL(k_dbar, dim3((h->g.N + 63) / 64), dim3(64, 16), 0, s, h->g.N, h->g.Ltau,
                      h->E64, h->c4, h->dbar64, h->dbar32);
   FPH_CHECK(hipGetLastError());
-  FPH_CHECK(pc_set_field(&h->pc, h->g, h->dbar64, h->lat.dtau, h->lat.t, h->a1, h->a2, s));
+  FPH_CHECK(pc_set_field(&h->pc, h->g, h->dbar64, h->lat.dtau, h->lat.t, h->a1, h->a2, s, 0,
+                         true));
   h->have_field = true;
   return FPH_OK;
 }
@@ -522,7 +523,7 @@ int fph_set_fields(fph_handle_t h, int32_t nfields, int32_t rhs_per_field, const
   FPH_CHECK(hipGetLastError());
   for (int f = 0; f < nfields; ++f)
     FPH_CHECK(pc_set_field(&h->pc, h->g, h->dbar64 + (long)f * h->g.N, h->lat.dtau, h->lat.t,
-                           h->a1, h->a2, s, f));
+                           h->a1, h->a2, s, f, false));
   h->g.fs = d;
   h->g.rpf = rhs_per_field;
   h->nfields = nfields;
@@ -1075,7 +1076,7 @@ hipError_t batch_enqueue(fph_batch_s* b, const BatchRunCfg& c, hipStream_t s) {
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(k_pc_bounds, dim3(1), dim3(256), 0, s, N, L.Ltau,
                        (const double*)(b->dbar64 + b->noff[k]), L.dtau, L.t, c.a1, c.a2,
-                       b->info + k, b->np + b->npoff[k]);
+                       b->info + k, b->np + b->npoff[k], 0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(k_pc_coef, dim3(L.Ltau / 2), dim3(256), 0, s, L.Ltau,
                        (const PcInfo*)(b->info + k), (const int*)(b->np + b->npoff[k]),

@@ -48,6 +48,9 @@ struct PcTables {
   int* np;         // N_P(w) for w < Ltau (device)
   double2* coef64; // [H][kNPMax]: c_m(2k)
   float2* coef32;
+  int kdmax;       // frequencies with room for a matrix (0: none)
+  double2* dense64;  // [kdmax][N][N]: the blocks of F F^T (one shared field only)
+  float2* dense32;
   void* Z;         // complex workspace, max_rhs * H * N (double2)
   void* Z2;
   double th, c4;   // tanh(dtau t) and cosh(dtau t)^4: P_A P_B = c4 P'_A P'_B, C2' = [[1, th], [th, 1]]
@@ -102,12 +105,35 @@ __global__ void k_pc_twiddles(int H, int H1, int H2, int Ltau, double2* tw64, do
   }
 }
 
+// How many blocks of F F^T, longest series first, to apply as N x N matrices
+// (k_pc_dense, k_kpm_split).  A block's series is a chain of 2 (N_P - 1)
+// exchanges of about 0.2 us each, and the longest one left sets the kernel's
+// time; a matrix is read once per apply by many workgroups side by side, at
+// some 4 MB per us beside the series, after about 1 us of start.  N_P(0) is
+// large only at the lowest frequencies (its a1/phi term), so a few matrices
+// can shorten the chain several times.  The count with the least estimated
+// time, if it gains at least 1 us per apply.  F F^T of two vectors, series / with
+// matrices: L = 16, Ltau 160, FP64 (N_P 64) 43.1 / 14.5 us; L = 32, Ltau 160, FP32
+// (N_P 45) 38.5 / 20.1 us; L = 32, Ltau 400, FP32 (N_P 63) 54.1 / 26.1 us.
+FPH_DEVINL int dense_count(const int* np, int N, int kdmax, int elem) {
+  double best = 0.4 * (np[0] - 1) - 1.0;
+  int kd = 0;
+  for (int k = 1; k <= kdmax; ++k) {
+    const double t = fmax(0.4 * (np[k] - 1), 1.0 + k * ((double)N * N * elem / 4e6));
+    if (t < best) {
+      best = t;
+      kd = k;
+    }
+  }
+  return kd;
+}
+
 // Bounds of the spectrum of Bbar = diag(dbar) C and N_P(w).  One block.
 //   bmin = min(dbar) e^{-4 dtau |t|}, bmax = max(dbar) e^{+4 dtau |t|}
 //   N_P(w) = max(1, floor(db (a1/phi_w' + a2))), w' = min(w, Ltau-1-w)
 __global__ void __launch_bounds__(256)
 k_pc_bounds(int N, int Ltau, const double* __restrict__ dbar, double dtau, double t, double a1,
-            double a2, PcInfo* info, int* np) {
+            double a2, PcInfo* info, int* np, int kdmax) {
   __shared__ double smin[256], smax[256];
   __shared__ int snp[256];
   double lo = 1e300, hi = -1e300;
@@ -149,6 +175,9 @@ k_pc_bounds(int N, int Ltau, const double* __restrict__ dbar, double dtau, doubl
     info->s = db > 0.0 ? 2.0 / db : 0.0;
     info->c = db > 0.0 ? 1.0 + 2.0 * bmin / db : 0.0;
     info->maxnp = snp[0];
+    // (np[o], o < H, is the order of the o-th longest series, w' = o)
+    info->kd64 = kdmax ? dense_count(np, N, kdmax, sizeof(double2)) : 0;
+    info->kd32 = kdmax ? dense_count(np, N, kdmax, sizeof(float2)) : 0;
   }
 }
 
@@ -1335,12 +1364,75 @@ __host__ __device__ inline int kpm_split_buf(const Geom& g) {
 // block at L = 32, Ltau = 400, FP32, 30 exchanges: 12.1 -> 9.7 us.
 enum { kHalves = 0, kOneWave = 1, kWavePerPart = 2 };
 
+// o = v of the lane with the other part of the plaquette.
+template <typename T, int LAY>
+FPH_DEVINL void split_swap(const T (&v)[4], T (&o)[4], T* xs, bool im, int lane) {
+  if constexpr (LAY == kWavePerPart) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) xs[(im * 4 + m) * 64 + lane] = v[m];
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < 4; ++m) o[m] = xs[((1 - im) * 4 + m) * 64 + lane];
+    __syncthreads();
+  } else {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) o[m] = __shfl_xor(v[m], 32, 64);
+  }
+}
+
+// Frequency index of the o-th longest series: 0, H-1, 1, H-2, ...
+FPH_DEVINL int block_freq(int o, int H) { return (o % 2 == 0) ? o / 2 : H - 1 - o / 2; }
+
+// Rows of a block matrix per workgroup of nt threads: two per wave.
+__host__ __device__ constexpr int dense_rows_per(int nt) { return nt / 32; }
+
+// One workgroup's rows of block o = b / RB (RB row groups per block) of
+// F F^T as a matrix: Zo = G Z for every right-hand side, the lanes of a wave
+// along the columns of two rows, Z of the block in LDS.  Bound by reading G
+// from the caches (L = 16, FP64: 1 MB per block; L = 32, FP32: 8 MB).
+template <typename T, int NT>
+FPH_DEVINL void dense_rows(const Geom& g, int H, int nrhs, int kd, int b,
+                           const typename Cplx<T>::type* __restrict__ dense,
+                           const typename Cplx<T>::type* __restrict__ Z,
+                           typename Cplx<T>::type* __restrict__ Zo, typename Cplx<T>::type* xs,
+                           const StIO& io) {
+  using T2 = typename Cplx<T>::type;
+  const int N = g.N, RB = (N + dense_rows_per(NT) - 1) / dense_rows_per(NT);
+  const int o = b / RB;
+  if (o >= kd) return;
+  const int k = block_freq(o, H);
+  const int lane = threadIdx.x & 63;
+  const int row = (b - o * RB) * dense_rows_per(NT) + 2 * (threadIdx.x >> 6);
+  const T2* G0 = dense + ((long)o * N + min(row, N - 2)) * N;  // (N is even: two whole rows)
+  const T2* G1 = G0 + N;
+  for (int r = 0; r < nrhs; ++r) {
+    if (io.in != nullptr && state_done(io, r)) continue;
+    const T2* Zr = Z + ((long)r * H + k) * N;
+    __syncthreads();  // every wave is done with the previous values
+    for (int c = threadIdx.x; c < N; c += NT) xs[c] = Zr[c];
+    __syncthreads();
+    T2 a0 = T2{0, 0}, a1 = T2{0, 0};
+#pragma unroll 4
+    for (int c = lane; c < N; c += 64) {
+      const T2 x = xs[c];
+      cmac(a0, G0[c], x);
+      cmac(a1, G1[c], x);
+    }
+    a0.x = wave_total(a0.x);
+    a0.y = wave_total(a0.y);
+    a1.x = wave_total(a1.x);
+    a1.y = wave_total(a1.y);
+    if (lane == 0 && row < N) st2c(Zo + ((long)r * H + k) * N + row, a0, a1);
+  }
+}
+
 template <typename T, int NT, bool ROW16, int LAY>
 __global__ void __launch_bounds__(NT)
 k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
             const int* __restrict__ np, const typename Cplx<T>::type* __restrict__ coef,
             const T* __restrict__ dbar, T th, T c4, const typename Cplx<T>::type* __restrict__ Z,
-            typename Cplx<T>::type* __restrict__ Zo, StIO io) {
+            typename Cplx<T>::type* __restrict__ Zo, const typename Cplx<T>::type* __restrict__ dense,
+            StIO io) {
   using T2 = typename Cplx<T>::type;
   static_assert(NT <= kNPMax, "one coefficient per thread is loaded ahead");
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1353,28 +1445,22 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
   T* buf0 = reinterpret_cast<T*>(smem_raw) + (im ? nbuf : 0);
   T* buf1 = buf0 + 2 * nbuf;
   T2* cfs = reinterpret_cast<T2*>(reinterpret_cast<T*>(smem_raw) + 4 * nbuf);
+  // Blocks of F F^T applied as matrices, by the workgroups past the series'.
+  const int kd = dense ? (sizeof(T) == 8 ? info->kd64 : info->kd32) : 0;
+  if ((int)blockIdx.x >= H * nrhs) {
+    dense_rows<T, NT>(g, H, nrhs, kd, (int)blockIdx.x - H * nrhs, dense, Z, Zo,
+                      reinterpret_cast<T2*>(smem_raw), io);
+    return;
+  }
   const int ko = blockIdx.x / nrhs;
   const int r = blockIdx.x % nrhs;
-  const int k = (ko % 2 == 0) ? ko / 2 : H - 1 - ko / 2;
+  const int k = block_freq(ko, H);
   const int q = LAY == kWavePerPart ? lane : (threadIdx.x >> 6) * 32 + (lane & 31);
   const bool own = q < g.Q;
   const Win w = make_win(g, q, own);
   const int i0 = w.x0 + w.row[1], iL = i0 + g.L;
 
-  // o = the other part's v.
-  auto swap = [&](const T (&v)[4], T (&o)[4]) {
-    if constexpr (LAY == kWavePerPart) {
-#pragma unroll
-      for (int m = 0; m < 4; ++m) xs[(im * 4 + m) * 64 + lane] = v[m];
-      __syncthreads();
-#pragma unroll
-      for (int m = 0; m < 4; ++m) o[m] = xs[((1 - im) * 4 + m) * 64 + lane];
-      __syncthreads();
-    } else {
-#pragma unroll
-      for (int m = 0; m < 4; ++m) o[m] = __shfl_xor(v[m], 32, 64);
-    }
-  };
+  auto swap = [&](const T (&v)[4], T (&o)[4]) { split_swap<T, LAY>(v, o, xs, im, lane); };
 
   // Solver state: as in k_kpm, one block per right-hand side reads and
   // writes it, folding it between the two series.
@@ -1388,7 +1474,7 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
   dbar += (long)f * g.N;
   const int NP = np[2 * k];
   const T sA = (T)info->s, cA = (T)info->c;
-  const bool idle = io.in != nullptr && !stt && state_done(io, r);
+  const bool idle = ko < kd || (io.in != nullptr && !stt && state_done(io, r));
   const T2 c_first = coef[(long)k * kNPMax + threadIdx.x];
   T x[4], db[4];
   {
@@ -1434,6 +1520,62 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
     st2c(Zout, T2{sel(im, t0, x[0]), sel(im, x[2], t0)}, T2{sel(im, t1, x[1]), sel(im, x[3], t1)});
   }
   if (stt) state_end(io, r, &s_sh, P_NONE, 0.0, 0, 1, true);
+}
+
+// The block matrices G = f(A) f(A)^H of F F^T that k_kpm_split applies instead
+// of their series: workgroup (j, o) runs the two series of order o on the
+// unit vector of site j, in FP64, and stores the result, column j, as row j
+// conjugated (G is Hermitian), so that the store is contiguous.  The FP32 matrix
+// is the FP64 one rounded, so FP32 applies are closer to the exact series than
+// the FP32 recurrence was (relative error 1.1e-6 -> 1.8e-7 at L = 32, Ltau 160,
+// N_P 45; FP64 unchanged, 1.7e-14).  Built with every shared field: 34 us for 16
+// blocks at L = 16, 25-115 us at L = 32, gained back within five applies.
+template <int NT, bool ROW16, int LAY>
+__global__ void __launch_bounds__(NT)
+k_pc_dense(Geom g, int H, const PcInfo* __restrict__ info, const int* __restrict__ np,
+           const double2* __restrict__ coef, const double* __restrict__ dbar, double th, double c4,
+           double2* __restrict__ G64, float2* __restrict__ G32) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ double xs[LAY == kWavePerPart ? 2 * 4 * 64 : 1];
+  const int o = blockIdx.y, j = blockIdx.x;
+  const int kd64 = info->kd64, kd32 = info->kd32;
+  if (o >= max(kd64, kd32)) return;
+  const int nbuf = kpm_split_buf<double>(g);
+  const int lane = threadIdx.x & 63;
+  const bool im = LAY == kWavePerPart ? threadIdx.x >= 64 : lane >= 32;
+  double* buf0 = reinterpret_cast<double*>(smem_raw) + (im ? nbuf : 0);
+  double* buf1 = buf0 + 2 * nbuf;
+  double2* cfs = reinterpret_cast<double2*>(reinterpret_cast<double*>(smem_raw) + 4 * nbuf);
+  const int k = block_freq(o, H);
+  const int q = LAY == kWavePerPart ? lane : (threadIdx.x >> 6) * 32 + (lane & 31);
+  const bool own = q < g.Q;
+  const Win w = make_win(g, q, own);
+  const int i0 = w.x0 + w.row[1], iL = i0 + g.L;
+  auto swap = [&](const double (&v)[4], double (&ov)[4]) {
+    split_swap<double, LAY>(v, ov, xs, im, lane);
+  };
+  const int NP = np[2 * k];
+  for (int m = threadIdx.x; m < NP; m += NT) cfs[m] = coef[(long)k * kNPMax + m];
+  const double db[4] = {c4 * dbar[i0], c4 * dbar[i0 + 1], c4 * dbar[iL], c4 * dbar[iL + 1]};
+  const int at[4] = {i0, i0 + 1, iL, iL + 1};
+  double x[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) x[m] = (!im && at[m] == j) ? 1.0 : 0.0;
+  __syncthreads();
+  const double sA = info->s, cA = info->c;
+  cheb_series_split<double, true, ROW16, LAY != kHalves>(w, NP, cfs, sA, cA, x, db, buf0, buf1, th, im, q, g.Q,
+                                                         swap);
+  cheb_series_split<double, false, ROW16, LAY != kHalves>(w, NP, cfs, sA, cA, x, db, buf0, buf1, th, im, q, g.Q,
+                                                          swap);
+  double ov[4];
+  swap(x, ov);
+  if (own) {  // row y0 by the real lane, row y0+1 by the imaginary one
+    const double2 v0 = make_double2(sel(im, ov[2], x[0]), -sel(im, x[2], ov[0]));
+    const double2 v1 = make_double2(sel(im, ov[3], x[1]), -sel(im, x[3], ov[1]));
+    const long at0 = ((long)o * g.N + j) * g.N + (im ? iL : i0);
+    if (o < kd64) st2c(G64 + at0, v0, v1);
+    if (o < kd32) st2c(G32 + at0, make_float2((float)v0.x, (float)v0.y), make_float2((float)v1.x, (float)v1.y));
+  }
 }
 
 // Per-block Chebyshev apply.  op 0: F (series in A), 1: F^T (conjugate
@@ -1597,6 +1739,15 @@ inline hipError_t pc_create(PcTables* pc, const Geom& g, int max_rhs) {
   PCALLOC(pc->np, (size_t)max_rhs * g.Ltau * sizeof(int));
   PCALLOC(pc->coef64, (size_t)max_rhs * H * kNPMax * sizeof(double2));
   PCALLOC(pc->coef32, (size_t)max_rhs * H * kNPMax * sizeof(float2));
+  // Matrices of the longest blocks: slices of up to 1 024 sites (above, one
+  // would be read slower than its series runs), systems that the launch
+  // sequence solves, up to 16 blocks and 100 MB.
+  const size_t nn = (size_t)g.N * g.N;
+  pc->kdmax = g.N <= 1024 && g.d > 2048 ? (int)std::min<size_t>({16, (size_t)H - 1, (100u << 20) / (nn * 24)}) : 0;
+  if (pc->kdmax > 0) {
+    PCALLOC(pc->dense64, pc->kdmax * nn * sizeof(double2));
+    PCALLOC(pc->dense32, pc->kdmax * nn * sizeof(float2));
+  }
   PCALLOC(pc->Z, (size_t)max_rhs * H * g.N * sizeof(double2));
   PCALLOC(pc->Z2, (size_t)max_rhs * H * g.N * sizeof(double2));
 #undef PCALLOC
@@ -1608,25 +1759,44 @@ inline hipError_t pc_create(PcTables* pc, const Geom& g, int max_rhs) {
 
 inline void pc_destroy(PcTables* pc) {
   void* ptrs[] = {pc->tw64, pc->W64, pc->F64, pc->tw32, pc->W32, pc->F32, pc->info, pc->np,
-                  pc->coef64, pc->coef32, pc->Z, pc->Z2};
+                  pc->coef64, pc->coef32, pc->dense64, pc->dense32, pc->Z, pc->Z2};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   std::memset(pc, 0, sizeof(*pc));
 }
 
-// Series tables of field f from its dbar (dbar64 points at that field's N values).
+template <int NT, bool ROW16 = false, int LAY = kHalves>
+hipError_t pc_launch_dense(const PcTables* pc, const Geom& g, const double* dbar, hipStream_t s) {
+  const size_t lds = 4 * (size_t)kpm_split_buf<double>(g) * sizeof(double) + kNPMax * sizeof(double2);
+  auto kern = k_pc_dense<NT, ROW16, LAY>;
+  hipError_t e = allow_lds((const void*)kern, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(g.N, pc->kdmax), dim3(NT), lds, s, g, pc->H, (const PcInfo*)pc->info,
+                     (const int*)pc->np, (const double2*)pc->coef64, dbar, pc->th, pc->c4, pc->dense64,
+                     pc->dense32);
+  return hipGetLastError();
+}
+
+// Series tables of field f from its dbar (dbar64 points at that field's N
+// values), and of a field shared by every right-hand side the block matrices.
 inline hipError_t pc_set_field(PcTables* pc, const Geom& g, const double* dbar64, double dtau,
-                               double t, double a1, double a2, hipStream_t s, int f = 0) {
+                               double t, double a1, double a2, hipStream_t s, int f, bool shared) {
   PcInfo* info = pc->info + f;
   int* np = pc->np + (long)f * g.Ltau;
   hipLaunchKernelGGL(k_pc_bounds, dim3(1), dim3(256), 0, s, g.N, g.Ltau, dbar64, dtau, t, a1, a2,
-                     info, np);
+                     info, np, shared ? pc->kdmax : 0);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_pc_coef, dim3(pc->H), dim3(256), 0, s, g.Ltau, (const PcInfo*)info,
                      (const int*)np, pc->coef64 + (long)f * pc->H * kNPMax,
                      pc->coef32 + (long)f * pc->H * kNPMax);
-  return hipGetLastError();
+  e = hipGetLastError();
+  if (e != hipSuccess || !shared || pc->kdmax == 0) return e;
+  if (g.hL == 16 && g.Q == 256) return pc_launch_dense<512, true>(pc, g, dbar64, s);
+  if (g.Q <= 32) return pc_launch_dense<64, false, kOneWave>(pc, g, dbar64, s);
+  if (g.Q <= 64) return pc_launch_dense<128, false, kWavePerPart>(pc, g, dbar64, s);
+  if (g.Q <= 128) return pc_launch_dense<256>(pc, g, dbar64, s);
+  return pc_launch_dense<512>(pc, g, dbar64, s);
 }
 
 // LDS bytes of a transform workgroup with tile width 2^lks.
@@ -1770,8 +1940,14 @@ hipError_t pc_launch_kpm_split(const PcTables* pc, const Geom& g, const T* dbar,
   hipError_t e = allow_lds((const void*)kern, lds);
   if (e != hipSuccess) return e;
   const auto* cf = (const T2*)(sizeof(T) == 8 ? (const void*)pc->coef64 : (const void*)pc->coef32);
-  hipLaunchKernelGGL(kern, dim3(pc->H * nrhs), dim3(NT), lds, s, g, pc->H, nrhs, op, pc->info,
-                     pc->np, cf, dbar, th, c4, Z, Zo, io);
+  // The matrices hold the blocks of F F^T of one field shared by every
+  // right-hand side.
+  const bool dn = op == 2 && pc->kdmax > 0 && g.fs == 0;
+  const T2* dense = dn ? (const T2*)(sizeof(T) == 8 ? (const void*)pc->dense64 : (const void*)pc->dense32)
+                       : nullptr;
+  const int rows = dense_rows_per(NT), RB = (g.N + rows - 1) / rows;
+  hipLaunchKernelGGL(kern, dim3(pc->H * nrhs + (dn ? pc->kdmax * RB : 0)), dim3(NT), lds, s, g, pc->H, nrhs,
+                     op, pc->info, pc->np, cf, dbar, th, c4, Z, Zo, dense, io);
   return hipGetLastError();
 }
 

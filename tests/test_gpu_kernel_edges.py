@@ -161,3 +161,34 @@ def test_small_solve_budget(L, Ltau, prec):
     s.set_field(torch.from_numpy(rng.standard_normal((Ltau, lat.N))).cuda())
     _, st = s.solve(torch.from_numpy(rng.standard_normal((1, Ltau, lat.N))).cuda(), tol=1e-12, prec=prec, maxiter=7)
     assert st[0]["status"] == 2 and st[0]["iters"] == 7
+
+
+# Blocks of F F^T applied as matrices (long series at the lowest frequencies): one and several
+# right-hand sides, a few and many plaquettes, and a handle that goes to a field per right-hand side
+# (series only) and back, where no matrix of an earlier field may be left.
+@pytest.mark.parametrize("L,Ltau", [(8, 100), (10, 160), (16, 80), (20, 60), (30, 80), (32, 160)])
+def test_precond_matrix_blocks(L, Ltau):
+    lat = OL.Lattice(L, Ltau, 0.1, 1.0, -0.1, 1.1)
+    rng = np.random.default_rng(7 * L + Ltau)
+    xs = rng.standard_normal((2, Ltau, lat.N)) * np.array([1.0, 0.5])[:, None, None]
+    v = rng.standard_normal((2, Ltau, lat.N))
+    C = OL.sparse_C(lat).tocsr()
+    pcs = [OP.Preconditioner(lat, x, 1.0, 1.0, C=C) for x in xs]
+    ref = [[pc.apply_FFt(w) for w in v] for pc in pcs]
+    s = _solver(lat, 2)
+    xg, vg = torch.from_numpy(xs).cuda(), torch.from_numpy(v).cuda()
+
+    def check(n, want):
+        for r in range(n):
+            assert _relmax(s.precond(vg[:n].contiguous(), "FFT").cpu().numpy()[r], want[r]) < 1e-12
+            got = s.precond(vg[:n].float().contiguous(), "FFT").cpu().numpy()[r]
+            assert _relmax(got.astype(np.float64), want[r]) < 1e-5
+
+    s.set_field(xg[0])
+    assert max(s.precond_info()[1]) >= 10  # the longest series is worth a matrix
+    check(1, ref[0])
+    check(2, ref[0])
+    s.set_fields(xg)
+    check(2, [ref[0][0], ref[1][1]])
+    s.set_field(xg[1])
+    check(2, ref[1])
