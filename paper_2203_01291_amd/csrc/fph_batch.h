@@ -164,18 +164,23 @@ FPH_DEVINL void batch_solve_item(const BatchItem& it, double tol, int maxiter, d
   bb = block_allsum<NT>(bb, red_sh, bcast);
   rr = block_allsum<NT>(rr, red_sh, bcast);
   const double tol2 = tol * tol * bb;
-  double rz = rr, rr_ref = rr, rr_true = bb, beta = 0.0;
+  double rz = 1.0, rr_ref = rr, rr_true = bb;
   int fresh = 1, iter = 0, outer = 0, matvecs = 0, status = 0;
   float* pold = it.pa;
   float* pnew = it.pb;
   if (bb == 0.0) status = 1;
   if (!isfinite(bb)) status = 8;
-  if (status == 0 && pre) {
-    rz = bpc_apply<NT>(it, opaque(g), it.r, it.z, lds, red_sh, bcast);
-    if (!(rz > 0.0) || !isfinite(rz)) status = isfinite(rz) ? 4 : 8;
-  }
 
+  // (Each phase has one place in the loop: the instructions of an iteration
+  // stay within the 64 KB instruction cache.)
   while (status == 0) {
+    const double rz_new = pre ? bpc_apply<NT>(it, opaque(g), it.r, it.z, lds, red_sh, bcast) : rr;
+    if (!(rz_new > 0.0) || !isfinite(rz_new)) {
+      status = isfinite(rz_new) ? 4 : 8;
+      break;
+    }
+    const double beta = fresh ? 0.0 : rz_new / rz;
+    rz = rz_new;
     // Direction update fused into the operator: Ap = A (z + beta p).
     {
       float* lds4 = reinterpret_cast<float*>(lds) + 4L * so * g.N;
@@ -213,16 +218,7 @@ FPH_DEVINL void batch_solve_item(const BatchItem& it, double tol, int maxiter, d
       status = 8;
       break;
     }
-    if (!(rr <= tol2 || rr < delta * delta * rr_ref || iter >= maxiter)) {
-      const double rz_new = pre ? bpc_apply<NT>(it, opaque(g), it.r, it.z, lds, red_sh, bcast) : rr;
-      if (!(rz_new > 0.0) || !isfinite(rz_new)) {
-        status = isfinite(rz_new) ? 4 : 8;
-        break;
-      }
-      beta = rz_new / rz;
-      rz = rz_new;
-      continue;
-    }
+    if (!(rr <= tol2 || rr < delta * delta * rr_ref || iter >= maxiter)) continue;
 
     // FP64 residual replacement.
     const double rr_iter = rr;
@@ -257,13 +253,6 @@ FPH_DEVINL void batch_solve_item(const BatchItem& it, double tol, int maxiter, d
     for (long k = 4L * threadIdx.x; k < d; k += 4L * NT) acc_rr += sq4(Vec4<float>::ld(it.r + k));
     rr = block_allsum<NT>(acc_rr, red_sh, bcast);
     if (rr > 100.0 * rr_iter) fresh = 1;  // replaced residual far from the iterated one
-    const double rz_new = pre ? bpc_apply<NT>(it, opaque(g), it.r, it.z, lds, red_sh, bcast) : rr;
-    if (!(rz_new > 0.0) || !isfinite(rz_new)) {
-      status = isfinite(rz_new) ? 4 : 8;
-      break;
-    }
-    beta = rz_new / rz;
-    rz = rz_new;
     rr_ref = rr;
   }
 
