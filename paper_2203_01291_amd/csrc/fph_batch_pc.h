@@ -34,6 +34,7 @@ struct PcView {
   const T2* F;          // H1 x H1 then H2 x H2 DFT matrices
   T c4;                 // cosh(dtau t)^4 (joins dbar in the series)
   int H, H1, H2;
+  const T2* dense;      // matrices of the longest blocks (k_pc_dense), or nullptr
 };
 
 // LDS budgets of the transforms' tiles and of the series' buffers: a workgroup
@@ -55,7 +56,7 @@ __host__ __device__ inline int bpc_tile_log2(int N, int H, int budget, int elem)
 // LDS (complex values) of the transforms' tables and tiles, and of the series of
 // one frequency.
 __host__ __device__ inline long bpc_lds_tables(int H1, int H2) {
-  return (long)H1 * H1 + (long)H2 * H2 + (long)H1 * H2;
+  return ((long)H1 * H1 + (long)H2 * H2 + (long)H1 * H2 + 1) & ~1L;  // (what follows stays aligned)
 }
 __host__ __device__ inline long bpc_lds_tf(int H, int lks) { return (2L * H) << lks; }
 __host__ __device__ inline long bpc_lds_series(int L) {
@@ -66,6 +67,7 @@ __host__ __device__ inline long bpc_lds_series(int L) {
 // (elem bytes per complex value): with up to 32 plaquettes one wave each, else
 // Q threads each.
 constexpr int kBpcWaveQ = 32;
+constexpr int kBpcDenseN = 36;  // most sites of a block matrix here
 __host__ __device__ inline int bpc_groups(int L, int H, int nt, int budget, int elem) {
   const int Q = L * L / 4;
   const int fit = budget / (int)(bpc_lds_series(L) * elem);
@@ -267,7 +269,8 @@ struct BpcCoef {
 // F F^T on every frequency block of Z, in place: block k gets the
 // conjugate series in A^T, then the series in A (as k_kpm with op 2).  Up to
 // kBpcWaveQ plaquettes each wave runs blocks of its own, its parts on its two
-// halves and without barriers (cheb_series_split).  Else the workgroup takes the blocks in rounds of G, longest series first (order o
+// halves and without barriers (cheb_series_split), after the longest blocks as
+// matrices where there are any.  Else the workgroup takes the blocks in rounds of G, longest series first (order o
 // serves frequency w' = o, and N_P does not grow with it), each group of Q
 // threads one block in its own LDS buffers, all with the step count of the
 // round's first block, so every thread takes the same barriers.  Threads
@@ -296,8 +299,24 @@ FPH_DEVINL void bpc_series(const Geom& g, const PcView<T>& pc, T th,
 #pragma unroll
       for (int m = 0; m < 4; ++m) o[m] = __shfl_xor(v[m], 32, 64);
     };
+    // The longest blocks as matrices, a thread per row, up to 36 sites (L = 4, 6; a
+    // row is a chain of loads eight columns at a time, at L = 8 longer than the
+    // series: 28 000 against 16 000 cycles at Ltau 32): G is Hermitian, so the lanes
+    // read along its rows and take the conjugate.
+    const int kd = pc.dense == nullptr || g.N > kBpcDenseN ? 0 : sizeof(T) == 8 ? pc.info->kd64 : pc.info->kd32;
+    for (int o0 = 0, per = NT / g.N; o0 < kd; o0 += per) {
+      const int o = o0 + (int)threadIdx.x / g.N, row = threadIdx.x % g.N;
+      const bool mine = (int)threadIdx.x < per * g.N && o < kd;
+      T2* Zk = Z + (long)freq(mine ? o : o0) * g.N;
+      const T2* Gr = pc.dense + (long)(mine ? o : o0) * g.N * g.N + row;
+      T2 acc = T2{0, 0};
+#pragma unroll 8
+      for (int c = 0; c < g.N; ++c) cmacc(acc, Gr[(long)c * g.N], Zk[c]);
+      __syncthreads();  // every row of these blocks has read its values
+      if (mine) Zk[row] = acc;
+    }
     if (wave < G) {
-      for (int o = wave; o < H; o += G) {
+      for (int o = kd + wave; o < H; o += G) {
         const int k = freq(o), NP = __builtin_amdgcn_readfirstlane(pc.np[2 * k]);
         const WaveCoef<T2> cf(pc.coef + (long)k * kNPMax, NP), cft(pc.coef + (long)k * kNPMax, NP);
         T2* Zk = Z + (long)k * g.N;

@@ -739,8 +739,11 @@ struct SolveRun {
 // 6.0; plain FP32-refined L = 10, Ltau 60: 8.3 / 7.1, L = 16, Ltau 40: 5.9 / 6.9).
 // More right-hand sides than compute units would queue.
 bool small_route(const SolveRun& run) {
+  const PcTables& pc = run.h->pc;
   const long most = run.pre ? 2048 : run.mixed ? 6144 : 4096;
-  return run.h->g.d <= most && run.h->g.Q <= kSmallNT && run.nrhs <= 256;
+  const size_t lds = run.mixed ? small_lds<float>(run.h->g, pc.H1, pc.H2, run.pre)
+                               : small_lds<double>(run.h->g, pc.H1, pc.H2, run.pre);
+  return lds <= kSmallLds && run.h->g.d <= most && run.h->g.Q <= kSmallNT && run.nrhs <= 256;
 }
 
 template <typename TI>
@@ -752,7 +755,6 @@ hipError_t small_launch(const fph_handle_s* h, int nrhs, const SolveRun& run, co
   SmallArgs<TI> A;
   A.s = a;
   A.uit = uit;
-  A.Z = reinterpret_cast<T2*>(pc.Z);
   A.pc = PcView<TI>{pc.info,
                     pc.np,
                     pick(pc.coef64, pc.coef32),
@@ -763,7 +765,8 @@ hipError_t small_launch(const fph_handle_s* h, int nrhs, const SolveRun& run, co
                     (TI)pc.c4,
                     pc.H,
                     pc.H1,
-                    pc.H2};
+                    pc.H2,
+                    pc.kdmax > 0 && h->g.fs == 0 ? pick(pc.dense64, pc.dense32) : nullptr};
   A.pre = run.pre;
   A.zero = run.zero;
   A.total = run.total;

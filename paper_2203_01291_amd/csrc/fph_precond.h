@@ -1740,10 +1740,13 @@ inline hipError_t pc_create(PcTables* pc, const Geom& g, int max_rhs) {
   PCALLOC(pc->coef64, (size_t)max_rhs * H * kNPMax * sizeof(double2));
   PCALLOC(pc->coef32, (size_t)max_rhs * H * kNPMax * sizeof(float2));
   // Matrices of the longest blocks: slices of up to 1 024 sites (above, one
-  // would be read slower than its series runs), systems that the launch
-  // sequence solves, up to 16 blocks and 100 MB.
+  // would be read slower than its series runs), up to 16 blocks and 100 MB; not
+  // for larger slices of a system that one workgroup solves (bpc_series takes
+  // them up to 36 sites).
   const size_t nn = (size_t)g.N * g.N;
-  pc->kdmax = g.N <= 1024 && g.d > 2048 ? (int)std::min<size_t>({16, (size_t)H - 1, (100u << 20) / (nn * 24)}) : 0;
+  pc->kdmax = g.N <= 1024 && (g.d > 2048 || g.N <= 36)
+                  ? (int)std::min<size_t>({16, (size_t)H - 1, (100u << 20) / (nn * 24)})
+                  : 0;
   if (pc->kdmax > 0) {
     PCALLOC(pc->dense64, pc->kdmax * nn * sizeof(double2));
     PCALLOC(pc->dense32, pc->kdmax * nn * sizeof(float2));

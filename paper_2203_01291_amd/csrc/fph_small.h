@@ -18,31 +18,32 @@
 namespace fph {
 
 constexpr int kSmallNT = 512;
+constexpr size_t kSmallLds = (size_t)156 << 10;  // LDS a workgroup may take
 
 template <typename TI>
 struct SmallArgs {
   SlotArgs<TI> s;
   TI* uit;                       // what the update advances: u_dev, or the FP32 correction
-  typename Cplx<TI>::type* Z;    // transform workspace, [nrhs][H][N]
   PcView<TI> pc;                 // of field 0
   int pre, zero;
   long total;                    // slots: 1 + maxiter + max_outer
   SolveInit init;
 };
 
-// LDS bytes: the transforms' tables, kept for the whole solve, then the larger
-// of four FP64 slices per chunk of the sweep, the transforms' tiles and the
+// LDS bytes: the transforms' tables, r and, preconditioned, z and the transform
+// workspace (a memory round trip costs some 1 000 cycles here), kept for the
+// whole solve; then the larger of four FP64 slices per chunk of the sweep, the transforms' tiles and the
 // series' buffers.
 template <typename TI>
 size_t small_lds(const Geom& g, int H1, int H2, bool pre) {
   const int S = (g.Q <= kSmallNT) ? kSmallNT / g.Q : 1, H = H1 * H2;
   size_t lds = 4 * (size_t)S * g.N * sizeof(double);
-  if (!pre) return lds;
+  if (!pre) return lds + g.d * sizeof(TI);
   constexpr int elem = 2 * sizeof(TI);
   const long tf = bpc_lds_tf(H, bpc_tile_log2(g.N, H, kBpcLdsAlone, elem));
   const long se = bpc_groups(g.L, H, kSmallNT, kBpcLdsAlone, elem) * bpc_lds_series(g.L);
   const size_t pc = (size_t)(tf > se ? tf : se) * elem;
-  return (lds > pc ? lds : pc) + (size_t)bpc_lds_tables(H1, H2) * elem;
+  return (lds > pc ? lds : pc) + (size_t)bpc_lds_tables(H1, H2) * elem + 3 * g.d * sizeof(TI);
 }
 
 // Launch: grid nrhs, kSmallNT threads, small_lds bytes.
@@ -55,7 +56,10 @@ k_small_solve(Geom g, SmallArgs<TI> a, PcgStatsDev* __restrict__ stats) {
   __shared__ double red_sh[NT / 64];
   __shared__ RhsState s_sh;
   T2* tab = reinterpret_cast<T2*>(smem_raw);
-  unsigned char* lds = smem_raw + (a.pre ? bpc_lds_tables(a.pc.H1, a.pc.H2) * sizeof(T2) : 0);
+  T2* Z = tab + (a.pre ? bpc_lds_tables(a.pc.H1, a.pc.H2) : 0);  // [H][N]: d values
+  TI* r = reinterpret_cast<TI*>(Z) + (a.pre ? g.d : 0);
+  TI* z = a.pre ? r + g.d : r;
+  unsigned char* lds = reinterpret_cast<unsigned char*>(z + g.d);
   const int rh = blockIdx.x;
   const int f = field_of(g, rh);
   const long base = (long)rh * g.d, fo = field_off(g, rh);
@@ -64,8 +68,14 @@ k_small_solve(Geom g, SmallArgs<TI> a, PcgStatsDev* __restrict__ stats) {
   a.pc.np += (long)f * g.Ltau;
   a.pc.coef += (long)f * a.pc.H * kNPMax;
   a.pc.dbar += (long)f * g.N;
-  T2* Z = a.Z + (long)rh * a.pc.H * g.N;
-  TI* r = a.s.r + base;
+  a.s.pa += base;
+  a.s.pb += base;
+  a.s.Ap += base;
+  a.s.b += base;
+  a.s.u += base;
+  a.s.u64b += base;
+  a.s.u32 += base;
+  a.uit += base;
   int S, sub, lane, nslot;
   block_layout<NT>(g, tid, S, sub, lane, nslot);
   const int Tch = (g.Ltau + S - 1) / S;
@@ -86,30 +96,30 @@ k_small_solve(Geom g, SmallArgs<TI> a, PcgStatsDev* __restrict__ stats) {
   if (tid == 0) solve_init_state(s_sh, a.init);
   if (a.zero)
     for (long k = 4L * tid; k < g.d; k += 4L * NT)
-      Vec4<double>::st(a.s.u + base + k, Vec4<double>::V{0.0, 0.0, 0.0, 0.0});
+      Vec4<double>::st(a.s.u + k, Vec4<double>::V{0.0, 0.0, 0.0, 0.0});
   __syncthreads();
   for (long slot = 0; slot < a.total && !s_sh.final_; ++slot) {
     double acc = 0.0, acc2 = 0.0;
     if (s_sh.replace) {
-      EpiResidual<TI> epi{a.s.b, a.s.r};
+      EpiResidual<TI> epi{a.s.b, r};
       double* lds4 = reinterpret_cast<double*>(lds) + lo;
       if constexpr (sizeof(TI) == 4) {
         InResid in{a.s.u, a.s.u64b, a.s.u32, nullptr, nullptr, 0};
         in.begin(s_sh);
         mtm_sweep<double, NT, 1, 1>(opaque(g), a.s.E64 + fo, a.s.th64, Tch, tau0, Tc, active, lane, nslot, lds4,
-                                    base, in, epi, acc, acc2, no_hook);
+                                    0, in, epi, acc, acc2, no_hook);
       } else {
         InPlain<double> in{a.s.u};
         mtm_sweep<double, NT, 1, 1>(opaque(g), a.s.E64 + fo, a.s.th64, Tch, tau0, Tc, active, lane, nslot, lds4,
-                                    base, in, epi, acc, acc2, no_hook);
+                                    0, in, epi, acc, acc2, no_hook);
       }
       fold(P_RES, acc, acc2);
     } else {
-      InPUpdate<TI, false> in{a.s.z, a.s.pa, a.s.pb, nullptr, nullptr, (TI)0, 0};
+      InPUpdate<TI, false> in{z, a.s.pa, a.s.pb, nullptr, nullptr, (TI)0, 0};
       EpiDot<TI> epi{a.s.Ap};
       in.begin(s_sh);
       mtm_sweep<TI, NT, 1, 1>(opaque(g), a.s.E + fo, a.s.th, Tch, tau0, Tc, active, lane, nslot,
-                              reinterpret_cast<TI*>(lds) + lo, base, in, epi, acc, acc2, no_hook);
+                              reinterpret_cast<TI*>(lds) + lo, 0, in, epi, acc, acc2, no_hook);
       acc = block_sum<NT>(acc, red_sh);
       if (tid == 0) {
         InPUpdate<TI, false>::on_state(s_sh);
@@ -119,9 +129,9 @@ k_small_solve(Geom g, SmallArgs<TI> a, PcgStatsDev* __restrict__ stats) {
       if (s_sh.done) continue;  // breakdown
       const TI alpha = (TI)s_sh.alpha;
       const bool uz = s_sh.u32z != 0;
-      const TI* p = ((s_sh.iter & 1) ? a.s.pa : a.s.pb) + base;
-      const TI* Ap = a.s.Ap + base;
-      TI* u = a.uit + base;
+      const TI* p = (s_sh.iter & 1) ? a.s.pa : a.s.pb;
+      const TI* Ap = a.s.Ap;
+      TI* u = a.uit;
       double rr = 0.0;
       for (long k = 4L * tid; k < g.d; k += 4L * NT) {
         auto uu = Vec4<TI>::ld(u + k), rv = Vec4<TI>::ld(r + k);
@@ -146,7 +156,7 @@ k_small_solve(Geom g, SmallArgs<TI> a, PcgStatsDev* __restrict__ stats) {
     bpc_forward<TI, NT, kBpcLdsAlone>(opaque(g), a.pc, r, Z, tab, l);
     bpc_series<TI, NT, kBpcLdsAlone>(opaque(g), a.pc, a.s.th, Z, l);
     fold(P_RZ,
-         bpc_inverse<TI, NT, kBpcLdsAlone>(opaque(g), a.pc, Z, r, const_cast<TI*>(a.s.z) + base, tab, l), 0.0);
+         bpc_inverse<TI, NT, kBpcLdsAlone>(opaque(g), a.pc, Z, r, z, tab, l), 0.0);
   }
 
   // The solution and S_F = b . u (as k_solve_final), then the statistics.
@@ -154,14 +164,14 @@ k_small_solve(Geom g, SmallArgs<TI> a, PcgStatsDev* __restrict__ stats) {
   const bool from_ws = s_sh.refined && s_sh.upar == 1, add32 = s_sh.refined && !s_sh.u32z;
   double act = 0.0;
   for (long k = 4L * tid; k < g.d; k += 4L * NT) {
-    auto uu = Vec4<double>::ld((from_ws ? a.s.u64b : a.s.u) + base + k);
+    auto uu = Vec4<double>::ld((from_ws ? a.s.u64b : a.s.u) + k);
     if (add32) {
-      const float4 c = Vec4<float>::ld(a.s.u32 + base + k);
+      const float4 c = Vec4<float>::ld(a.s.u32 + k);
       uu.x += (double)c.x; uu.y += (double)c.y; uu.z += (double)c.z; uu.w += (double)c.w;
     }
     if (zero) uu = Vec4<double>::V{0.0, 0.0, 0.0, 0.0};
-    if (zero || from_ws || add32) Vec4<double>::st(a.s.u + base + k, uu);
-    const auto bv = Vec4<double>::ld(a.s.b + base + k);
+    if (zero || from_ws || add32) Vec4<double>::st(a.s.u + k, uu);
+    const auto bv = Vec4<double>::ld(a.s.b + k);
     act += bv.x * uu.x + bv.y * uu.y + bv.z * uu.z + bv.w * uu.w;
   }
   act = block_sum<NT>(act, red_sh);

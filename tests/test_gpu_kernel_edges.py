@@ -192,3 +192,22 @@ def test_precond_matrix_blocks(L, Ltau):
     check(2, [ref[0][0], ref[1][1]])
     s.set_field(xg[1])
     check(2, ref[1])
+
+
+# One shared field, so that the one-launch solve takes its longest blocks as matrices.
+@pytest.mark.parametrize("L,Ltau", [(4, 100), (4, 128), (6, 56)])
+@pytest.mark.parametrize("prec", ["f64", "f32_refined"])
+def test_small_solve_matrix_blocks(L, Ltau, prec):
+    lat = OL.Lattice(L, Ltau, 0.1, 1.0, 0.1, 1.0)
+    rng = np.random.default_rng(41 * L + Ltau)
+    x = rng.standard_normal((Ltau, lat.N))
+    b = rng.standard_normal((3, Ltau, lat.N))
+    s = _solver(lat, 3)
+    s.set_field(torch.from_numpy(x).cuda())
+    u, stats = s.solve(torch.from_numpy(b).cuda(), tol=1e-11, prec=prec, precond=True)
+    C = OL.sparse_C(lat).tocsr()
+    res = b - OL.apply_MT(lat, x, OL.apply_M(lat, x, u.cpu().numpy(), C), C)
+    plain = s.solve(torch.from_numpy(b).cuda(), tol=1e-11, prec=prec)[1]
+    for r in range(3):
+        assert stats[r]["status"] == 1 and np.linalg.norm(res[r]) <= 1.1e-11 * np.linalg.norm(b[r])
+        assert stats[r]["iters"] <= plain[r]["iters"]  # a wrong matrix would not precondition
