@@ -72,7 +72,8 @@ struct FftPlan {
 unsigned magic(unsigned d) { return d <= 1 ? 0u : (unsigned)(((1ull << 32) + d - 1) / d); }
 __device__ __forceinline__ int udiv(int e, unsigned m) { return m ? (int)__umulhi((unsigned)e, m) : e; }
 
-FftPlan make_plan(int n) {
+// small_first: a 4 before the 8s (a first stage from memory has more, smaller butterflies).
+FftPlan make_plan(int n, bool small_first) {
   FftPlan p;
   std::memset(&p, 0, sizeof(p));
   p.n = n;
@@ -83,6 +84,10 @@ FftPlan make_plan(int n) {
     ++twos;
   }
   auto add = [&](int r) { p.R[p.ns++] = r; };
+  if (small_first && twos >= 5 && twos % 3 != 0) {
+    add(4);
+    twos -= 2;
+  }
   while (twos >= 5 || twos == 3) {  // 16 is 4 * 4, not 8 * 2
     add(8);
     twos -= 3;
@@ -271,7 +276,7 @@ struct XyArgs {
 // of 400 x 32 x 32, 14-15 us each with direct DFTs and one grid per launch.
 template <bool INV, int NT>
 __global__ void __launch_bounds__(NT)
-k_fft_xy(int L, int N, FftPlan pl, XyArgs A, const double2* __restrict__ twL) {
+k_fft_xy(int L, int N, FftPlan py, FftPlan px, XyArgs A, const double2* __restrict__ twL) {
   extern __shared__ double2 sh[];
   const int LP = L + 1;
   double2* tw = sh;
@@ -282,17 +287,17 @@ k_fft_xy(int L, int N, FftPlan pl, XyArgs A, const double2* __restrict__ twL) {
   const XyJob jb = A.job[logical - slice * A.njob];
   const long base = (long)slice * N;
   for (int e = threadIdx.x; e < L; e += NT) tw[e] = INV ? conjd(twL[e]) : twL[e];
-  const int ns = pl.ns;
   int cur = 0;
   for (int pass = 0; pass < 2; ++pass) {  // 0: along y, 1: along x
+    const int ns = pass ? px.ns : py.ns;
     const int sn = pass ? 1 : LP, sb = pass ? LP : 1;
     int Ns = 1;
     for (int i = 0; i < ns; ++i) {
-      const int R = pl.R[i];
+      const int R = pass ? px.R[i] : py.R[i];
       const bool first = pass == 0 && i == 0, last = pass == 1 && i == ns - 1;
       const double2* src = buf + cur * nbuf;
       double2* dst = buf + (cur ^ 1) * nbuf;
-      const unsigned mn = pl.mn, mnb = pl.mNb[i];
+      const unsigned mn = px.mn, mnb = px.mNb[i];  // (mnb for the last stage, along x)
       const int nb = L / R;
       auto split = [&](int e, int& s, int& j) {
         if (last) {
@@ -322,7 +327,7 @@ k_fft_xy(int L, int N, FftPlan pl, XyArgs A, const double2* __restrict__ twL) {
         else jb.out[o] = v;
       };
       if (!first || Ns > 1) __syncthreads();
-      fft_stage_sel<INV, NT>(R, L, Ns, pl.mNs[i], nb * L, tw, split, ld, st);
+      fft_stage_sel<INV, NT>(R, L, Ns, pass ? px.mNs[i] : py.mNs[i], nb * L, tw, split, ld, st);
       Ns *= R;
       cur ^= 1;
     }
@@ -450,7 +455,7 @@ struct fph_meas_s {
   int max_rhs;
   int L, N, T, ls;
   long d;
-  FftPlan pL, pT;
+  FftPlan pY, pX, pT;
   double2 *twL, *tw2;  // exp(-2 pi i m / L), exp(-i pi m / Ltau)
   double2* grid[kGrids];  // complex grids [Ltau][N]
   double2 *acc, *acc2, *run;
@@ -465,10 +470,10 @@ hipError_t launch_xy(const fph_meas_s* m, bool inv, const XyArgs& A, hipStream_t
   const dim3 g(m->T * A.njob);
   if (m->N <= 1024) {
     auto k = inv ? k_fft_xy<true, 256> : k_fft_xy<false, 256>;
-    hipLaunchKernelGGL(k, g, dim3(256), m->lds_xy, s, m->L, m->N, m->pL, A, (const double2*)m->twL);
+    hipLaunchKernelGGL(k, g, dim3(256), m->lds_xy, s, m->L, m->N, m->pY, m->pX, A, (const double2*)m->twL);
   } else {
     auto k = inv ? k_fft_xy<true, 512> : k_fft_xy<false, 512>;
-    hipLaunchKernelGGL(k, g, dim3(512), m->lds_xy, s, m->L, m->N, m->pL, A, (const double2*)m->twL);
+    hipLaunchKernelGGL(k, g, dim3(512), m->lds_xy, s, m->L, m->N, m->pY, m->pX, A, (const double2*)m->twL);
   }
   return hipGetLastError();
 }
@@ -559,8 +564,9 @@ int fph_meas_create(fph_meas_t* out, fph_handle_t h, void* stream) {
   m->T = lat.Ltau;
   m->ls = ls;
   m->d = (long)N * lat.Ltau;
-  m->pL = make_plan(lat.L);
-  m->pT = make_plan(lat.Ltau);
+  m->pY = make_plan(lat.L, true);
+  m->pX = make_plan(lat.L, false);
+  m->pT = make_plan(lat.Ltau, true);
   m->lds_xy = lds_xy;
   m->lds_t = lds_t;
   hipError_t e = hipSuccess;
