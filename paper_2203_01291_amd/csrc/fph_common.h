@@ -212,7 +212,8 @@ struct PcInfo {
   double bmin, bmax;
   double s, c;          // A = s * Bbar - c
   int maxnp;
-  int kd64, kd32;       // blocks of F F^T applied as matrices, by precision (DenseBlocks)
+  int kd64, kd32;       // blocks of F F^T applied as matrices, by precision (k_pc_dense)
+  int want64, want32;   // the counts once the field's matrices are built
   int pad;
 };
 

@@ -358,6 +358,12 @@ int fph::precond_parts(fph_handle_t h, int32_t prec, int32_t nrhs) {
   return (h->g.N + (1 << lks) - 1) >> lks;
 }
 
+int fph::precond_matrices(fph_handle_t h, void* stream) {
+  if (!h->have_field) return FPH_E_NOFIELD;
+  const hipError_t e = pc_dense(&h->pc, h->g, h->dbar64, (hipStream_t)stream);
+  return e == hipSuccess ? FPH_OK : fail_hip(e);
+}
+
 int fph::precond_apply_dot(fph_handle_t h, int32_t prec, int32_t nrhs, const void* in_dev, void* out_dev,
                            double* part_dev, void* stream) {
   if (part_dev == nullptr) return FPH_E_NULL;
@@ -916,6 +922,7 @@ extern "C" int pcg_solve(fph_handle_t h, int32_t nrhs, const double* b_dev, doub
     return FPH_OK;
   }
   SolveRun run(h, nrhs, b_dev, u_dev, opts);
+  if (run.pre) FPH_CHECK(pc_dense(&h->pc, h->g, h->dbar64, s));
   if (small_route(run)) {
     FPH_CHECK(small_solve(run, st, s));
     return FPH_OK;
@@ -932,6 +939,7 @@ extern "C" int pcg_solve_sync(fph_handle_t h, int32_t nrhs, const double* b_dev,
   const int rc = check_solve(h, nrhs, b_dev, u_dev, opts);
   if (rc != FPH_OK) return rc;
   hipStream_t s = (hipStream_t)stream;
+  if (opts->use_precond) FPH_CHECK(pc_dense(&h->pc, h->g, h->dbar64, s));
   if (opts->variant == 2) {
     FPH_CHECK(coop_enqueue(h, b_dev, u_dev, opts, h->stats_dev, s));
   } else if (SolveRun run(h, nrhs, b_dev, u_dev, opts); small_route(run)) {

@@ -51,6 +51,7 @@ struct PcTables {
   int kdmax;       // frequencies with room for a matrix (0: none)
   double2* dense64;  // [kdmax][N][N]: the blocks of F F^T (one shared field only)
   float2* dense32;
+  bool dense_built;  // enqueued for the field set last (pc_dense)
   void* Z;         // complex workspace, max_rhs * H * N (double2)
   void* Z2;
   double th, c4;   // tanh(dtau t) and cosh(dtau t)^4: P_A P_B = c4 P'_A P'_B, C2' = [[1, th], [th, 1]]
@@ -176,8 +177,9 @@ k_pc_bounds(int N, int Ltau, const double* __restrict__ dbar, double dtau, doubl
     info->c = db > 0.0 ? 1.0 + 2.0 * bmin / db : 0.0;
     info->maxnp = snp[0];
     // (np[o], o < H, is the order of the o-th longest series, w' = o)
-    info->kd64 = kdmax ? dense_count(np, N, kdmax, sizeof(double2)) : 0;
-    info->kd32 = kdmax ? dense_count(np, N, kdmax, sizeof(float2)) : 0;
+    info->want64 = kdmax ? dense_count(np, N, kdmax, sizeof(double2)) : 0;
+    info->want32 = kdmax ? dense_count(np, N, kdmax, sizeof(float2)) : 0;
+    info->kd64 = info->kd32 = 0;  // no matrix of this field yet
   }
 }
 
@@ -1528,8 +1530,10 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
 // conjugated (G is Hermitian), so that the store is contiguous.  The FP32 matrix
 // is the FP64 one rounded, so FP32 applies are closer to the exact series than
 // the FP32 recurrence was (relative error 1.1e-6 -> 1.8e-7 at L = 32, Ltau 160,
-// N_P 45; FP64 unchanged, 1.7e-14).  Built with every shared field: 34 us for 16
-// blocks at L = 16, 25-115 us at L = 32, gained back within five applies.
+// N_P 45; FP64 unchanged, 1.7e-14).  Built by the first solve on a shared field:
+// 34 us for 16 blocks at L = 16, 25-115 us at L = 32, gained back within five
+// applies.  A single apply does not build them (ten FP32 vectors at L = 32, Ltau
+// 400 with a new field: 95 us, 186 us if it did) and uses them if they are there.
 template <int NT, bool ROW16, int LAY>
 __global__ void __launch_bounds__(NT)
 k_pc_dense(Geom g, int H, const PcInfo* __restrict__ info, const int* __restrict__ np,
@@ -1538,8 +1542,8 @@ k_pc_dense(Geom g, int H, const PcInfo* __restrict__ info, const int* __restrict
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ double xs[LAY == kWavePerPart ? 2 * 4 * 64 : 1];
   const int o = blockIdx.y, j = blockIdx.x;
-  const int kd64 = info->kd64, kd32 = info->kd32;
-  if (o >= max(kd64, kd32)) return;
+  const int kd64 = info->want64, kd32 = info->want32;
+  if (o >= max(kd64, kd32) || info->kd64 + info->kd32 > 0) return;  // not wanted, or built
   const int nbuf = kpm_split_buf<double>(g);
   const int lane = threadIdx.x & 63;
   const bool im = LAY == kWavePerPart ? threadIdx.x >= 64 : lane >= 32;
@@ -1576,6 +1580,12 @@ k_pc_dense(Geom g, int H, const PcInfo* __restrict__ info, const int* __restrict
     if (o < kd64) st2c(G64 + at0, v0, v1);
     if (o < kd32) st2c(G32 + at0, make_float2((float)v0.x, (float)v0.y), make_float2((float)v1.x, (float)v1.y));
   }
+}
+
+// The matrices are built: from here on they are used.
+__global__ void k_pc_dense_done(PcInfo* info) {
+  info->kd64 = info->want64;
+  info->kd32 = info->want32;
 }
 
 // Per-block Chebyshev apply.  op 0: F (series in A), 1: F^T (conjugate
@@ -1748,8 +1758,8 @@ inline hipError_t pc_create(PcTables* pc, const Geom& g, int max_rhs) {
                   ? (int)std::min<size_t>({16, (size_t)H - 1, (100u << 20) / (nn * 24)})
                   : 0;
   if (pc->kdmax > 0) {
-    PCALLOC(pc->dense64, pc->kdmax * nn * sizeof(double2));
-    PCALLOC(pc->dense32, pc->kdmax * nn * sizeof(float2));
+    PCALLOC(pc->dense64, pc->kdmax * nn * (sizeof(double2) + sizeof(float2)));
+    pc->dense32 = reinterpret_cast<float2*>(pc->dense64 + pc->kdmax * nn);
   }
   PCALLOC(pc->Z, (size_t)max_rhs * H * g.N * sizeof(double2));
   PCALLOC(pc->Z2, (size_t)max_rhs * H * g.N * sizeof(double2));
@@ -1762,7 +1772,7 @@ inline hipError_t pc_create(PcTables* pc, const Geom& g, int max_rhs) {
 
 inline void pc_destroy(PcTables* pc) {
   void* ptrs[] = {pc->tw64, pc->W64, pc->F64, pc->tw32, pc->W32, pc->F32, pc->info, pc->np,
-                  pc->coef64, pc->coef32, pc->dense64, pc->dense32, pc->Z, pc->Z2};
+                  pc->coef64, pc->coef32, pc->dense64, pc->Z, pc->Z2};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   std::memset(pc, 0, sizeof(*pc));
@@ -1781,7 +1791,8 @@ hipError_t pc_launch_dense(const PcTables* pc, const Geom& g, const double* dbar
 }
 
 // Series tables of field f from its dbar (dbar64 points at that field's N
-// values), and of a field shared by every right-hand side the block matrices.
+// values); `shared`: the field serves every right-hand side, and its longest
+// blocks may become matrices (pc_dense).
 inline hipError_t pc_set_field(PcTables* pc, const Geom& g, const double* dbar64, double dtau,
                                double t, double a1, double a2, hipStream_t s, int f, bool shared) {
   PcInfo* info = pc->info + f;
@@ -1793,13 +1804,35 @@ inline hipError_t pc_set_field(PcTables* pc, const Geom& g, const double* dbar64
   hipLaunchKernelGGL(k_pc_coef, dim3(pc->H), dim3(256), 0, s, g.Ltau, (const PcInfo*)info,
                      (const int*)np, pc->coef64 + (long)f * pc->H * kNPMax,
                      pc->coef32 + (long)f * pc->H * kNPMax);
-  e = hipGetLastError();
-  if (e != hipSuccess || !shared || pc->kdmax == 0) return e;
-  if (g.hL == 16 && g.Q == 256) return pc_launch_dense<512, true>(pc, g, dbar64, s);
-  if (g.Q <= 32) return pc_launch_dense<64, false, kOneWave>(pc, g, dbar64, s);
-  if (g.Q <= 64) return pc_launch_dense<128, false, kWavePerPart>(pc, g, dbar64, s);
-  if (g.Q <= 128) return pc_launch_dense<256>(pc, g, dbar64, s);
-  return pc_launch_dense<512>(pc, g, dbar64, s);
+  pc->dense_built = false;
+  return hipGetLastError();
+}
+
+// Builds the block matrices of a shared field before its first solve.  What the
+// kernels use is the device's count (kd64, kd32: zero from k_pc_bounds until
+// k_pc_dense_done), so a field set or replayed in any order is never paired
+// with another field's matrices; the host only skips the launches it has
+// enqueued already, and always records them in a captured sequence, where they
+// return at once when the matrices are there.
+inline hipError_t pc_dense(PcTables* pc, const Geom& g, const double* dbar64, hipStream_t s) {
+  if (pc->kdmax == 0 || g.fs != 0) return hipSuccess;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    cap = hipStreamCaptureStatusNone;
+  }
+  const bool eager = cap == hipStreamCaptureStatusNone;
+  if (eager && pc->dense_built) return hipSuccess;
+  hipError_t e;
+  if (g.hL == 16 && g.Q == 256) e = pc_launch_dense<512, true>(pc, g, dbar64, s);
+  else if (g.Q <= 32) e = pc_launch_dense<64, false, kOneWave>(pc, g, dbar64, s);
+  else if (g.Q <= 64) e = pc_launch_dense<128, false, kWavePerPart>(pc, g, dbar64, s);
+  else if (g.Q <= 128) e = pc_launch_dense<256>(pc, g, dbar64, s);
+  else e = pc_launch_dense<512>(pc, g, dbar64, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_pc_dense_done, dim3(1), dim3(1), 0, s, pc->info);
+  if ((e = hipGetLastError()) == hipSuccess && eager) pc->dense_built = true;
+  return e;
 }
 
 // LDS bytes of a transform workgroup with tile width 2^lks.

@@ -1217,10 +1217,12 @@ int ssh_solve(fph_ssh_t c, int32_t nrhs, const double* b_dev, double* u_dev, con
   if (pre && nrhs > c->pc_max_rhs) return FPH_E_NRHS;
   if (!(opts->tol > 0.0) || !std::isfinite(opts->tol) || opts->maxiter < 1 || opts->chunk < 0)
     return FPH_E_ARG;
-  if (opts->prec == FPH_F32_REFINED) {
-    if (opts->max_outer < 0 || !(opts->ru_delta >= 0.0)) return FPH_E_ARG;
-    return solve_refined(c, nrhs, b_dev, u_dev, opts, stats_host, stream);
+  if (opts->prec == FPH_F32_REFINED && (opts->max_outer < 0 || !(opts->ru_delta >= 0.0))) return FPH_E_ARG;
+  if (pre) {
+    const int rc = fph::precond_matrices(c->pc, stream);
+    if (rc != FPH_OK) return rc;
   }
+  if (opts->prec == FPH_F32_REFINED) return solve_refined(c, nrhs, b_dev, u_dev, opts, stats_host, stream);
   hipStream_t s = (hipStream_t)stream;
   const long d = c->G.d;
   const long n = (long)nrhs * d;

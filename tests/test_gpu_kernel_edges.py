@@ -179,6 +179,7 @@ def test_precond_matrix_blocks(L, Ltau):
     xg, vg = torch.from_numpy(xs).cuda(), torch.from_numpy(v).cuda()
 
     def check(n, want):
+        s.solve(vg[:n].contiguous(), tol=1e-2, precond=True)  # a solve builds the matrices
         for r in range(n):
             assert _relmax(s.precond(vg[:n].contiguous(), "FFT").cpu().numpy()[r], want[r]) < 1e-12
             got = s.precond(vg[:n].float().contiguous(), "FFT").cpu().numpy()[r]
@@ -211,3 +212,49 @@ def test_small_solve_matrix_blocks(L, Ltau, prec):
     for r in range(3):
         assert stats[r]["status"] == 1 and np.linalg.norm(res[r]) <= 1.1e-11 * np.linalg.norm(b[r])
         assert stats[r]["iters"] <= plain[r]["iters"]  # a wrong matrix would not precondition
+
+
+# Block matrices and captured graphs: a solve captured without the field, replayed after eager changes
+# of the field; a field set by a replay and solved for eagerly.  The apply of F F^T after each solve uses
+# the matrices that are there, against the series of a handle that has none.
+def test_precond_matrices_under_capture():
+    lat = OL.Lattice(16, 80, 0.1, 1.0, 0.0, 1.0)
+    rng = np.random.default_rng(3)
+    xs = [torch.from_numpy(c * rng.standard_normal((lat.Ltau, lat.N))).cuda() for c in (1.0, 0.4, 1.3)]
+    v = torch.from_numpy(rng.standard_normal((1, lat.Ltau, lat.N))).cuda()
+    want = []
+    for x in xs:
+        s = _solver(lat, 1)
+        s.set_field(x)
+        want.append(s.precond(v, "FFT").clone())
+    s = _solver(lat, 1)
+    x, out = xs[0].clone(), torch.empty_like(v)
+    s.set_field(x)
+    u = torch.zeros_like(v)
+    st = torch.empty(4, dtype=torch.float64, device="cuda")
+    s.solve_async(v, u, stats=st, tol=1e-2, maxiter=40, precond=True)
+    torch.cuda.synchronize()
+    apply_only, field_only = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(apply_only):
+        s.solve_async(v, u, stats=st, tol=1e-2, maxiter=40, precond=True)
+        s.precond(v, "FFT", out=out)
+    with torch.cuda.graph(field_only):
+        s.set_field(x)
+
+    def close(a, b):  # series or matrix: the same operator to rounding
+        assert float((a - b).norm() / b.norm()) < 1e-12
+
+    for k in (1, 2, 0, 0, 2):
+        s.set_field(xs[k])
+        out.zero_()
+        apply_only.replay()
+        close(out, want[k])
+        s.solve(v, tol=1e-2, precond=True)
+        close(s.precond(v, "FFT"), want[k])
+    for k in (1, 0, 2):
+        x.copy_(xs[k])
+        field_only.replay()
+        s.solve(v, tol=1e-2, precond=True)
+        close(s.precond(v, "FFT"), want[k])
+        apply_only.replay()
+        close(out, want[k])
