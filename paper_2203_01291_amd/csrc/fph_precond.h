@@ -294,13 +294,11 @@ FPH_DEVINL void dft_pair(const T2* fr, const T2* y, int s, int n, T2& a, T2& b) 
 // Forward transform of one tile of sites: Z[r][k][i] = (U in)_{2k}.
 // Stage 0, item (tau < H, site), coalesced: y_tau = e^{-i pi tau/Ltau}
 // (in_tau - i in_{tau+H}) into LDS.  With CGUPD both inputs first receive
-// the CG update u += alpha p, r -= alpha Ap (r is `in`, updated in place),
-// publishing |r|^2 as P_RR partials; the direction is pb on even iteration
-// counts, pa on odd.  A right-hand side whose FP64 residual was just
-// evaluated (the folded partials were P_RES) is transformed without the
-// update; an FP32 correction u the state marks as zero is read as zero.
-// The state loads are issued first, then the loads of the first pass (two
-// items per thread) other than the direction, which needs the state.
+// the CG update r -= alpha Ap (r is `in`, updated in place), publishing |r|^2
+// as P_RR partials (u += alpha p is the next kernel's, update_u).  A
+// right-hand side whose FP64 residual was just evaluated (the folded partials
+// were P_RES) is transformed without the update.
+// The state loads are issued first, then the loads of the first pass.
 // Step 1, item (site, n2, k1): output k1 of the H1-point DFT over
 // n1 of y_{H2 n1 + n2}, times W_H^{n2 k1}.  Step 2, item (site, k1, k2):
 // the H2-point DFT over n2 -> Z_{k1 + H1 k2}.
@@ -311,8 +309,8 @@ template <typename T, int H1, int NT, bool CGUPD, int KI>
 __global__ void __launch_bounds__(NT)
 k_tfwd(Geom g, int H2, const typename Cplx<T>::type* __restrict__ tw,
        const typename Cplx<T>::type* __restrict__ W, const typename Cplx<T>::type* __restrict__ F,
-       T* __restrict__ in, typename Cplx<T>::type* __restrict__ Z, T* __restrict__ u,
-       const T* pa, const T* pb, const T* __restrict__ Ap, int lks, int ntiles, StIO io) {
+       T* __restrict__ in, typename Cplx<T>::type* __restrict__ Z, const T* __restrict__ Ap, int lks,
+       int ntiles, StIO io) {
   using T2 = typename Cplx<T>::type;
   constexpr int kI = KI;  // stage-0 items per thread and pass
   const int KS = 1 << lks;
@@ -334,9 +332,9 @@ k_tfwd(Geom g, int H2, const typename Cplx<T>::type* __restrict__ tw,
   const int npair = H << lks;
 
   // Inputs of one pass of stage 0 (kI items per thread): r (and with
-  // CGUPD Ap, u, the direction p) at slices tau and tau + H, and the twist.
+  // CGUPD Ap) at slices tau and tau + H, and the twist.
   struct Pass {
-    T ra[kI], rb[kI], aa[kI], ab[kI], ua[kI], ub[kI], pa[kI], pb[kI];
+    T ra[kI], rb[kI], aa[kI], ab[kI];
     T2 tw[kI];
   };
   // Items past the last pair, or on a site past the end of a ragged tile,
@@ -344,7 +342,7 @@ k_tfwd(Geom g, int H2, const typename Cplx<T>::type* __restrict__ tw,
   // unconditional, so none waits for the others, and the values are never
   // used (stage 0 skips such items and stores nothing for a ragged site; a
   // ragged site's column of the transforms is not written out).
-  auto load = [&](Pass& P, int e0, bool all, bool dir, const T* p) {
+  auto load = [&](Pass& P, int e0) {
 #pragma unroll
     for (int j = 0; j < kI; ++j) {
       const int e = e0 + j * NT;
@@ -352,22 +350,12 @@ k_tfwd(Geom g, int H2, const typename Cplx<T>::type* __restrict__ tw,
       const int tau = ec >> lks;
       const int site = min(i0 + (ec & (KS - 1)), g.N - 1);
       const long oa = base + (long)tau * g.N + site;
-      if (all) {
-        P.ra[j] = in[oa];
-        P.rb[j] = in[oa + hN];
-        P.tw[j] = tw[tau];
-      }
+      P.ra[j] = in[oa];
+      P.rb[j] = in[oa + hN];
+      P.tw[j] = tw[tau];
       if (CGUPD) {
-        if (all) {
-          P.aa[j] = Ap[oa];
-          P.ab[j] = Ap[oa + hN];
-          P.ua[j] = u[oa];
-          P.ub[j] = u[oa + hN];
-        }
-        if (dir) {
-          P.pa[j] = p[oa];
-          P.pb[j] = p[oa + hN];
-        }
+        P.aa[j] = Ap[oa];
+        P.ab[j] = Ap[oa + hN];
       }
     }
   };
@@ -380,7 +368,7 @@ k_tfwd(Geom g, int H2, const typename Cplx<T>::type* __restrict__ tw,
   StLoad<16> sl;
   if (io.in != nullptr) state_issue(io, r, sl);
   Pass P0;
-  load(P0, threadIdx.x, true, false, pa);
+  load(P0, threadIdx.x);
   constexpr int kTab = kTabRegs ? 6 : 1;  // (H1^2 + H2^2 + H) <= 6 NT: H1 <= 20, H2 <= 32
   // Entry k of the LDS table is F[k] for k < nF, else W[k - nF]: one load
   // from a selected address (W's index clamped into range), no branch.
@@ -412,29 +400,7 @@ k_tfwd(Geom g, int H2, const typename Cplx<T>::type* __restrict__ tw,
   const T scale = (T)(1.0 / sqrt((double)g.Ltau));
   double acc_rr = 0.0;
   const bool upd = CGUPD && s_sh.folded == P_PAP;
-  const bool uz = CGUPD && s_sh.u32z != 0;
-
-  // Stage 0.  The direction p (the buffer the state names) is used only
-  // to update u; for the first pass that update is deferred to the end of
-  // the kernel, so the loads of p issued here arrive while the DFT runs.
-  T alpha = (T)0;
-  const T* p = pa;
-  if (CGUPD) {
-    alpha = (T)s_sh.alpha;
-    p = (s_sh.iter & 1) ? pa : pb;  // direction written by this iteration
-    if (upd) load(P0, threadIdx.x, false, true, p);
-  }
-  auto update_u = [&](const Pass& P, int e0) {
-#pragma unroll
-    for (int j = 0; j < kI; ++j) {
-      const int e = e0 + j * NT;
-      const int tau = e >> lks, sidx = e & (KS - 1);
-      if (e >= npair || i0 + sidx >= g.N) continue;
-      const long oa = base + (long)tau * g.N + i0 + sidx;
-      u[oa] = (uz ? (T)0 : P.ua[j]) + alpha * P.pa[j];
-      u[oa + hN] = (uz ? (T)0 : P.ub[j]) + alpha * P.pb[j];
-    }
-  };
+  const T alpha = CGUPD ? (T)s_sh.alpha : (T)0;
   auto stage0 = [&](const Pass& P, int e0) {
 #pragma unroll
     for (int j = 0; j < kI; ++j) {
@@ -457,9 +423,8 @@ k_tfwd(Geom g, int H2, const typename Cplx<T>::type* __restrict__ tw,
   stage0(P0, threadIdx.x);
   for (int e0 = threadIdx.x + kI * NT; e0 < npair; e0 += kI * NT) {
     Pass P;
-    load(P, e0, true, upd, p);
+    load(P, e0);
     stage0(P, e0);
-    if (upd) update_u(P, e0);
   }
   __syncthreads();
   // Steps 1 and 2 compute their outputs in pairs (k, k + n/2, dft_pair)
@@ -520,13 +485,9 @@ k_tfwd(Geom g, int H2, const typename Cplx<T>::type* __restrict__ tw,
     }
   }
 
-  if (upd) update_u(P0, threadIdx.x);
   if (io.in != nullptr) {
     double bs = 0.0;
-    if (upd) {
-      bs = block_sum<NT, true>(acc_rr, red_sh);
-      if (threadIdx.x == 0) s_sh.u32z = 0;
-    }
+    if (upd) bs = block_sum<NT, true>(acc_rr, red_sh);
     state_end(io, r, &s_sh, upd ? P_RR : P_NONE, bs, tile, ntiles, tile == 0);
   }
 }
@@ -769,6 +730,70 @@ k_tinv(Geom g, int H2, const typename Cplx<T>::type* __restrict__ tw,
 // paused, as one scalar load beside the block's other table loads.
 FPH_DEVINL bool state_done(const StIO& io, int r) {
   return *(const __attribute__((address_space(4))) int*)(uintptr_t)&io.in[r].done != 0;
+}
+
+// u += alpha p of a CG iteration, by workgroups of the series kernel past its
+// others (block b of nblk per right-hand side), which have nothing to wait for
+// and run on compute units that the series leave idle.  pend == P_RR says that
+// the forward transform, the kernel before, has updated r; the direction is pb
+// on even iteration counts, pa on odd; a correction u that the state marks as
+// zero is not read (the mark is taken off in kpm_end).  Bound by its three
+// vectors' cache traffic.  In the forward transform, whose tiles are a latency
+// chain already, it cost more than it does here (transform / series before and
+// after, us: L = 64, Ltau 400, FP32 15.3 / 12.0 -> 11.4 / 12.9; L = 32, Ltau 400
+// 7.8 / 6.8 -> 6.6 / 7.2; L = 32, Ltau 160, ten right-hand sides 13.4 / 15.3 ->
+// 12.0 / 16.5, where the series fill the compute units), so it is always here.
+template <typename T>
+struct UUpd {
+  T* u;
+  const T *pa, *pb;
+  int nblk;  // workgroups per right-hand side; 0: nothing to update
+};
+constexpr int kUVecs = 4;  // vectors per thread
+
+template <typename T>
+constexpr int u_vec() { return sizeof(T) == 4 ? 4 : 1; }  // values per load: FP32 workspaces are aligned, d % 4 == 0
+
+template <typename T>
+inline int u_blocks(const Geom& g, int nt) {
+  const long per = (long)nt * kUVecs * u_vec<T>();
+  return (int)((g.d + per - 1) / per);
+}
+
+template <typename T, int NT>
+FPH_DEVINL void update_u(const Geom& g, const UUpd<T>& U, int b, const StIO& io) {
+  constexpr int V = u_vec<T>();
+  struct alignas(V * sizeof(T)) Vec { T v[V]; };
+  const int r = b / U.nblk, c = b - r * U.nblk;
+  const auto* S = (const __attribute__((address_space(4))) RhsState*)(uintptr_t)(io.in + r);
+  if (S->pend != P_RR) return;
+  const T alpha = (T)S->alpha;
+  const bool uz = S->u32z != 0;
+  const Vec* p = reinterpret_cast<const Vec*>(((S->iter & 1) ? U.pa : U.pb) + (long)r * g.d);
+  Vec* u = reinterpret_cast<Vec*>(U.u + (long)r * g.d);
+  const long n = g.d / V, e0 = (long)c * NT * kUVecs + threadIdx.x;
+  Vec pv[kUVecs], uv[kUVecs];
+#pragma unroll
+  for (int j = 0; j < kUVecs; ++j) {  // (entries past the end read the last one)
+    const long e = min(e0 + (long)j * NT, n - 1);
+    pv[j] = p[e];
+    uv[j] = u[e];
+  }
+#pragma unroll
+  for (int j = 0; j < kUVecs; ++j) {
+    const long e = e0 + (long)j * NT;
+    if (e >= n) continue;
+#pragma unroll
+    for (int k = 0; k < V; ++k) uv[j].v[k] = (uz ? (T)0 : uv[j].v[k]) + alpha * pv[j].v[k];
+    u[e] = uv[j];
+  }
+}
+
+// The state a series block hands on: where it folded an iteration's |r|^2, the
+// launch has written u.
+FPH_DEVINL void kpm_end(const StIO& io, int r, RhsState* s) {
+  if (threadIdx.x == 0 && s->folded == P_RR) s->u32z = 0;
+  state_end(io, r, s, P_NONE, 0.0, 0, 1, true);
 }
 
 // Sites around the even plaquette with corner (x0, y0): rows y0-1, y0,
@@ -1434,7 +1459,7 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
             const int* __restrict__ np, const typename Cplx<T>::type* __restrict__ coef,
             const T* __restrict__ dbar, T th, T c4, const typename Cplx<T>::type* __restrict__ Z,
             typename Cplx<T>::type* __restrict__ Zo, const typename Cplx<T>::type* __restrict__ dense,
-            StIO io) {
+            int ndense, UUpd<T> U, StIO io) {
   using T2 = typename Cplx<T>::type;
   static_assert(NT <= kNPMax, "one coefficient per thread is loaded ahead");
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1449,6 +1474,10 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
   T2* cfs = reinterpret_cast<T2*>(reinterpret_cast<T*>(smem_raw) + 4 * nbuf);
   // Blocks of F F^T applied as matrices, by the workgroups past the series'.
   const int kd = dense ? (sizeof(T) == 8 ? info->kd64 : info->kd32) : 0;
+  if ((int)blockIdx.x >= H * nrhs + ndense) {
+    update_u<T, NT>(g, U, (int)blockIdx.x - H * nrhs - ndense, io);
+    return;
+  }
   if ((int)blockIdx.x >= H * nrhs) {
     dense_rows<T, NT>(g, H, nrhs, kd, (int)blockIdx.x - H * nrhs, dense, Z, Zo,
                       reinterpret_cast<T2*>(smem_raw), io);
@@ -1492,7 +1521,7 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
   if (stt && op != 2) {
     state_finish<NT>(io, r, sl, &s_sh);
     if (s_sh.done) {
-      state_end(io, r, &s_sh, P_NONE, 0.0, 0, 1, true);
+      kpm_end(io, r, &s_sh);
       return;
     }
   }
@@ -1506,7 +1535,7 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
   if (op == 2 && stt) {
     state_finish<NT>(io, r, sl, &s_sh);
     if (s_sh.done) {
-      state_end(io, r, &s_sh, P_NONE, 0.0, 0, 1, true);
+      kpm_end(io, r, &s_sh);
       return;
     }
   }
@@ -1521,7 +1550,7 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
     T2* Zout = Zo + ((long)r * H + k) * g.N + (im ? iL : i0);
     st2c(Zout, T2{sel(im, t0, x[0]), sel(im, x[2], t0)}, T2{sel(im, t1, x[1]), sel(im, x[3], t1)});
   }
-  if (stt) state_end(io, r, &s_sh, P_NONE, 0.0, 0, 1, true);
+  if (stt) kpm_end(io, r, &s_sh);
 }
 
 // The block matrices G = f(A) f(A)^H of F F^T that k_kpm_split applies instead
@@ -1599,9 +1628,13 @@ __global__ void __launch_bounds__(NT)
 k_kpm(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
       const int* __restrict__ np, const typename Cplx<T>::type* __restrict__ coef,
       const T* __restrict__ dbar, T th, T c4, const typename Cplx<T>::type* __restrict__ Z,
-      typename Cplx<T>::type* __restrict__ Zo, StIO io) {
+      typename Cplx<T>::type* __restrict__ Zo, UUpd<T> U, StIO io) {
   using T2 = typename Cplx<T>::type;
   static_assert(NT <= kNPMax, "one coefficient per thread is loaded ahead");
+  if ((int)blockIdx.x >= H * nrhs) {
+    update_u<T, NT>(g, U, (int)blockIdx.x - H * nrhs, io);
+    return;
+  }
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ RhsState s_sh;
   const int nbuf = 2 * kpm_row_stride(g.hL) * g.L + kWinPad;
@@ -1658,7 +1691,7 @@ k_kpm(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
     else
       state_begin<NT>(io, r, &s_sh, nullptr);
     if (s_sh.done) {
-      state_end(io, r, &s_sh, P_NONE, 0.0, 0, 1, true);
+      kpm_end(io, r, &s_sh);
       return;
     }
   }
@@ -1709,7 +1742,7 @@ k_kpm(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
       if (late) {
         state_finish<NT>(io, r, sl, &s_sh);
         if (s_sh.done) {
-          state_end(io, r, &s_sh, P_NONE, 0.0, 0, 1, true);
+          kpm_end(io, r, &s_sh);
           return;
         }
       }
@@ -1723,7 +1756,7 @@ k_kpm(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
     st2c(Zout + i0, acc[0], acc[1]);
     st2c(Zout + iL, acc[2], acc[3]);
   }
-  if (stt) state_end(io, r, &s_sh, P_NONE, 0.0, 0, 1, true);
+  if (stt) kpm_end(io, r, &s_sh);
 }
 
 // ----------------------------------------------------------------- host
@@ -1868,8 +1901,8 @@ int pc_tile_log2(const PcTables* pc, const Geom& g, int nrhs) {
 
 template <typename T, int H1, int NT>
 hipError_t pc_launch_fwd(const PcTables* pc, const Geom& g, int nrhs, int lks, T* in,
-                         typename Cplx<T>::type* Z, T* u, const T* pa, const T* pb, const T* Ap,
-                         StateSeq& sq, bool cgupd, hipStream_t s) {
+                         typename Cplx<T>::type* Z, const T* Ap, StateSeq& sq, bool cgupd,
+                         hipStream_t s) {
   const int KS = 1 << lks;
   const int ntiles = (g.N + KS - 1) / KS;
   if (pc->H1 * pc->H1 + pc->H2 * pc->H2 + pc->H > 6 * NT) return hipErrorInvalidValue;
@@ -1889,7 +1922,7 @@ hipError_t pc_launch_fwd(const PcTables* pc, const Geom& g, int nrhs, int lks, T
   }
   hipError_t e = allow_lds((const void*)kern, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, grid, dim3(NT), lds, s, g, pc->H2, tw, W, F, in, Z, u, pa, pb, Ap, lks,
+  hipLaunchKernelGGL(kern, grid, dim3(NT), lds, s, g, pc->H2, tw, W, F, in, Z, Ap, lks,
                      ntiles, io);
   return hipGetLastError();
 }
@@ -1922,12 +1955,11 @@ hipError_t pc_launch_inv(const PcTables* pc, const Geom& g, int nrhs, int lks,
 
 template <typename T>
 hipError_t pc_fwd(const PcTables* pc, const Geom& g, int nrhs, T* in, typename Cplx<T>::type* Z,
-                  T* u, const T* pa, const T* pb, const T* Ap, StateSeq& sq, bool cgupd,
-                  hipStream_t s) {
+                  const T* Ap, StateSeq& sq, bool cgupd, hipStream_t s) {
   const int lks = pc_tile_log2<T>(pc, g, nrhs);
   switch (pc->H1) {
 #define FPH_FWD_CASE(h1) \
-  case h1: return pc_launch_fwd<T, h1, kTNT>(pc, g, nrhs, lks, in, Z, u, pa, pb, Ap, sq, cgupd, s);
+  case h1: return pc_launch_fwd<T, h1, kTNT>(pc, g, nrhs, lks, in, Z, Ap, sq, cgupd, s);
     FPH_FWD_CASE(1) FPH_FWD_CASE(2) FPH_FWD_CASE(3) FPH_FWD_CASE(4) FPH_FWD_CASE(5)
     FPH_FWD_CASE(8) FPH_FWD_CASE(10) FPH_FWD_CASE(16) FPH_FWD_CASE(20)
 #undef FPH_FWD_CASE
@@ -1951,8 +1983,9 @@ hipError_t pc_inv(const PcTables* pc, const Geom& g, int nrhs, const typename Cp
 
 template <typename T, int NT, bool ROW16 = false>
 hipError_t pc_launch_kpm(const PcTables* pc, const Geom& g, const T* dbar, int op, int nrhs,
-                         const typename Cplx<T>::type* Z, typename Cplx<T>::type* Zo,
+                         const typename Cplx<T>::type* Z, typename Cplx<T>::type* Zo, UUpd<T> U,
                          StateSeq& sq, T th, T c4, hipStream_t s) {
+  U.nblk = U.u ? u_blocks<T>(g, NT) : 0;
   const StIO io = sq.next();
   const size_t nbuf = 2 * (size_t)kpm_row_stride(g.hL) * g.L + kWinPad;
   const size_t lds = (2 * nbuf + kNPMax) * sizeof(typename Cplx<T>::type);
@@ -1960,15 +1993,16 @@ hipError_t pc_launch_kpm(const PcTables* pc, const Geom& g, const T* dbar, int o
   hipError_t e = allow_lds((const void*)kern, lds);
   if (e != hipSuccess) return e;
   const auto* cf = (const typename Cplx<T>::type*)(sizeof(T) == 8 ? (const void*)pc->coef64 : (const void*)pc->coef32);
-  hipLaunchKernelGGL(kern, dim3(pc->H * nrhs), dim3(NT), lds, s, g, pc->H, nrhs, op, pc->info,
-                     pc->np, cf, dbar, th, c4, Z, Zo, io);
+  hipLaunchKernelGGL(kern, dim3((pc->H + U.nblk) * nrhs), dim3(NT), lds, s, g, pc->H, nrhs, op, pc->info,
+                     pc->np, cf, dbar, th, c4, Z, Zo, U, io);
   return hipGetLastError();
 }
 
 template <typename T, int NT, bool ROW16 = false, int LAY = kHalves>
 hipError_t pc_launch_kpm_split(const PcTables* pc, const Geom& g, const T* dbar, int op, int nrhs,
-                               const typename Cplx<T>::type* Z, typename Cplx<T>::type* Zo,
+                               const typename Cplx<T>::type* Z, typename Cplx<T>::type* Zo, UUpd<T> U,
                                StateSeq& sq, T th, T c4, hipStream_t s) {
+  U.nblk = U.u ? u_blocks<T>(g, NT) : 0;
   using T2 = typename Cplx<T>::type;
   const StIO io = sq.next();
   const size_t lds = 4 * (size_t)kpm_split_buf<T>(g) * sizeof(T) + kNPMax * sizeof(T2);
@@ -1982,15 +2016,16 @@ hipError_t pc_launch_kpm_split(const PcTables* pc, const Geom& g, const T* dbar,
   const T2* dense = dn ? (const T2*)(sizeof(T) == 8 ? (const void*)pc->dense64 : (const void*)pc->dense32)
                        : nullptr;
   const int rows = dense_rows_per(NT), RB = (g.N + rows - 1) / rows;
-  hipLaunchKernelGGL(kern, dim3(pc->H * nrhs + (dn ? pc->kdmax * RB : 0)), dim3(NT), lds, s, g, pc->H, nrhs,
-                     op, pc->info, pc->np, cf, dbar, th, c4, Z, Zo, dense, io);
+  const int nd = dn ? pc->kdmax * RB : 0;
+  hipLaunchKernelGGL(kern, dim3((pc->H + U.nblk) * nrhs + nd), dim3(NT), lds, s, g, pc->H, nrhs, op, pc->info,
+                     pc->np, cf, dbar, th, c4, Z, Zo, dense, nd, U, io);
   return hipGetLastError();
 }
 
 template <typename T>
 hipError_t pc_kpm(const PcTables* pc, const Geom& g, const T* dbar, int op, int nrhs,
-                  const typename Cplx<T>::type* Z, typename Cplx<T>::type* Zo, StateSeq& sq,
-                  T th, T c4, hipStream_t s) {
+                  const typename Cplx<T>::type* Z, typename Cplx<T>::type* Zo, const UUpd<T>& U,
+                  StateSeq& sq, T th, T c4, hipStream_t s) {
   // Split parts up to 256 plaquettes (8 waves); with 16 waves per block
   // (L = 40) the barrier costs more than the shorter steps give (26.2
   // against 24.2 us per FP32 F F^T at Ltau = 100, 30.7 against 28.7 in FP64).
@@ -2002,18 +2037,18 @@ hipError_t pc_kpm(const PcTables* pc, const Geom& g, const T* dbar, int op, int 
   // four, 49.1 / 46.5 for ten); FP64 gains or ties throughout.
   if (g.hL == 16 && g.Q == 256) {
     if (sizeof(T) == 8 || (long)pc->H * nrhs <= 512)
-      return pc_launch_kpm_split<T, 512, true>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
-    return pc_launch_kpm<T, 256, true>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
+      return pc_launch_kpm_split<T, 512, true>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
+    return pc_launch_kpm<T, 256, true>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
   }
   if (g.Q <= 32)
-    return pc_launch_kpm_split<T, 64, false, kOneWave>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
+    return pc_launch_kpm_split<T, 64, false, kOneWave>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
   if (g.Q <= 64)
-    return pc_launch_kpm_split<T, 128, false, kWavePerPart>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4,
+    return pc_launch_kpm_split<T, 128, false, kWavePerPart>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4,
                                                             s);
-  if (g.Q <= 128) return pc_launch_kpm_split<T, 256>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
-  if (g.Q <= 256) return pc_launch_kpm_split<T, 512>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
-  if (g.Q <= 512) return pc_launch_kpm<T, 512>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
-  return pc_launch_kpm<T, 1024>(pc, g, dbar, op, nrhs, Z, Zo, sq, th, c4, s);
+  if (g.Q <= 128) return pc_launch_kpm_split<T, 256>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
+  if (g.Q <= 256) return pc_launch_kpm_split<T, 512>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
+  if (g.Q <= 512) return pc_launch_kpm<T, 512>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
+  return pc_launch_kpm<T, 1024>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
 }
 
 // out = op(in) (op: 0 F, 1 F^T, 2 F F^T).  With rdot != nullptr the inverse
@@ -2024,10 +2059,9 @@ hipError_t pc_apply(const PcTables* pc, const Geom& g, const T* dbar, int op, in
   using T2 = typename Cplx<T>::type;
   T2* Z = reinterpret_cast<T2*>(pc->Z);
   T2* Z2 = reinterpret_cast<T2*>(pc->Z2);
-  hipError_t e = pc_fwd<T>(pc, g, nrhs, const_cast<T*>(in), Z, nullptr, nullptr, nullptr,
-                           nullptr, sq, false, s);
+  hipError_t e = pc_fwd<T>(pc, g, nrhs, const_cast<T*>(in), Z, nullptr, sq, false, s);
   if (e != hipSuccess) return e;
-  e = pc_kpm<T>(pc, g, dbar, op, nrhs, Z, Z2, sq, (T)pc->th, (T)pc->c4, s);
+  e = pc_kpm<T>(pc, g, dbar, op, nrhs, Z, Z2, UUpd<T>{}, sq, (T)pc->th, (T)pc->c4, s);
   if (e != hipSuccess) return e;
   return pc_inv<T>(pc, g, nrhs, Z2, out, rdot ? 1 : 0, rdot, sq, s);
 }
@@ -2042,9 +2076,9 @@ hipError_t pc_cg_update(const PcTables* pc, const Geom& g, const T* dbar, int nr
   using T2 = typename Cplx<T>::type;
   T2* Z = reinterpret_cast<T2*>(pc->Z);
   T2* Z2 = reinterpret_cast<T2*>(pc->Z2);
-  hipError_t e = pc_fwd<T>(pc, g, nrhs, r, Z, u, pa, pb, Ap, sq, true, s);
+  hipError_t e = pc_fwd<T>(pc, g, nrhs, r, Z, Ap, sq, true, s);
   if (e != hipSuccess) return e;
-  e = pc_kpm<T>(pc, g, dbar, 2, nrhs, Z, Z2, sq, (T)pc->th, (T)pc->c4, s);
+  e = pc_kpm<T>(pc, g, dbar, 2, nrhs, Z, Z2, UUpd<T>{u, pa, pb, 0}, sq, (T)pc->th, (T)pc->c4, s);
   if (e != hipSuccess) return e;
   return pc_inv<T>(pc, g, nrhs, Z2, z, 1, r, sq, s);
 }

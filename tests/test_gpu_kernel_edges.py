@@ -258,3 +258,22 @@ def test_precond_matrices_under_capture():
         close(s.precond(v, "FFT"), want[k])
         apply_only.replay()
         close(out, want[k])
+
+
+# The iterate's update by workgroups of the series kernel: sizes whose last workgroup is nearly empty
+# or whose only one is, for every form of the series kernel, several right-hand sides.
+@pytest.mark.parametrize("L,Ltau", [(6, 84), (12, 30), (16, 50), (18, 20), (24, 20), (32, 10), (34, 12), (48, 6)])
+@pytest.mark.parametrize("prec", ["f64", "f32_refined"])
+def test_precond_solve_update(L, Ltau, prec):
+    lat = OL.Lattice(L, Ltau, 0.1, 1.0, 0.1, 1.0)
+    rng = np.random.default_rng(17 * L + Ltau)
+    x = rng.standard_normal((Ltau, lat.N))
+    b = rng.standard_normal((3, Ltau, lat.N))
+    b[1] *= 1e-3
+    s = _solver(lat, 3)
+    s.set_field(torch.from_numpy(x).cuda())
+    u, stats = s.solve(torch.from_numpy(b).cuda(), tol=1e-11, prec=prec, precond=True)
+    C = OL.sparse_C(lat).tocsr()
+    res = b - OL.apply_MT(lat, x, OL.apply_M(lat, x, u.cpu().numpy(), C), C)
+    for r in range(3):
+        assert stats[r]["status"] == 1 and np.linalg.norm(res[r]) <= 1.1e-11 * np.linalg.norm(b[r])
