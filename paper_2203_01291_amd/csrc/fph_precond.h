@@ -2066,9 +2066,9 @@ hipError_t pc_apply(const PcTables* pc, const Geom& g, const T* dbar, int op, in
   return pc_inv<T>(pc, g, nrhs, Z2, out, rdot ? 1 : 0, rdot, sq, s);
 }
 
-// Preconditioned CG update: u += alpha p, r -= alpha Ap (|r|^2 as P_RR),
-// then z = F F^T r (the KPM kernel folds P_RR and skips finished
-// right-hand sides) and r.z as P_RZ.  Three launches.
+// Preconditioned CG update: r -= alpha Ap (|r|^2 as P_RR), then z = F F^T r
+// (the KPM kernel folds P_RR, skips finished right-hand sides and updates
+// u += alpha p) and r.z as P_RZ.  Three launches.
 template <typename T>
 hipError_t pc_cg_update(const PcTables* pc, const Geom& g, const T* dbar, int nrhs, T* u,
                         const T* pa, const T* pb, T* r, const T* Ap, T* z, StateSeq& sq,

@@ -15,8 +15,9 @@
 //     - nothing (finished, or paused);
 //   then, without the preconditioner, k_cg_update (u += alpha p,
 //   r -= alpha Ap, |r|^2; or, after a residual evaluation, only the decision
-//   that folds it); with it, the forward transform with the same update,
-//   the Chebyshev series F F^T and the inverse transform with r.z.
+//   that folds it); with it, the forward transform with the update of r,
+//   the Chebyshev series F F^T with that of u, and the inverse transform with
+//   r.z.
 //
 // A slot performs one CG iteration or one residual evaluation, so a solve
 // that may run `maxiter` iterations and `max_outer` evaluations after the
