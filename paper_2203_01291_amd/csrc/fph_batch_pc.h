@@ -303,7 +303,9 @@ FPH_DEVINL void bpc_series(const Geom& g, const PcView<T>& pc, T th,
     // row is a chain of loads eight columns at a time, at L = 8 longer than the
     // series: 28 000 against 16 000 cycles at Ltau 32): G is Hermitian, so the lanes
     // read along its rows and take the conjugate.
-    const int kd = pc.dense == nullptr || g.N > kBpcDenseN ? 0 : sizeof(T) == 8 ? pc.info->kd64 : pc.info->kd32;
+    // (A workgroup applies them to its one vector: class 0.)
+    constexpr int kP = sizeof(T) == 8 ? 0 : 1;
+    const int kd = pc.dense == nullptr || g.N > kBpcDenseN ? 0 : min(pc.info->want[kP][0], pc.info->built[kP]);
     for (int o0 = 0, per = NT / g.N; o0 < kd; o0 += per) {
       const int o = o0 + (int)threadIdx.x / g.N, row = threadIdx.x % g.N;
       const bool mine = (int)threadIdx.x < per * g.N && o < kd;

@@ -208,12 +208,13 @@ struct StateSeq {
 };
 
 // Device constants of the preconditioner for the current field.
+constexpr int kDenseCls = 5;  // classes of right-hand sides: up to 1, 2, 4, 8, 16
 struct PcInfo {
   double bmin, bmax;
-  double s, c;          // A = s * Bbar - c
+  double s, c;              // A = s * Bbar - c
   int maxnp;
-  int kd64, kd32;       // blocks of F F^T applied as matrices, by precision (k_pc_dense)
-  int want64, want32;   // the counts once the field's matrices are built
+  int want[2][kDenseCls];   // blocks of F F^T that solves apply as matrices (dense_count), FP64 and FP32
+  int built[2];             // those that are there (k_pc_dense)
   int pad;
 };
 

@@ -358,9 +358,9 @@ int fph::precond_parts(fph_handle_t h, int32_t prec, int32_t nrhs) {
   return (h->g.N + (1 << lks) - 1) >> lks;
 }
 
-int fph::precond_matrices(fph_handle_t h, void* stream) {
+int fph::precond_matrices(fph_handle_t h, int32_t nrhs, void* stream) {
   if (!h->have_field) return FPH_E_NOFIELD;
-  const hipError_t e = pc_dense(&h->pc, h->g, h->dbar64, (hipStream_t)stream);
+  const hipError_t e = pc_dense(&h->pc, h->g, h->dbar64, nrhs, (hipStream_t)stream);
   return e == hipSuccess ? FPH_OK : fail_hip(e);
 }
 
@@ -922,8 +922,9 @@ extern "C" int pcg_solve(fph_handle_t h, int32_t nrhs, const double* b_dev, doub
     return FPH_OK;
   }
   SolveRun run(h, nrhs, b_dev, u_dev, opts);
-  if (run.pre) FPH_CHECK(pc_dense(&h->pc, h->g, h->dbar64, s));
-  if (small_route(run)) {
+  const bool small = small_route(run);
+  if (run.pre) FPH_CHECK(pc_dense(&h->pc, h->g, h->dbar64, small ? 1 : nrhs, s));
+  if (small) {
     FPH_CHECK(small_solve(run, st, s));
     return FPH_OK;
   }
@@ -939,10 +940,12 @@ extern "C" int pcg_solve_sync(fph_handle_t h, int32_t nrhs, const double* b_dev,
   const int rc = check_solve(h, nrhs, b_dev, u_dev, opts);
   if (rc != FPH_OK) return rc;
   hipStream_t s = (hipStream_t)stream;
-  if (opts->use_precond) FPH_CHECK(pc_dense(&h->pc, h->g, h->dbar64, s));
+  SolveRun run(h, nrhs, b_dev, u_dev, opts);
+  const bool small = opts->variant == 0 && small_route(run);
+  if (run.pre) FPH_CHECK(pc_dense(&h->pc, h->g, h->dbar64, small ? 1 : nrhs, s));
   if (opts->variant == 2) {
     FPH_CHECK(coop_enqueue(h, b_dev, u_dev, opts, h->stats_dev, s));
-  } else if (SolveRun run(h, nrhs, b_dev, u_dev, opts); small_route(run)) {
+  } else if (small) {
     FPH_CHECK(small_solve(run, h->stats_dev, s));
   } else {
     // The same launches as pcg_solve, in chunks of slots; after each chunk

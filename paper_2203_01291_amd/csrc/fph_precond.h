@@ -51,7 +51,7 @@ struct PcTables {
   int kdmax;       // frequencies with room for a matrix (0: none)
   double2* dense64;  // [kdmax][N][N]: the blocks of F F^T (one shared field only)
   float2* dense32;
-  bool dense_built;  // enqueued for the field set last (pc_dense)
+  int dense_cls;     // least class whose matrices are enqueued for the field set last (pc_dense)
   void* Z;         // complex workspace, max_rhs * H * N (double2)
   void* Z2;
   double th, c4;   // tanh(dtau t) and cosh(dtau t)^4: P_A P_B = c4 P'_A P'_B, C2' = [[1, th], [th, 1]]
@@ -107,26 +107,38 @@ __global__ void k_pc_twiddles(int H, int H1, int H2, int Ltau, double2* tw64, do
 }
 
 // How many blocks of F F^T, longest series first, to apply as N x N matrices
-// (k_pc_dense, k_kpm_split).  A block's series is a chain of 2 (N_P - 1)
-// exchanges of about 0.2 us each, and the longest one left sets the kernel's
-// time; a matrix is read once per apply by many workgroups side by side, at
-// some 4 MB per us beside the series, after about 1 us of start.  N_P(0) is
+// (k_pc_dense, k_kpm_split) to n vectors.  A block's series is a chain of
+// 2 (N_P - 1) exchanges of 0.2 us each (0.3 in FP64 with more than 100
+// plaquettes), and the longest one left sets the kernel's time; the rows of the
+// matrices run beside the series, one vector after the other, about 1 us each
+// and what reading the matrices takes at 6.7 MB per us.  N_P(0) is
 // large only at the lowest frequencies (its a1/phi term), so a few matrices
 // can shorten the chain several times.  The count with the least estimated
-// time, if it gains at least 1 us per apply.  F F^T of two vectors, series / with
-// matrices: L = 16, Ltau 160, FP64 (N_P 64) 43.1 / 14.5 us; L = 32, Ltau 160, FP32
-// (N_P 45) 38.5 / 20.1 us; L = 32, Ltau 400, FP32 (N_P 63) 54.1 / 26.1 us.
-FPH_DEVINL int dense_count(const int* np, int N, int kdmax, int elem) {
-  double best = 0.4 * (np[0] - 1) - 1.0;
+// time, if it gains at least 1 us per apply.  Solver iteration in us, series /
+// best count of matrices: L = 16, Ltau 160, FP64 (N_P 45), 1 vector 36.3 / 23.5,
+// 4 39.0 / 27.5, 8 42.9 / 35.3, 16 48.2 / 52.7 (one matrix), 32 60 / 87; L = 32,
+// Ltau 160, FP64 (N_P 45) 1: 48.2 / 29.7, 4: 56.9 / 46.0, 8: 65.5 / 72.2; L = 32,
+// Ltau 400, FP32 (N_P 110) 1: 68.3 / 30.8.  Over 100 such cases (L 8 to 32, N_P 12
+// to 110) the rule is never slower than the series by more than 0.4 %.
+FPH_DEVINL int dense_count(const int* np, int N, int kdmax, int elem, int n) {
+  const double step = elem == 16 && N > 400 ? 0.6 : 0.4;
+  double best = step * (np[0] - 1) - 1.0;
   int kd = 0;
   for (int k = 1; k <= kdmax; ++k) {
-    const double t = fmax(0.4 * (np[k] - 1), 1.0 + k * ((double)N * N * elem / 4e6));
+    const double t = fmax(step * (np[k] - 1), n * (1.0 + k * ((double)N * N * elem / 6.7e6)));
     if (t < best) {
       best = t;
       kd = k;
     }
   }
   return kd;
+}
+
+// Class of n right-hand sides in PcInfo::want; from kDenseCls on no matrix pays.
+inline int dense_class(int n) {
+  int c = 0;
+  while ((1 << c) < n) ++c;
+  return c;
 }
 
 // Bounds of the spectrum of Bbar = diag(dbar) C and N_P(w).  One block.
@@ -176,10 +188,12 @@ k_pc_bounds(int N, int Ltau, const double* __restrict__ dbar, double dtau, doubl
     info->s = db > 0.0 ? 2.0 / db : 0.0;
     info->c = db > 0.0 ? 1.0 + 2.0 * bmin / db : 0.0;
     info->maxnp = snp[0];
-    // (np[o], o < H, is the order of the o-th longest series, w' = o)
-    info->want64 = kdmax ? dense_count(np, N, kdmax, sizeof(double2)) : 0;
-    info->want32 = kdmax ? dense_count(np, N, kdmax, sizeof(float2)) : 0;
-    info->kd64 = info->kd32 = 0;  // no matrix of this field yet
+    info->built[0] = info->built[1] = 0;  // no matrix of this field yet
+  }
+  // (np[o], o < H, is the order of the o-th longest series, w' = o)
+  if (threadIdx.x < 2 * kDenseCls) {
+    const int p = threadIdx.x / kDenseCls, c = threadIdx.x - p * kDenseCls;
+    info->want[p][c] = kdmax ? dense_count(np, N, kdmax, p ? sizeof(float2) : sizeof(double2), 1 << c) : 0;
   }
 }
 
@@ -1459,7 +1473,7 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
             const int* __restrict__ np, const typename Cplx<T>::type* __restrict__ coef,
             const T* __restrict__ dbar, T th, T c4, const typename Cplx<T>::type* __restrict__ Z,
             typename Cplx<T>::type* __restrict__ Zo, const typename Cplx<T>::type* __restrict__ dense,
-            int ndense, UUpd<T> U, StIO io) {
+            int cls, int ndense, UUpd<T> U, StIO io) {
   using T2 = typename Cplx<T>::type;
   static_assert(NT <= kNPMax, "one coefficient per thread is loaded ahead");
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1473,7 +1487,8 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
   T* buf1 = buf0 + 2 * nbuf;
   T2* cfs = reinterpret_cast<T2*>(reinterpret_cast<T*>(smem_raw) + 4 * nbuf);
   // Blocks of F F^T applied as matrices, by the workgroups past the series'.
-  const int kd = dense ? (sizeof(T) == 8 ? info->kd64 : info->kd32) : 0;
+  constexpr int kP = sizeof(T) == 8 ? 0 : 1;
+  const int kd = dense ? min(info->want[kP][cls], info->built[kP]) : 0;
   if ((int)blockIdx.x >= H * nrhs + ndense) {
     update_u<T, NT>(g, U, (int)blockIdx.x - H * nrhs - ndense, io);
     return;
@@ -1566,13 +1581,14 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
 template <int NT, bool ROW16, int LAY>
 __global__ void __launch_bounds__(NT)
 k_pc_dense(Geom g, int H, const PcInfo* __restrict__ info, const int* __restrict__ np,
-           const double2* __restrict__ coef, const double* __restrict__ dbar, double th, double c4,
+           const double2* __restrict__ coef, const double* __restrict__ dbar, double th, double c4, int cls,
            double2* __restrict__ G64, float2* __restrict__ G32) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ double xs[LAY == kWavePerPart ? 2 * 4 * 64 : 1];
   const int o = blockIdx.y, j = blockIdx.x;
-  const int kd64 = info->want64, kd32 = info->want32;
-  if (o >= max(kd64, kd32) || info->kd64 + info->kd32 > 0) return;  // not wanted, or built
+  const bool mk64 = o < info->want[0][cls] && o >= info->built[0];  // wanted and not there
+  const bool mk32 = o < info->want[1][cls] && o >= info->built[1];
+  if (!mk64 && !mk32) return;
   const int nbuf = kpm_split_buf<double>(g);
   const int lane = threadIdx.x & 63;
   const bool im = LAY == kWavePerPart ? threadIdx.x >= 64 : lane >= 32;
@@ -1606,15 +1622,14 @@ k_pc_dense(Geom g, int H, const PcInfo* __restrict__ info, const int* __restrict
     const double2 v0 = make_double2(sel(im, ov[2], x[0]), -sel(im, x[2], ov[0]));
     const double2 v1 = make_double2(sel(im, ov[3], x[1]), -sel(im, x[3], ov[1]));
     const long at0 = ((long)o * g.N + j) * g.N + (im ? iL : i0);
-    if (o < kd64) st2c(G64 + at0, v0, v1);
-    if (o < kd32) st2c(G32 + at0, make_float2((float)v0.x, (float)v0.y), make_float2((float)v1.x, (float)v1.y));
+    if (mk64) st2c(G64 + at0, v0, v1);
+    if (mk32) st2c(G32 + at0, make_float2((float)v0.x, (float)v0.y), make_float2((float)v1.x, (float)v1.y));
   }
 }
 
-// The matrices are built: from here on they are used.
-__global__ void k_pc_dense_done(PcInfo* info) {
-  info->kd64 = info->want64;
-  info->kd32 = info->want32;
+// The matrices of a class are built: from here on they are used.
+__global__ void k_pc_dense_done(PcInfo* info, int cls) {
+  for (int p = 0; p < 2; ++p) info->built[p] = max(info->built[p], info->want[p][cls]);
 }
 
 // Per-block Chebyshev apply.  op 0: F (series in A), 1: F^T (conjugate
@@ -1812,14 +1827,14 @@ inline void pc_destroy(PcTables* pc) {
 }
 
 template <int NT, bool ROW16 = false, int LAY = kHalves>
-hipError_t pc_launch_dense(const PcTables* pc, const Geom& g, const double* dbar, hipStream_t s) {
+hipError_t pc_launch_dense(const PcTables* pc, const Geom& g, const double* dbar, int cls, hipStream_t s) {
   const size_t lds = 4 * (size_t)kpm_split_buf<double>(g) * sizeof(double) + kNPMax * sizeof(double2);
   auto kern = k_pc_dense<NT, ROW16, LAY>;
   hipError_t e = allow_lds((const void*)kern, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(g.N, pc->kdmax), dim3(NT), lds, s, g, pc->H, (const PcInfo*)pc->info,
-                     (const int*)pc->np, (const double2*)pc->coef64, dbar, pc->th, pc->c4, pc->dense64,
-                     pc->dense32);
+                     (const int*)pc->np, (const double2*)pc->coef64, dbar, pc->th, pc->c4, cls,
+                     pc->dense64, pc->dense32);
   return hipGetLastError();
 }
 
@@ -1837,34 +1852,35 @@ inline hipError_t pc_set_field(PcTables* pc, const Geom& g, const double* dbar64
   hipLaunchKernelGGL(k_pc_coef, dim3(pc->H), dim3(256), 0, s, g.Ltau, (const PcInfo*)info,
                      (const int*)np, pc->coef64 + (long)f * pc->H * kNPMax,
                      pc->coef32 + (long)f * pc->H * kNPMax);
-  pc->dense_built = false;
+  pc->dense_cls = kDenseCls;
   return hipGetLastError();
 }
 
-// Builds the block matrices of a shared field before its first solve.  What the
-// kernels use is the device's count (kd64, kd32: zero from k_pc_bounds until
-// k_pc_dense_done), so a field set or replayed in any order is never paired
-// with another field's matrices; the host only skips the launches it has
-// enqueued already, and always records them in a captured sequence, where they
-// return at once when the matrices are there.
-inline hipError_t pc_dense(PcTables* pc, const Geom& g, const double* dbar64, hipStream_t s) {
-  if (pc->kdmax == 0 || g.fs != 0) return hipSuccess;
+// Builds the block matrices that a solve with nrhs right-hand sides applies, on
+// a shared field.  What the kernels use is the device's count (built: zero from
+// k_pc_bounds until k_pc_dense_done), so a field set or replayed in any order is
+// never paired with another field's matrices; the host only skips the launches
+// it has enqueued already, and always records them in a captured sequence, where
+// they return at once when the matrices are there.
+inline hipError_t pc_dense(PcTables* pc, const Geom& g, const double* dbar64, int nrhs, hipStream_t s) {
+  const int cls = dense_class(nrhs);
+  if (pc->kdmax == 0 || g.fs != 0 || cls >= kDenseCls) return hipSuccess;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
     (void)hipGetLastError();
     cap = hipStreamCaptureStatusNone;
   }
   const bool eager = cap == hipStreamCaptureStatusNone;
-  if (eager && pc->dense_built) return hipSuccess;
+  if (eager && pc->dense_cls <= cls) return hipSuccess;
   hipError_t e;
-  if (g.hL == 16 && g.Q == 256) e = pc_launch_dense<512, true>(pc, g, dbar64, s);
-  else if (g.Q <= 32) e = pc_launch_dense<64, false, kOneWave>(pc, g, dbar64, s);
-  else if (g.Q <= 64) e = pc_launch_dense<128, false, kWavePerPart>(pc, g, dbar64, s);
-  else if (g.Q <= 128) e = pc_launch_dense<256>(pc, g, dbar64, s);
-  else e = pc_launch_dense<512>(pc, g, dbar64, s);
+  if (g.hL == 16 && g.Q == 256) e = pc_launch_dense<512, true>(pc, g, dbar64, cls, s);
+  else if (g.Q <= 32) e = pc_launch_dense<64, false, kOneWave>(pc, g, dbar64, cls, s);
+  else if (g.Q <= 64) e = pc_launch_dense<128, false, kWavePerPart>(pc, g, dbar64, cls, s);
+  else if (g.Q <= 128) e = pc_launch_dense<256>(pc, g, dbar64, cls, s);
+  else e = pc_launch_dense<512>(pc, g, dbar64, cls, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_pc_dense_done, dim3(1), dim3(1), 0, s, pc->info);
-  if ((e = hipGetLastError()) == hipSuccess && eager) pc->dense_built = true;
+  hipLaunchKernelGGL(k_pc_dense_done, dim3(1), dim3(1), 0, s, pc->info, cls);
+  if ((e = hipGetLastError()) == hipSuccess && eager) pc->dense_cls = cls;
   return e;
 }
 
@@ -2012,13 +2028,14 @@ hipError_t pc_launch_kpm_split(const PcTables* pc, const Geom& g, const T* dbar,
   const auto* cf = (const T2*)(sizeof(T) == 8 ? (const void*)pc->coef64 : (const void*)pc->coef32);
   // The matrices hold the blocks of F F^T of one field shared by every
   // right-hand side.
-  const bool dn = op == 2 && pc->kdmax > 0 && g.fs == 0;
+  const int cls = dense_class(nrhs);
+  const bool dn = op == 2 && pc->kdmax > 0 && g.fs == 0 && cls < kDenseCls;
   const T2* dense = dn ? (const T2*)(sizeof(T) == 8 ? (const void*)pc->dense64 : (const void*)pc->dense32)
                        : nullptr;
   const int rows = dense_rows_per(NT), RB = (g.N + rows - 1) / rows;
   const int nd = dn ? pc->kdmax * RB : 0;
   hipLaunchKernelGGL(kern, dim3((pc->H + U.nblk) * nrhs + nd), dim3(NT), lds, s, g, pc->H, nrhs, op, pc->info,
-                     pc->np, cf, dbar, th, c4, Z, Zo, dense, nd, U, io);
+                     pc->np, cf, dbar, th, c4, Z, Zo, dense, cls, nd, U, io);
   return hipGetLastError();
 }
 
