@@ -12,9 +12,9 @@ namespace fph {
 // Records hipGetErrorString(e) as the message of FPH_E_HIP and returns FPH_E_HIP.
 int record_hip_error(hipError_t e);
 
-// Builds what a solve's applies of F F^T to nrhs vectors on the current field
-// gain from and a single apply does not (pc_dense); call once per solve.
-int precond_matrices(fph_handle_t h, int32_t nrhs, void* stream);
+// Builds what a solve's applies of F F^T to nrhs vectors in precision prec on the
+// current field gain from and a single apply does not (pc_dense); call once per solve.
+int precond_matrices(fph_handle_t h, int32_t prec, int32_t nrhs, void* stream);
 
 // fph_precond_apply of F F^T that also writes partial sums of in_r . out_r,
 // part_dev[r * nparts + k], k < nparts; nparts (at most N) = precond_parts.

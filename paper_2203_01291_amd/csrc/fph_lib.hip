@@ -358,9 +358,10 @@ int fph::precond_parts(fph_handle_t h, int32_t prec, int32_t nrhs) {
   return (h->g.N + (1 << lks) - 1) >> lks;
 }
 
-int fph::precond_matrices(fph_handle_t h, int32_t nrhs, void* stream) {
+int fph::precond_matrices(fph_handle_t h, int32_t prec, int32_t nrhs, void* stream) {
   if (!h->have_field) return FPH_E_NOFIELD;
-  const hipError_t e = pc_dense(&h->pc, h->g, h->dbar64, nrhs, (hipStream_t)stream);
+  const hipError_t e = prec == FPH_F64 ? pc_dense<double>(&h->pc, h->g, h->dbar64, nrhs, (hipStream_t)stream)
+                                       : pc_dense<float>(&h->pc, h->g, h->dbar64, nrhs, (hipStream_t)stream);
   return e == hipSuccess ? FPH_OK : fail_hip(e);
 }
 
@@ -703,6 +704,13 @@ struct SolveRun {
                           w32.pb, w32.Ap, b, w32.r, u, h->u64b, h->u32};
   }
 
+  // The preconditioner's block matrices (a workgroup of a one-launch solve has one vector).
+  hipError_t matrices(bool small, hipStream_t s) {
+    if (!pre) return hipSuccess;
+    const int n = small ? 1 : nrhs;
+    return mixed ? pc_dense<float>(&h->pc, h->g, h->dbar64, n, s) : pc_dense<double>(&h->pc, h->g, h->dbar64, n, s);
+  }
+
   hipError_t start(hipStream_t s) {
     hipLaunchKernelGGL(k_solve_init, dim3(1), dim3(64), 0, s, nrhs, init, sq.latest());
     hipError_t e = hipGetLastError();
@@ -923,7 +931,7 @@ extern "C" int pcg_solve(fph_handle_t h, int32_t nrhs, const double* b_dev, doub
   }
   SolveRun run(h, nrhs, b_dev, u_dev, opts);
   const bool small = small_route(run);
-  if (run.pre) FPH_CHECK(pc_dense(&h->pc, h->g, h->dbar64, small ? 1 : nrhs, s));
+  FPH_CHECK(run.matrices(small, s));
   if (small) {
     FPH_CHECK(small_solve(run, st, s));
     return FPH_OK;
@@ -942,7 +950,7 @@ extern "C" int pcg_solve_sync(fph_handle_t h, int32_t nrhs, const double* b_dev,
   hipStream_t s = (hipStream_t)stream;
   SolveRun run(h, nrhs, b_dev, u_dev, opts);
   const bool small = opts->variant == 0 && small_route(run);
-  if (run.pre) FPH_CHECK(pc_dense(&h->pc, h->g, h->dbar64, small ? 1 : nrhs, s));
+  FPH_CHECK(run.matrices(small, s));
   if (opts->variant == 2) {
     FPH_CHECK(coop_enqueue(h, b_dev, u_dev, opts, h->stats_dev, s));
   } else if (small) {

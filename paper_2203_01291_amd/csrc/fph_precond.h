@@ -51,7 +51,7 @@ struct PcTables {
   int kdmax;       // frequencies with room for a matrix (0: none)
   double2* dense64;  // [kdmax][N][N]: the blocks of F F^T (one shared field only)
   float2* dense32;
-  int dense_cls;     // least class whose matrices are enqueued for the field set last (pc_dense)
+  int dense_cls[2];  // least class whose matrices are enqueued for the field set last (pc_dense), FP64 and FP32
   void* Z;         // complex workspace, max_rhs * H * N (double2)
   void* Z2;
   double th, c4;   // tanh(dtau t) and cosh(dtau t)^4: P_A P_B = c4 P'_A P'_B, C2' = [[1, th], [th, 1]]
@@ -1571,24 +1571,24 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
 // The block matrices G = f(A) f(A)^H of F F^T that k_kpm_split applies instead
 // of their series: workgroup (j, o) runs the two series of order o on the
 // unit vector of site j, in FP64, and stores the result, column j, as row j
-// conjugated (G is Hermitian), so that the store is contiguous.  The FP32 matrix
+// conjugated (G is Hermitian), so that the store is contiguous.  An FP32 matrix
 // is the FP64 one rounded, so FP32 applies are closer to the exact series than
 // the FP32 recurrence was (relative error 1.1e-6 -> 1.8e-7 at L = 32, Ltau 160,
 // N_P 45; FP64 unchanged, 1.7e-14).  Built by the first solve on a shared field:
 // 34 us for 16 blocks at L = 16, 25-115 us at L = 32, gained back within five
 // applies.  A single apply does not build them (ten FP32 vectors at L = 32, Ltau
 // 400 with a new field: 95 us, 186 us if it did) and uses them if they are there.
-template <int NT, bool ROW16, int LAY>
+template <typename T, int NT, bool ROW16, int LAY>
 __global__ void __launch_bounds__(NT)
 k_pc_dense(Geom g, int H, const PcInfo* __restrict__ info, const int* __restrict__ np,
            const double2* __restrict__ coef, const double* __restrict__ dbar, double th, double c4, int cls,
-           double2* __restrict__ G64, float2* __restrict__ G32) {
+           typename Cplx<T>::type* __restrict__ G) {
+  using T2 = typename Cplx<T>::type;
+  constexpr int kP = sizeof(T) == 8 ? 0 : 1;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ double xs[LAY == kWavePerPart ? 2 * 4 * 64 : 1];
   const int o = blockIdx.y, j = blockIdx.x;
-  const bool mk64 = o < info->want[0][cls] && o >= info->built[0];  // wanted and not there
-  const bool mk32 = o < info->want[1][cls] && o >= info->built[1];
-  if (!mk64 && !mk32) return;
+  if (o >= info->want[kP][cls] || o < info->built[kP]) return;  // not wanted, or there
   const int nbuf = kpm_split_buf<double>(g);
   const int lane = threadIdx.x & 63;
   const bool im = LAY == kWavePerPart ? threadIdx.x >= 64 : lane >= 32;
@@ -1619,17 +1619,15 @@ k_pc_dense(Geom g, int H, const PcInfo* __restrict__ info, const int* __restrict
   double ov[4];
   swap(x, ov);
   if (own) {  // row y0 by the real lane, row y0+1 by the imaginary one
-    const double2 v0 = make_double2(sel(im, ov[2], x[0]), -sel(im, x[2], ov[0]));
-    const double2 v1 = make_double2(sel(im, ov[3], x[1]), -sel(im, x[3], ov[1]));
-    const long at0 = ((long)o * g.N + j) * g.N + (im ? iL : i0);
-    if (mk64) st2c(G64 + at0, v0, v1);
-    if (mk32) st2c(G32 + at0, make_float2((float)v0.x, (float)v0.y), make_float2((float)v1.x, (float)v1.y));
+    const T2 v0 = T2{(T)sel(im, ov[2], x[0]), (T)-sel(im, x[2], ov[0])};
+    const T2 v1 = T2{(T)sel(im, ov[3], x[1]), (T)-sel(im, x[3], ov[1])};
+    st2c(G + ((long)o * g.N + j) * g.N + (im ? iL : i0), v0, v1);
   }
 }
 
-// The matrices of a class are built: from here on they are used.
-__global__ void k_pc_dense_done(PcInfo* info, int cls) {
-  for (int p = 0; p < 2; ++p) info->built[p] = max(info->built[p], info->want[p][cls]);
+// The matrices of a class are built (p: FP64 or FP32): from here on they are used.
+__global__ void k_pc_dense_done(PcInfo* info, int p, int cls) {
+  info->built[p] = max(info->built[p], info->want[p][cls]);
 }
 
 // Per-block Chebyshev apply.  op 0: F (series in A), 1: F^T (conjugate
@@ -1826,15 +1824,16 @@ inline void pc_destroy(PcTables* pc) {
   std::memset(pc, 0, sizeof(*pc));
 }
 
-template <int NT, bool ROW16 = false, int LAY = kHalves>
+template <typename T, int NT, bool ROW16 = false, int LAY = kHalves>
 hipError_t pc_launch_dense(const PcTables* pc, const Geom& g, const double* dbar, int cls, hipStream_t s) {
   const size_t lds = 4 * (size_t)kpm_split_buf<double>(g) * sizeof(double) + kNPMax * sizeof(double2);
-  auto kern = k_pc_dense<NT, ROW16, LAY>;
+  auto kern = k_pc_dense<T, NT, ROW16, LAY>;
   hipError_t e = allow_lds((const void*)kern, lds);
   if (e != hipSuccess) return e;
+  using T2 = typename Cplx<T>::type;
+  T2* G = (T2*)(sizeof(T) == 8 ? (void*)pc->dense64 : (void*)pc->dense32);
   hipLaunchKernelGGL(kern, dim3(g.N, pc->kdmax), dim3(NT), lds, s, g, pc->H, (const PcInfo*)pc->info,
-                     (const int*)pc->np, (const double2*)pc->coef64, dbar, pc->th, pc->c4, cls,
-                     pc->dense64, pc->dense32);
+                     (const int*)pc->np, (const double2*)pc->coef64, dbar, pc->th, pc->c4, cls, G);
   return hipGetLastError();
 }
 
@@ -1852,35 +1851,52 @@ inline hipError_t pc_set_field(PcTables* pc, const Geom& g, const double* dbar64
   hipLaunchKernelGGL(k_pc_coef, dim3(pc->H), dim3(256), 0, s, g.Ltau, (const PcInfo*)info,
                      (const int*)np, pc->coef64 + (long)f * pc->H * kNPMax,
                      pc->coef32 + (long)f * pc->H * kNPMax);
-  pc->dense_cls = kDenseCls;
+  pc->dense_cls[0] = pc->dense_cls[1] = kDenseCls;
   return hipGetLastError();
 }
 
-// Builds the block matrices that a solve with nrhs right-hand sides applies, on
-// a shared field.  What the kernels use is the device's count (built: zero from
-// k_pc_bounds until k_pc_dense_done), so a field set or replayed in any order is
-// never paired with another field's matrices; the host only skips the launches
-// it has enqueued already, and always records them in a captured sequence, where
-// they return at once when the matrices are there.
-inline hipError_t pc_dense(PcTables* pc, const Geom& g, const double* dbar64, int nrhs, hipStream_t s) {
+// Whether the series kernel is k_kpm_split (its rule stands with pc_kpm).
+template <typename T>
+bool pc_split(const PcTables* pc, const Geom& g, int nrhs) {
+  return g.Q <= 256 && (sizeof(T) == 8 || g.hL != 16 || (long)pc->H * nrhs <= 512);
+}
+
+// The class whose matrices an apply of F F^T to nrhs vectors takes, or -1 where
+// it takes none: they hold the blocks of one field shared by every vector, and
+// k_kpm_split reads them.
+template <typename T>
+int pc_dense_class(const PcTables* pc, const Geom& g, int nrhs) {
   const int cls = dense_class(nrhs);
-  if (pc->kdmax == 0 || g.fs != 0 || cls >= kDenseCls) return hipSuccess;
+  return pc->kdmax > 0 && g.fs == 0 && cls < kDenseCls && pc_split<T>(pc, g, nrhs) ? cls : -1;
+}
+
+// Builds the block matrices that a solve with nrhs right-hand sides in
+// iteration precision T applies.  What the kernels use is the device's count
+// (built: zero from k_pc_bounds until k_pc_dense_done), so a field set or
+// replayed in any order is never paired with another field's matrices; the host
+// only skips the launches it has enqueued already, and always records them in a
+// captured sequence, where they return at once when the matrices are there.
+template <typename T>
+hipError_t pc_dense(PcTables* pc, const Geom& g, const double* dbar64, int nrhs, hipStream_t s) {
+  constexpr int p = sizeof(T) == 8 ? 0 : 1;
+  const int cls = pc_dense_class<T>(pc, g, nrhs);
+  if (cls < 0) return hipSuccess;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
     (void)hipGetLastError();
     cap = hipStreamCaptureStatusNone;
   }
   const bool eager = cap == hipStreamCaptureStatusNone;
-  if (eager && pc->dense_cls <= cls) return hipSuccess;
+  if (eager && pc->dense_cls[p] <= cls) return hipSuccess;
   hipError_t e;
-  if (g.hL == 16 && g.Q == 256) e = pc_launch_dense<512, true>(pc, g, dbar64, cls, s);
-  else if (g.Q <= 32) e = pc_launch_dense<64, false, kOneWave>(pc, g, dbar64, cls, s);
-  else if (g.Q <= 64) e = pc_launch_dense<128, false, kWavePerPart>(pc, g, dbar64, cls, s);
-  else if (g.Q <= 128) e = pc_launch_dense<256>(pc, g, dbar64, cls, s);
-  else e = pc_launch_dense<512>(pc, g, dbar64, cls, s);
+  if (g.hL == 16) e = pc_launch_dense<T, 512, true>(pc, g, dbar64, cls, s);
+  else if (g.Q <= 32) e = pc_launch_dense<T, 64, false, kOneWave>(pc, g, dbar64, cls, s);
+  else if (g.Q <= 64) e = pc_launch_dense<T, 128, false, kWavePerPart>(pc, g, dbar64, cls, s);
+  else if (g.Q <= 128) e = pc_launch_dense<T, 256>(pc, g, dbar64, cls, s);
+  else e = pc_launch_dense<T, 512>(pc, g, dbar64, cls, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_pc_dense_done, dim3(1), dim3(1), 0, s, pc->info, cls);
-  if ((e = hipGetLastError()) == hipSuccess && eager) pc->dense_cls = cls;
+  hipLaunchKernelGGL(k_pc_dense_done, dim3(1), dim3(1), 0, s, pc->info, p, cls);
+  if ((e = hipGetLastError()) == hipSuccess && eager) pc->dense_cls[p] = cls;
   return e;
 }
 
@@ -2026,10 +2042,8 @@ hipError_t pc_launch_kpm_split(const PcTables* pc, const Geom& g, const T* dbar,
   hipError_t e = allow_lds((const void*)kern, lds);
   if (e != hipSuccess) return e;
   const auto* cf = (const T2*)(sizeof(T) == 8 ? (const void*)pc->coef64 : (const void*)pc->coef32);
-  // The matrices hold the blocks of F F^T of one field shared by every
-  // right-hand side.
-  const int cls = dense_class(nrhs);
-  const bool dn = op == 2 && pc->kdmax > 0 && g.fs == 0 && cls < kDenseCls;
+  const int cls = op == 2 ? pc_dense_class<T>(pc, g, nrhs) : -1;
+  const bool dn = cls >= 0;
   const T2* dense = dn ? (const T2*)(sizeof(T) == 8 ? (const void*)pc->dense64 : (const void*)pc->dense32)
                        : nullptr;
   const int rows = dense_rows_per(NT), RB = (g.N + rows - 1) / rows;
@@ -2052,20 +2066,19 @@ hipError_t pc_kpm(const PcTables* pc, const Geom& g, const T* dbar, int op, int 
   // unsplit form needs fewer instructions (Ltau = 400: split 19.1 against
   // 20.8 us for one right-hand side, 23.2 / 24.1 for two, 33.2 / 32.2 for
   // four, 49.1 / 46.5 for ten); FP64 gains or ties throughout.
-  if (g.hL == 16 && g.Q == 256) {
-    if (sizeof(T) == 8 || (long)pc->H * nrhs <= 512)
-      return pc_launch_kpm_split<T, 512, true>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
-    return pc_launch_kpm<T, 256, true>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
+  if (!pc_split<T>(pc, g, nrhs)) {
+    if (g.hL == 16) return pc_launch_kpm<T, 256, true>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
+    if (g.Q <= 512) return pc_launch_kpm<T, 512>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
+    return pc_launch_kpm<T, 1024>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
   }
+  if (g.hL == 16) return pc_launch_kpm_split<T, 512, true>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
   if (g.Q <= 32)
     return pc_launch_kpm_split<T, 64, false, kOneWave>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
   if (g.Q <= 64)
     return pc_launch_kpm_split<T, 128, false, kWavePerPart>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4,
                                                             s);
   if (g.Q <= 128) return pc_launch_kpm_split<T, 256>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
-  if (g.Q <= 256) return pc_launch_kpm_split<T, 512>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
-  if (g.Q <= 512) return pc_launch_kpm<T, 512>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
-  return pc_launch_kpm<T, 1024>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
+  return pc_launch_kpm_split<T, 512>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
 }
 
 // out = op(in) (op: 0 F, 1 F^T, 2 F F^T).  With rdot != nullptr the inverse

@@ -1219,7 +1219,7 @@ int ssh_solve(fph_ssh_t c, int32_t nrhs, const double* b_dev, double* u_dev, con
     return FPH_E_ARG;
   if (opts->prec == FPH_F32_REFINED && (opts->max_outer < 0 || !(opts->ru_delta >= 0.0))) return FPH_E_ARG;
   if (pre) {
-    const int rc = fph::precond_matrices(c->pc, nrhs, stream);
+    const int rc = fph::precond_matrices(c->pc, opts->prec == FPH_F64 ? FPH_F64 : FPH_F32, nrhs, stream);
     if (rc != FPH_OK) return rc;
   }
   if (opts->prec == FPH_F32_REFINED) return solve_refined(c, nrhs, b_dev, u_dev, opts, stats_host, stream);

@@ -1,0 +1,88 @@
+"""Which kernels a call enqueues, shown without a GPU: the library runs on the recording HIP runtime of
+_hip_recorder.c, in a process of its own."""
+
+import json
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, json, sys
+sys.path.insert(0, {root!r})
+rec = ctypes.CDLL({so!r}, mode=ctypes.RTLD_GLOBAL)
+rec.rec_name.restype, rec.rec_threads.restype = ctypes.c_char_p, ctypes.c_long
+from paper_2203_01291_amd import _lib
+lib = ctypes.CDLL(_lib.LIB_PATH)
+for name, (res, args) in _lib.EXPORTS.items():
+    getattr(lib, name).restype, getattr(lib, name).argtypes = res, args
+P = ctypes.c_void_p(1 << 20)  # a device pointer that nothing reads
+def lattice(L, Ltau):
+    return _lib.Lattice(L, Ltau, 0.1, 1.0, 0.0, 1.0)
+def handle(L, Ltau, n):
+    h = ctypes.c_void_p()
+    rc = lib.fph_create(ctypes.byref(h), ctypes.byref(lattice(L, Ltau)), n)
+    return h if rc == 0 else rc
+def opts(prec, precond=1, maxiter=2):
+    return ctypes.byref(_lib.PcgOpts(1e-8, maxiter, precond, prec, 1, 0.0, 0, 0, 1, 0, 1.0, 1.0))
+def names():
+    out = [rec.rec_name(i).decode() for i in range(rec.rec_count())]
+    rec.rec_reset()
+    return out
+out = {{}}
+"""
+
+
+@pytest.fixture(scope="module")
+def record(tmp_path_factory):
+    from paper_2203_01291_amd import _lib
+    gcc = shutil.which("gcc")
+    if gcc is None or not os.path.exists(_lib.LIB_PATH):
+        pytest.skip("needs gcc and the built library")
+    so = str(tmp_path_factory.mktemp("rec") / "rec.so")
+    subprocess.run([gcc, "-O1", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "_hip_recorder.c")], check=True)
+
+    def run(body):
+        code = PRELUDE.format(root=ROOT, so=so) + body + "\nprint(json.dumps(out))"
+        r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stderr
+        return json.loads(r.stdout.splitlines()[-1])
+
+    return run
+
+
+# Block matrices are built in the precision a solve reads, once per field, and only where its series
+# kernel reads any: not by k_kpm (FP32 L = 32 with many blocks), not for many right-hand sides.
+def test_matrices_are_built_where_they_are_read(record):
+    out = record("""
+def solve(h, prec, n, sync=False):
+    names()
+    f = lib.pcg_solve_sync if sync else lib.pcg_solve
+    assert f(h, n, P, P, opts(prec), P if not sync else None, None) == 0
+    return sorted({"d" if "k_pc_denseId" in k else "f" for k in names()
+                   if "k_pc_dense" in k and "done" not in k})
+F64, F32 = _lib.FPH_F64, _lib.FPH_F32_REFINED
+h = handle(32, 400, 10)
+lib.fph_set_field(h, P, 1.0, 1.0, None)
+out["unread"] = solve(h, F32, 10) + solve(h, F32, 3, True)
+out["read"] = solve(h, F32, 2)
+h = handle(16, 160, 40)
+lib.fph_set_field(h, P, 1.0, 1.0, None)
+out["many"] = solve(h, F64, 40) + solve(h, F32, 17)
+out["f64"] = solve(h, F64, 4)
+out["again"] = solve(h, F64, 4) + solve(h, F64, 7, True)
+out["fewer"] = solve(h, F64, 1)
+out["f32"] = solve(h, F32, 4, True)
+rec.rec_capturing(1)
+out["captured"] = solve(h, F64, 4)
+rec.rec_capturing(0)
+lib.fph_set_fields(h, 2, 2, P, 1.0, 1.0, None)
+out["fields"] = solve(h, F64, 4)
+""")
+    assert out == {"unread": [], "read": ["f"], "many": [], "f64": ["d"], "again": [], "fewer": ["d"],
+                   "f32": ["f"], "captured": ["d"], "fields": []}
