@@ -16,7 +16,8 @@ int record_hip_error(hipError_t e);
 // current field gain from and a single apply does not (pc_dense); call once per solve.
 int precond_matrices(fph_handle_t h, int32_t prec, int32_t nrhs, void* stream);
 
-// fph_precond_apply of F F^T that also writes partial sums of in_r . out_r,
+// F F^T of a solver: fph_precond_apply that takes the matrices of
+// precond_matrices where there are any and also writes partial sums of in_r . out_r,
 // part_dev[r * nparts + k], k < nparts; nparts (at most N) = precond_parts.
 int precond_parts(fph_handle_t h, int32_t prec, int32_t nrhs);
 int precond_apply_dot(fph_handle_t h, int32_t prec, int32_t nrhs, const void* in_dev, void* out_dev,

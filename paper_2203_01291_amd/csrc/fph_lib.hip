@@ -330,7 +330,7 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 namespace {
 
-// fph_precond_apply; with part, also partials of in_r . out_r.
+// fph_precond_apply; with part (a solver's F F^T) also partials of in_r . out_r.
 int precond_call(fph_handle_t h, int32_t op, int32_t prec, int32_t nrhs, const void* in_dev, void* out_dev,
                  double* part, void* stream) {
   if (h == nullptr || in_dev == nullptr || out_dev == nullptr) return FPH_E_NULL;
@@ -341,10 +341,10 @@ int precond_call(fph_handle_t h, int32_t op, int32_t prec, int32_t nrhs, const v
   hipError_t e;
   StateSeq sq{{nullptr, nullptr}, {nullptr, nullptr}, 0, 0, false, part};
   if (prec == FPH_F64)
-    e = pc_apply<double>(&h->pc, h->g, h->dbar64, op, nrhs, (const double*)in_dev, (double*)out_dev,
+    e = pc_apply<double>(&h->pc, h->g, h->dbar64, op, nrhs, part != nullptr, (const double*)in_dev, (double*)out_dev,
                          part ? (const double*)in_dev : nullptr, sq, s);
   else
-    e = pc_apply<float>(&h->pc, h->g, h->dbar32, op, nrhs, (const float*)in_dev, (float*)out_dev,
+    e = pc_apply<float>(&h->pc, h->g, h->dbar32, op, nrhs, part != nullptr, (const float*)in_dev, (float*)out_dev,
                         part ? (const float*)in_dev : nullptr, sq, s);
   if (e != hipSuccess) return fail_hip(e);
   return FPH_OK;

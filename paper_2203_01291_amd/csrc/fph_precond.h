@@ -1576,8 +1576,7 @@ k_kpm_split(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
 // the FP32 recurrence was (relative error 1.1e-6 -> 1.8e-7 at L = 32, Ltau 160,
 // N_P 45; FP64 unchanged, 1.7e-14).  Built by the first solve on a shared field:
 // 34 us for 16 blocks at L = 16, 25-115 us at L = 32, gained back within five
-// applies.  A single apply does not build them (ten FP32 vectors at L = 32, Ltau
-// 400 with a new field: 95 us, 186 us if it did) and uses them if they are there.
+// applies.
 template <typename T, int NT, bool ROW16, int LAY>
 __global__ void __launch_bounds__(NT)
 k_pc_dense(Geom g, int H, const PcInfo* __restrict__ info, const int* __restrict__ np,
@@ -2031,7 +2030,7 @@ hipError_t pc_launch_kpm(const PcTables* pc, const Geom& g, const T* dbar, int o
 }
 
 template <typename T, int NT, bool ROW16 = false, int LAY = kHalves>
-hipError_t pc_launch_kpm_split(const PcTables* pc, const Geom& g, const T* dbar, int op, int nrhs,
+hipError_t pc_launch_kpm_split(const PcTables* pc, const Geom& g, const T* dbar, int op, int nrhs, int cls,
                                const typename Cplx<T>::type* Z, typename Cplx<T>::type* Zo, UUpd<T> U,
                                StateSeq& sq, T th, T c4, hipStream_t s) {
   U.nblk = U.u ? u_blocks<T>(g, NT) : 0;
@@ -2042,7 +2041,6 @@ hipError_t pc_launch_kpm_split(const PcTables* pc, const Geom& g, const T* dbar,
   hipError_t e = allow_lds((const void*)kern, lds);
   if (e != hipSuccess) return e;
   const auto* cf = (const T2*)(sizeof(T) == 8 ? (const void*)pc->coef64 : (const void*)pc->coef32);
-  const int cls = op == 2 ? pc_dense_class<T>(pc, g, nrhs) : -1;
   const bool dn = cls >= 0;
   const T2* dense = dn ? (const T2*)(sizeof(T) == 8 ? (const void*)pc->dense64 : (const void*)pc->dense32)
                        : nullptr;
@@ -2053,8 +2051,11 @@ hipError_t pc_launch_kpm_split(const PcTables* pc, const Geom& g, const T* dbar,
   return hipGetLastError();
 }
 
+// matrices: F F^T of a solver, which takes the block matrices that are there (an
+// apply of its own always runs the series, so its result does not depend on
+// what the handle did before).
 template <typename T>
-hipError_t pc_kpm(const PcTables* pc, const Geom& g, const T* dbar, int op, int nrhs,
+hipError_t pc_kpm(const PcTables* pc, const Geom& g, const T* dbar, int op, int nrhs, bool matrices,
                   const typename Cplx<T>::type* Z, typename Cplx<T>::type* Zo, const UUpd<T>& U,
                   StateSeq& sq, T th, T c4, hipStream_t s) {
   // Split parts up to 256 plaquettes (8 waves); with 16 waves per block
@@ -2071,27 +2072,28 @@ hipError_t pc_kpm(const PcTables* pc, const Geom& g, const T* dbar, int op, int 
     if (g.Q <= 512) return pc_launch_kpm<T, 512>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
     return pc_launch_kpm<T, 1024>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
   }
-  if (g.hL == 16) return pc_launch_kpm_split<T, 512, true>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
+  const int cls = matrices ? pc_dense_class<T>(pc, g, nrhs) : -1;
+  if (g.hL == 16) return pc_launch_kpm_split<T, 512, true>(pc, g, dbar, op, nrhs, cls, Z, Zo, U, sq, th, c4, s);
   if (g.Q <= 32)
-    return pc_launch_kpm_split<T, 64, false, kOneWave>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
+    return pc_launch_kpm_split<T, 64, false, kOneWave>(pc, g, dbar, op, nrhs, cls, Z, Zo, U, sq, th, c4, s);
   if (g.Q <= 64)
-    return pc_launch_kpm_split<T, 128, false, kWavePerPart>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4,
-                                                            s);
-  if (g.Q <= 128) return pc_launch_kpm_split<T, 256>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
-  return pc_launch_kpm_split<T, 512>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
+    return pc_launch_kpm_split<T, 128, false, kWavePerPart>(pc, g, dbar, op, nrhs, cls, Z, Zo, U, sq, th,
+                                                            c4, s);
+  if (g.Q <= 128) return pc_launch_kpm_split<T, 256>(pc, g, dbar, op, nrhs, cls, Z, Zo, U, sq, th, c4, s);
+  return pc_launch_kpm_split<T, 512>(pc, g, dbar, op, nrhs, cls, Z, Zo, U, sq, th, c4, s);
 }
 
 // out = op(in) (op: 0 F, 1 F^T, 2 F F^T).  With rdot != nullptr the inverse
 // transform also publishes rdot . out as P_RZ partials, or into sq.plain.
 template <typename T>
-hipError_t pc_apply(const PcTables* pc, const Geom& g, const T* dbar, int op, int nrhs,
+hipError_t pc_apply(const PcTables* pc, const Geom& g, const T* dbar, int op, int nrhs, bool matrices,
                     const T* in, T* out, const T* rdot, StateSeq& sq, hipStream_t s) {
   using T2 = typename Cplx<T>::type;
   T2* Z = reinterpret_cast<T2*>(pc->Z);
   T2* Z2 = reinterpret_cast<T2*>(pc->Z2);
   hipError_t e = pc_fwd<T>(pc, g, nrhs, const_cast<T*>(in), Z, nullptr, sq, false, s);
   if (e != hipSuccess) return e;
-  e = pc_kpm<T>(pc, g, dbar, op, nrhs, Z, Z2, UUpd<T>{}, sq, (T)pc->th, (T)pc->c4, s);
+  e = pc_kpm<T>(pc, g, dbar, op, nrhs, matrices, Z, Z2, UUpd<T>{}, sq, (T)pc->th, (T)pc->c4, s);
   if (e != hipSuccess) return e;
   return pc_inv<T>(pc, g, nrhs, Z2, out, rdot ? 1 : 0, rdot, sq, s);
 }
@@ -2108,7 +2110,7 @@ hipError_t pc_cg_update(const PcTables* pc, const Geom& g, const T* dbar, int nr
   T2* Z2 = reinterpret_cast<T2*>(pc->Z2);
   hipError_t e = pc_fwd<T>(pc, g, nrhs, r, Z, Ap, sq, true, s);
   if (e != hipSuccess) return e;
-  e = pc_kpm<T>(pc, g, dbar, 2, nrhs, Z, Z2, UUpd<T>{u, pa, pb, 0}, sq, (T)pc->th, (T)pc->c4, s);
+  e = pc_kpm<T>(pc, g, dbar, 2, nrhs, true, Z, Z2, UUpd<T>{u, pa, pb, 0}, sq, (T)pc->th, (T)pc->c4, s);
   if (e != hipSuccess) return e;
   return pc_inv<T>(pc, g, nrhs, Z2, z, 1, r, sq, s);
 }

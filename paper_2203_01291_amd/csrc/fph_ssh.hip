@@ -855,7 +855,7 @@ int solve_refined(fph_ssh_s* c, int nrhs, const double* b_dev, double* u_dev, co
     hipLaunchKernelGGL(k_to_f32, dim3(grid_for(n)), dim3(256), 0, s, n, (const double*)c->r, c->r32);
     SSH_CHECK(hipGetLastError());
     if (pre) {
-      const int rc = fph_precond_apply(c->pc, FPH_PC_FFT, FPH_F32, nrhs, c->r32, c->z32, stream);
+      const int rc = fph::precond_apply_dot(c->pc, FPH_F32, nrhs, c->r32, c->z32, c->part2, stream);
       if (rc != FPH_OK) return rc;
     }
     SSH_CHECK(dots<float>(c, nrhs, c->r32, c->r32, s));
@@ -1232,7 +1232,7 @@ int ssh_solve(fph_ssh_t c, int32_t nrhs, const double* b_dev, double* u_dev, con
   double* z = pre ? c->z : c->r;  // z = F F^T r, or r itself
   const double* p2 = pre ? c->part2 : c->part;
   auto precondition = [&]() -> int {
-    return pre ? fph_precond_apply(c->pc, FPH_PC_FFT, FPH_F64, nrhs, c->r, c->z, stream) : FPH_OK;
+    return pre ? fph::precond_apply_dot(c->pc, FPH_F64, nrhs, c->r, c->z, c->part2, stream) : FPH_OK;
   };
   auto sum_host = [&](std::vector<double>& out) -> int {
     std::vector<double> part((size_t)nrhs * kRedBlocks);
@@ -1308,10 +1308,8 @@ int ssh_solve(fph_ssh_t c, int32_t nrhs, const double* b_dev, double* u_dev, con
       hipLaunchKernelGGL(k_cg_xr<double>, dim3(kXrBlocks, nrhs), dim3(256), 0, s, d, sa, c->G.Ltau, pq,
                          (const double*)pn, (const double*)c->q, u_dev, c->r, c->part);
       SSH_CHECK(hipGetLastError());
-      if (pre) {
-        rc = fph::precond_apply_dot(c->pc, FPH_F64, nrhs, c->r, c->z, c->part2, stream);
-        if (rc != FPH_OK) return rc;
-      }
+      rc = precondition();
+      if (rc != FPH_OK) return rc;
       if (!fused || k + 1 == chunk) {  // the fused launch of the next step does it otherwise
         hipLaunchKernelGGL(k_cg_scalar, dim3(nrhs), dim3(256), 0, s, 2, kXrBlocks, nbz, (const double*)c->part,
                            p2, sa);

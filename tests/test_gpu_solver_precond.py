@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from oracle import lattice as OL
+from oracle import precond as OP
 from paper_2203_01291_amd.solver import FermionSolver
 
 pytestmark = pytest.mark.gpu
@@ -37,3 +38,118 @@ def test_matrices_by_right_hand_sides(L, Ltau, a, nrhs, matrices, prec):
     u, st = s.solve(b, **how)
     assert all(v["iters"] == 1 for v in st)
     assert torch.equal(u, series) == (prec not in matrices)
+
+
+# One iteration's iterate over its norm, per right-hand side.
+def _direction(solver, b, prec, **kw):
+    u, st = solver.solve(b, tol=1e-30, maxiter=1, max_outer=1, precond=True, prec=prec, **kw)
+    assert all(v["iters"] == 1 for v in st)
+    u = u.cpu().numpy()
+    return u / np.sqrt((u * u).sum((1, 2), keepdims=True))
+
+
+def _close(got, b, pcs, prec):
+    for r, pc in enumerate(pcs):
+        ref = pc.apply_FFt(b[r])
+        ref /= np.sqrt((ref * ref).sum())
+        # rounding of a series of a few tens of terms in each precision, as for a single apply
+        assert np.max(np.abs(got[r] - ref)) < (1e-12 if prec == "f64" else 1e-5) * np.max(np.abs(ref)), r
+
+
+# A shared field (series, matrices where they gain), a field per right-hand side (series only) and another
+# shared field after it, whose solve must not meet a matrix of an earlier one.  In one launch: one wave per
+# frequency with and without matrices (L = 4, 6, 8), several frequencies per workgroup (L = 22), Ltau / 2
+# odd (L = 10).  In slots: every form of the series kernel, with and without matrices.
+@pytest.mark.parametrize("L,Ltau", [(4, 2), (4, 100), (4, 128), (6, 56), (8, 32), (10, 18), (22, 4),
+                                    (8, 100), (10, 160), (16, 80), (20, 60), (24, 40), (30, 40), (32, 40), (34, 8),
+                                    (48, 6)])
+@pytest.mark.parametrize("prec", ["f64", "f32_refined"])
+def test_direction_of_a_solve(L, Ltau, prec):
+    lat = OL.Lattice(L, Ltau, 0.1, 1.0, -0.1, 1.1)
+    rng = np.random.default_rng(11 * L + Ltau)
+    xs = rng.standard_normal((2, Ltau, lat.N)) * np.array([1.0, 0.5])[:, None, None]
+    b = rng.standard_normal((2, Ltau, lat.N))
+    C = OL.sparse_C(lat).tocsr()
+    pcs = [OP.Preconditioner(lat, x, 1.0, 1.0, C=C) for x in xs]
+    xg, bg = torch.from_numpy(xs).cuda(), torch.from_numpy(b).cuda()
+    s = _solver(lat, 2)
+    s.set_field(xg[0])
+    _close(_direction(s, bg[:1].contiguous(), prec), b, pcs[:1], prec)
+    _close(_direction(s, bg, prec), b, pcs[:1] * 2, prec)
+    s.set_fields(xg)
+    _close(_direction(s, bg, prec), b, pcs, prec)
+    s.set_field(xg[1])
+    _close(_direction(s, bg, prec), b, pcs[1:] * 2, prec)
+
+
+# Solves captured with and without the field, replayed after eager changes of it, against eager solves of
+# handles that never met another field.
+@pytest.mark.parametrize("prec", ["f64", "f32_refined"])
+def test_direction_under_capture(prec):
+    lat = OL.Lattice(16, 80, 0.1, 1.0, 0.0, 1.0)
+    rng = np.random.default_rng(3)
+    xs = [torch.from_numpy(c * rng.standard_normal((lat.Ltau, lat.N))).cuda() for c in (1.0, 0.4, 1.3)]
+    b = torch.from_numpy(rng.standard_normal((1, lat.Ltau, lat.N))).cuda()
+    how = dict(tol=1e-30, maxiter=1, max_outer=1, precond=True, prec=prec)
+    want = []
+    for x in xs:
+        s = _solver(lat, 1)
+        s.set_field(x)
+        want.append(s.solve(b, **how)[0])
+    s = _solver(lat, 1)
+    x, u = xs[0].clone(), torch.zeros_like(b)
+    s.set_field(x)
+    st = torch.empty(4, dtype=torch.float64, device="cuda")
+    s.solve_async(b, u, stats=st, zero_guess=True, **how)
+    torch.cuda.synchronize()
+    solve_only, both = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(solve_only):
+        s.solve_async(b, u, stats=st, zero_guess=True, **how)
+    with torch.cuda.graph(both):
+        s.set_field(x)
+        s.solve_async(b, u, stats=st, zero_guess=True, **how)
+
+    def same(a, k):  # series or matrix: the same operator to rounding
+        assert float((a - want[k]).norm() / want[k].norm()) < (1e-12 if prec == "f64" else 1e-5)
+
+    for k in (1, 2, 0, 0, 2):
+        s.set_field(xs[k])
+        solve_only.replay()
+        same(u, k)
+        same(s.solve(b, **how)[0], k)
+        x.copy_(xs[(k + 1) % 3])
+        both.replay()
+        same(u, (k + 1) % 3)
+        same(s.solve(b, **how)[0], (k + 1) % 3)
+
+
+# The SSH solve takes the adiabatic preconditioner of its on-site factor.
+@pytest.mark.parametrize("L,Ltau,nrhs", [(6, 56, 1), (16, 80, 2), (32, 40, 1)])
+@pytest.mark.parametrize("prec", ["f64", "f32_refined"])
+def test_direction_of_an_ssh_solve(L, Ltau, nrhs, prec):
+    from paper_2203_01291_amd.ssh import SSHSolver
+    lat = OL.Lattice(L, Ltau, 0.1, 1.0, -0.1, 0.9)
+    rng = np.random.default_rng(L)
+    x = 0.6 * rng.standard_normal((Ltau, lat.N))
+    b = rng.standard_normal((nrhs, Ltau, lat.N))
+    s = SSHSolver(L, Ltau, 0.1, 1.0, -0.1, 0.9, 0.2, max_rhs=nrhs)
+    s.attach_preconditioner(_solver(lat, nrhs), 1.0, 1.0)
+    s.set_field(torch.from_numpy(x).cuda())
+    pc = OP.Preconditioner(lat, x, 1.0, 1.0, C=OL.sparse_C(lat).tocsr())
+    _close(_direction(s, torch.from_numpy(b).cuda(), prec), b, [pc] * nrhs, prec)
+
+
+# An apply of its own is a function of the field and its input: the same bits before and after solves,
+# which use matrices.
+@pytest.mark.parametrize("L,Ltau", [(6, 56), (16, 80), (32, 60)])
+def test_apply_does_not_depend_on_solves(L, Ltau):
+    lat = OL.Lattice(L, Ltau, 0.1, 1.0, 0.0, 1.0)
+    rng = np.random.default_rng(L)
+    v = torch.from_numpy(rng.standard_normal((1, Ltau, lat.N))).cuda()
+    s = _solver(lat, 1)
+    s.set_field(torch.from_numpy(rng.standard_normal((Ltau, lat.N))).cuda())
+    before = [s.precond(w, "FFT") for w in (v, v.float())]
+    for prec in ("f64", "f32_refined"):
+        s.solve(v, tol=1e-2, precond=True, prec=prec)
+    for w, ref in zip((v, v.float()), before):
+        assert torch.equal(s.precond(w, "FFT"), ref)
