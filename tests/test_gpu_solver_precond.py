@@ -123,6 +123,30 @@ def test_direction_under_capture(prec):
         same(s.solve(b, **how)[0], (k + 1) % 3)
 
 
+# In the workgroups of a batch, at the shapes of the tests of whole solves.
+@pytest.mark.parametrize("shapes", [[(4, 6, 2), (6, 8, 1)], [(10, 42, 2), (12, 40, 1), (8, 100, 1)],
+                                    [(24, 60, 1), (16, 32, 2)], [(32, 20, 1), (22, 24, 1)], [(4, 20, 1100)]])
+@pytest.mark.parametrize("tune", [False, True])
+def test_direction_of_a_batch(shapes, tune):
+    from paper_2203_01291_amd.solver import FermionBatch
+    systems, host = [], []
+    for n, (L, Ltau, nrhs) in enumerate(shapes):
+        lat = OL.Lattice(L, Ltau, 0.1, 1.0, 0.1, 1.0)
+        rng = np.random.default_rng(17 * n + L)
+        x = rng.standard_normal((Ltau, lat.N))
+        b = rng.standard_normal((nrhs, Ltau, lat.N))
+        systems.append((lat, torch.from_numpy(x).cuda(), torch.from_numpy(b).cuda()))
+        host.append((b, OP.Preconditioner(lat, x, 1.0, 1.0, C=OL.sparse_C(lat).tocsr())))
+    batch = FermionBatch(systems)
+    if tune:
+        batch.tune(tol=1e-30, maxiter=1, precond=True)
+    stats = batch.solve(tol=1e-30, maxiter=1, precond=True)
+    assert all(st["iters"] == 1 for st in stats)
+    for (b, pc), u in zip(host, batch.u):
+        u = u.cpu().numpy()[:3]
+        _close(u / np.sqrt((u * u).sum((1, 2), keepdims=True)), b, [pc] * len(u), "f32_refined")
+
+
 # The SSH solve takes the adiabatic preconditioner of its on-site factor.
 @pytest.mark.parametrize("L,Ltau,nrhs", [(6, 56, 1), (16, 80, 2), (32, 40, 1)])
 @pytest.mark.parametrize("prec", ["f64", "f32_refined"])
