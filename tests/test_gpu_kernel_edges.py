@@ -277,3 +277,48 @@ def test_precond_solve_update(L, Ltau, prec):
     res = b - OL.apply_MT(lat, x, OL.apply_M(lat, x, u.cpu().numpy(), C), C)
     for r in range(3):
         assert stats[r]["status"] == 1 and np.linalg.norm(res[r]) <= 1.1e-11 * np.linalg.norm(b[r])
+
+
+# Zero, healthy and non-finite right-hand sides side by side, the iteration cap and a warm start, in the
+# launch sequence of larger systems: with matrices (L = 16), the split series (L = 18), the unsplit (L = 34).
+@pytest.mark.parametrize("L,Ltau", [(16, 40), (18, 40), (34, 10)])
+@pytest.mark.parametrize("prec", ["f64", "f32_refined"])
+@pytest.mark.parametrize("precond", [False, True])
+def test_slot_edge_cases(L, Ltau, prec, precond):
+    lat = OL.Lattice(L, Ltau, 0.1, 1.0, 0.1, 1.0)
+    rng = np.random.default_rng(L)
+    x = rng.standard_normal((Ltau, lat.N))
+    b = rng.standard_normal((4, Ltau, lat.N))
+    b[0] = 0.0
+    C = OL.sparse_C(lat).tocsr()
+    s = _solver(lat, 4)
+    s.set_field(torch.from_numpy(x).cuda())
+    how = dict(prec=prec, precond=precond)
+
+    def solved(u, st, r):
+        un = u[r].cpu().numpy()
+        res = b[r] - OL.apply_MT(lat, x, OL.apply_M(lat, x, un, C), C)
+        assert st[r]["status"] == 1 and np.linalg.norm(res) <= 1.1e-11 * np.linalg.norm(b[r])
+
+    bg = torch.from_numpy(b).cuda()
+    u, st = s.solve(bg, u=torch.ones_like(bg), tol=1e-11, **how)
+    assert not u[0].any() and st[0]["status"] == 1
+    for r in (1, 2, 3):
+        solved(u, st, r)
+    # the cap: every right-hand side stops there with a finite iterate that has moved
+    for maxiter in (1, 2, 5):
+        v, st = s.solve(bg[1:].contiguous(), tol=1e-14, maxiter=maxiter, **how)
+        assert all(q["status"] == 2 and q["iters"] == maxiter for q in st)
+        assert bool(torch.isfinite(v).all()) and all(bool(v[r].any()) for r in range(3))
+    # from the solution no iteration is left
+    v, st = s.solve(bg, u=u.clone(), tol=1e-10, **how)
+    assert all(q["status"] == 1 and q["iters"] <= 1 for q in st)
+    # a non-finite entry is reported and stays with its right-hand side
+    for bad in (np.nan, np.inf):
+        bn = bg.clone()
+        bn[2, Ltau // 2, 3] = bad
+        v, st = s.solve(bn, tol=1e-11, **how)
+        assert st[2]["status"] & 8 and not st[2]["status"] & 1
+        assert not v[0].any() and st[0]["status"] == 1
+        for r in (1, 3):
+            solved(v, st, r)
