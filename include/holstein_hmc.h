@@ -159,7 +159,8 @@ const char* fph_strerror(int code);
 /* Create a handle for one lattice and up to max_rhs right-hand sides;
  * allocates all device workspace once (Sec. II C defines the parameters),
  * among it up to 100 MB for block matrices of the preconditioner where
- * N <= 1024; the first preconditioned solve after fph_set_field fills them.
+ * N <= 1024 (left out where that much is not free; solves then run the
+ * series); preconditioned solves after fph_set_field fill what they read.
  * Returns FPH_E_LATTICE for an unsupported lattice, FPH_E_NRHS for
  * max_rhs < 1.  On error *h is set to NULL. */
 int fph_create(fph_handle_t* h, const fph_lattice_t* lat, int32_t max_rhs);

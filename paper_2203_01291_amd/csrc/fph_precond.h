@@ -1794,22 +1794,26 @@ inline hipError_t pc_create(PcTables* pc, const Geom& g, int max_rhs) {
   PCALLOC(pc->np, (size_t)max_rhs * g.Ltau * sizeof(int));
   PCALLOC(pc->coef64, (size_t)max_rhs * H * kNPMax * sizeof(double2));
   PCALLOC(pc->coef32, (size_t)max_rhs * H * kNPMax * sizeof(float2));
-  // Matrices of the longest blocks: slices of up to 1 024 sites (above, one
-  // would be read slower than its series runs), up to 16 blocks and 100 MB; not
-  // for larger slices of a system that one workgroup solves (bpc_series takes
-  // them up to 36 sites).
-  const size_t nn = (size_t)g.N * g.N;
-  pc->kdmax = g.N <= 1024 && (g.d > 2048 || g.N <= 36)
-                  ? (int)std::min<size_t>({16, (size_t)H - 1, (100u << 20) / (nn * 24)})
-                  : 0;
-  if (pc->kdmax > 0) {
-    PCALLOC(pc->dense64, pc->kdmax * nn * (sizeof(double2) + sizeof(float2)));
-    pc->dense32 = reinterpret_cast<float2*>(pc->dense64 + pc->kdmax * nn);
-  }
   PCALLOC(pc->Z, (size_t)max_rhs * H * g.N * sizeof(double2));
   PCALLOC(pc->Z2, (size_t)max_rhs * H * g.N * sizeof(double2));
 #undef PCALLOC
   if (e != hipSuccess) return e;
+  // Matrices of the longest blocks: slices of up to 1 024 sites (above, one
+  // would be read slower than its series runs), up to 16 blocks and 100 MB; not
+  // for larger slices of a system that one workgroup solves (bpc_series takes
+  // them up to 36 sites).  They only make solves faster: where there is no room
+  // for them the series run throughout.
+  const size_t nn = (size_t)g.N * g.N;
+  pc->kdmax = g.N <= 1024 && (g.d > 2048 || g.N <= 36)
+                  ? (int)std::min<size_t>({16, (size_t)H - 1, (100u << 20) / (nn * 24)})
+                  : 0;
+  if (pc->kdmax > 0 &&
+      hipMalloc((void**)&pc->dense64, pc->kdmax * nn * (sizeof(double2) + sizeof(float2))) != hipSuccess) {
+    (void)hipGetLastError();
+    pc->dense64 = nullptr;
+    pc->kdmax = 0;
+  }
+  if (pc->kdmax > 0) pc->dense32 = reinterpret_cast<float2*>(pc->dense64 + pc->kdmax * nn);
   hipLaunchKernelGGL(k_pc_twiddles, dim3((H + nF + 255) / 256), dim3(256), 0, 0, H, pc->H1,
                      pc->H2, g.Ltau, pc->tw64, pc->W64, pc->F64, pc->tw32, pc->W32, pc->F32);
   return hipGetLastError();

@@ -86,3 +86,23 @@ out["fields"] = solve(h, F64, 4)
 """)
     assert out == {"unread": [], "read": ["f"], "many": [], "f64": ["d"], "again": [], "fewer": ["d"],
                    "f32": ["f"], "captured": ["d"], "fields": []}
+
+
+# A handle needs no room for block matrices: refused, it runs the series.
+def test_no_room_for_matrices(record):
+    out = record("""
+def built(h):
+    names()
+    lib.fph_set_field(h, P, 1.0, 1.0, None)
+    assert lib.pcg_solve(h, 1, P, P, opts(_lib.FPH_F64), P, None) == 0
+    return any("k_pc_dense" in k for k in names())
+out["room"] = built(handle(16, 16, 1))
+rec.rec_limit(ctypes.c_size_t(1 << 20))  # the matrices are 11 MB, all else is smaller
+h = handle(16, 16, 1)
+out["created"] = isinstance(h, ctypes.c_void_p)
+out["built"] = built(h)
+out["free"] = lib.fph_destroy(h)
+rec.rec_limit(ctypes.c_size_t(1 << 10))
+out["refused"] = handle(16, 16, 1)
+""")
+    assert out == {"room": True, "created": True, "built": False, "free": 0, "refused": -100}
