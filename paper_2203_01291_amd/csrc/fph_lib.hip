@@ -1023,7 +1023,7 @@ struct fph_batch_s {
   float2 *tw32, *W32, *F32;
   int nt, ms, per_cu;         // launch shape
   bool tuned;                 // chosen by fph_batch_tune; else by batch_shape
-  long dmax;                  // unknowns of the largest item
+  long dmax, dsum;            // unknowns of the largest item, and of all
   int num_cu;
   int qmax;
   hipStream_t cap;            // capture stream
@@ -1125,25 +1125,31 @@ __global__ void k_copy_batch_stats(int n, const BatchStat* __restrict__ in,
 }
 
 // Launch shape of a batch that was not tuned.  An item is a chain of short
-// phases with workgroup barriers; until items queue up several deep, its own
-// time counts and more waves shorten it.  Without the preconditioner 512
-// threads win throughout (ms, 256 / 512 / 1 024 threads: 288 items of L 8-24,
-// Ltau 100: 125 / 60 / 59; 768 items: 146 / 102 / 130; 40 of L 4-6, Ltau 40:
-// 2.0 / 1.7 / 3.2; 2 560: 421 / 376 / -).  With it the transforms and series
-// feed 1 024 threads unless every item is small (288 items: 65 / 44 / 33; 768:
-// 82 / 70 / 65; 18 of up to 15 360 unknowns: 6.7 / 5.3 / 5.0; 20 of 4 000: 2.0 /
-// 1.8 / 2.2) or many items share a compute unit (2 560: 212 with 256).
+// phases with workgroup barriers: while a compute unit has one item, more waves
+// shorten it; once it has several (as many unknowns as `num_cu` of the largest
+// items), they hide each other's waits and fewer waves per item waste less at
+// its barriers.  Without the preconditioner (ms, 256 / 512 threads) 256 items of
+// L = 8, Ltau 40: 1.44 / 1.29, 300: 1.60 / 2.33, 1 200: 4.54 / 5.97; 300 of L = 4,
+// Ltau 40: 0.88 / 1.39; above some 5 000 unknowns 512 gain with both (700 of L = 16,
+// Ltau 60: 21.6 / 18.6; 288 of L 8 to 24, Ltau 100: 58.5 / 28.2).  With it (256 / 512
+// / 1 024) 64 items of L = 8, Ltau 40: 0.74 / 0.62 / 0.69, 300: 0.86 / 1.15 / 1.42; 300
+// of L = 12, Ltau 60: 3.2 / 4.7 / 5.5; slices of more than 64 plaquettes feed 1 024
+// (64 of L = 32, Ltau 8: 1.00 / 1.00 / 0.63, 700: 2.39 / 3.14 / 2.14; 108 of L 8 to
+// 24, Ltau 100: 36.7 / 25.0 / 16.9) until many items share a unit (2 560: 212 with
+// 256).
 void batch_shape(fph_batch_s* b, const BatchRunCfg& c) {
+  const bool several = b->dsum > b->num_cu * b->dmax, small = b->qmax <= 64;
   b->ms = 1;
-  if (!c.pre || b->dmax <= 8192) {
-    b->nt = 512;
-    b->per_cu = 2;
+  b->per_cu = 2;
+  if (!c.pre) {
+    b->nt = several && b->dmax <= 5120 ? 256 : 512;
+  } else if (small && (several || b->dmax <= 8192)) {
+    b->nt = several ? 256 : 512;
   } else if (b->nitems <= 4 * b->num_cu) {
     b->nt = 1024;
     b->per_cu = 1;
   } else {
     b->nt = 256;
-    b->per_cu = 2;
   }
 }
 
@@ -1188,7 +1194,7 @@ int fph_batch_create(fph_batch_t* out, const fph_system_t* sys, int32_t nsys) {
   if (nsys < 1) return FPH_E_ARG;
   long etot = 0, wtot = 0, ntot = 0, nptot = 0, ctot = 0, twtot = 0, ftot = 0;
   int nitems = 0, qmax = 1;
-  long dmax = 0;
+  long dmax = 0, dsum = 0;
   for (int k = 0; k < nsys; ++k) {
     const fph_lattice_t& L = sys[k].lat;
     if (sys[k].x_dev == nullptr || sys[k].b_dev == nullptr || sys[k].u_dev == nullptr)
@@ -1211,12 +1217,14 @@ int fph_batch_create(fph_batch_t* out, const fph_system_t* sys, int32_t nsys) {
     nitems += sys[k].nrhs;
     qmax = std::max(qmax, N / 4);
     dmax = std::max(dmax, d);
+    dsum += d * sys[k].nrhs;
   }
   fph_batch_s* b = new fph_batch_s();
   b->nsys = nsys;
   b->nitems = nitems;
   b->qmax = qmax;
   b->dmax = dmax;
+  b->dsum = dsum;
   b->sys.assign(sys, sys + nsys);
   b->have_graph = false;
   b->tuned = false;

@@ -106,3 +106,32 @@ rec.rec_limit(ctypes.c_size_t(1 << 10))
 out["refused"] = handle(16, 16, 1)
 """)
     assert out == {"room": True, "created": True, "built": False, "free": 0, "refused": -100}
+
+
+# Threads of an untuned batch: more while a compute unit (256 of them) has one item, fewer once it has
+# several, by unknowns and not by items.
+def test_batch_shapes(record):
+    out = record("""
+def threads(*systems):
+    arr = (_lib.System * len(systems))(*[_lib.System(lattice(L, Ltau), P, n, P, P) for L, Ltau, n in systems])
+    b, got = ctypes.c_void_p(), []
+    assert lib.fph_batch_create(ctypes.byref(b), arr, len(systems)) == 0
+    for precond in (0, 1):
+        rec.rec_reset()
+        assert lib.fph_batch_solve(b, opts(_lib.FPH_F32_REFINED, precond), None, None) == 0
+        got += [rec.rec_threads(i) for i in range(rec.rec_count()) if b"k_batch_solve" in rec.rec_name(i)]
+    lib.fph_batch_destroy(b)
+    return got
+out["few small"] = threads((4, 40, 256))
+out["many small"] = threads((4, 40, 257))
+out["largest of the small"] = threads((16, 20, 300))
+out["above"] = threads((8, 100, 300))
+out["large"] = threads((16, 60, 100))
+out["many large"] = threads((16, 60, 300))
+out["wide"] = threads((32, 8, 16))
+out["many wide"] = threads((32, 8, 1200))
+out["uneven"] = threads((4, 40, 700), (16, 40, 20))
+""")
+    assert out == {"few small": [512, 512], "many small": [256, 256], "largest of the small": [256, 256],
+                   "above": [512, 256], "large": [512, 1024], "many large": [512, 256], "wide": [512, 1024],
+                   "many wide": [512, 256], "uneven": [512, 1024]}
