@@ -7,7 +7,7 @@
 // transform along tau per site (k_fft_t).  Both are mixed-radix Stockham
 // FFTs in LDS: radices 8, 5, 4, 3 and 2 as register butterflies, larger prime
 // factors as direct sums, so 5 n log2 n operations per line instead of the
-// n (P + Q) of a two-factor direct form.
+// n (P + Q) of a two-factor direct form; short sides are direct (k_dft_xy).
 //  * Correlations need only the real part of the last inverse transform, and
 //    for complex sequences z = a1 + i a2, w = b1 + i b2
 //      Re sum_i conj(z_i) w_{i+D} = (a1 * b1)_D + (a2 * b2)_D,
@@ -44,12 +44,14 @@ __device__ __forceinline__ double2 cfma(double2 a, double2 b, double2 c) {  // c
 }
 __device__ __forceinline__ double2 conjd(double2 a) { return make_double2(a.x, -a.y); }
 
-// tw[m] = exp(-2 pi i m / n), m < n.
+// tw[m] = exp(-2 pi i m / n), m < n, to the last bits: the rounding of 2 m / n,
+// which its sine and cosine would carry on, is put right to first order.
 __global__ void __launch_bounds__(256) k_meas_twiddles(int n, double2* __restrict__ tw) {
   for (int m = blockIdx.x * 256 + threadIdx.x; m < n; m += gridDim.x * 256) {
     double s, c;
-    sincospi(2.0 * m / n, &s, &c);
-    tw[m] = make_double2(c, -s);
+    const double t = 2.0 * m / n, e = M_PI * (fma(-t, (double)n, 2.0 * m) / n);
+    sincospi(t, &s, &c);
+    tw[m] = make_double2(fma(-s, e, c), -fma(c, e, s));
   }
 }
 
@@ -222,9 +224,10 @@ __device__ __forceinline__ void fft_stage_any(int R, int n, int Ns, unsigned mNs
     int s, j;
     split(e - r * items, s, j);
     const int k = j - udiv(j, mNs) * Ns;
-    const int step = (k * ts + r * nb) % n;
+    const int step = k * ts + r * nb;  // (below n)
     double2 acc = make_double2(0.0, 0.0);
     int m = 0;
+#pragma unroll 4
     for (int q = 0; q < R; ++q) {
       acc = cfma(ld(j + q * nb, s), tw[m], acc);
       m += step;
@@ -244,6 +247,18 @@ __device__ __forceinline__ void fft_stage_sel(int R, int n, int Ns, unsigned mNs
     case 3: fft_stage<3, INV, NT>(n, Ns, mNs, items, tw, split, ld, st); break;
     case 2: fft_stage<2, INV, NT>(n, Ns, mNs, items, tw, split, ld, st); break;
     default: fft_stage_any<NT>(R, n, Ns, mNs, items, tw, split, ld, st); break;
+  }
+}
+
+// The first stage of a line of even length (make_plan starts with 8, 4 or 2): its
+// loads from memory sit in a stage of their own, one kind of load per instance,
+// so that a butterfly issues all of them before it waits for the first.
+template <bool INV, int NT, class Split, class Ld, class St>
+__device__ __forceinline__ void fft_first(int R, int n, int items, const Split& split, const Ld& ld, const St& st) {
+  switch (R) {
+    case 8: fft_stage<8, INV, NT>(n, 1, 0u, items, nullptr, split, ld, st); break;
+    case 4: fft_stage<4, INV, NT>(n, 1, 0u, items, nullptr, split, ld, st); break;
+    default: fft_stage<2, INV, NT>(n, 1, 0u, items, nullptr, split, ld, st); break;
   }
 }
 
@@ -288,49 +303,125 @@ k_fft_xy(int L, int N, FftPlan py, FftPlan px, XyArgs A, const double2* __restri
   const XyJob jb = A.job[logical - slice * A.njob];
   const long base = (long)slice * N;
   for (int e = threadIdx.x; e < L; e += NT) tw[e] = INV ? conjd(twL[e]) : twL[e];
-  int cur = 0;
-  for (int pass = 0; pass < 2; ++pass) {  // 0: along y, 1: along x
-    const int ns = pass ? px.ns : py.ns;
-    const int sn = pass ? 1 : LP, sb = pass ? LP : 1;
-    int Ns = 1;
-    for (int i = 0; i < ns; ++i) {
-      const int R = pass ? px.R[i] : py.R[i];
-      const bool first = pass == 0 && i == 0, last = pass == 1 && i == ns - 1;
-      const double2* src = buf + cur * nbuf;
-      double2* dst = buf + (cur ^ 1) * nbuf;
-      const unsigned mn = px.mn, mnb = px.mNb[i];  // (mnb for the last stage, along x)
-      const int nb = L / R;
-      auto split = [&](int e, int& s, int& j) {
-        if (last) {
-          s = udiv(e, mnb);
-          j = e - s * nb;
-        } else {
-          j = udiv(e, mn);
-          s = e - j * L;
-        }
-      };
-      auto ld = [&](int k, int s) {
-        if (!first) return src[k * sn + s * sb];
-        const long o = base + (long)k * L + s;  // row y = k, column x = s
-        if (jb.in) return jb.in[o];
-        double re = jb.a[o], im = 0.0;
-        if (jb.b) re *= jb.b[o];
-        if (jb.c) im = jb.d ? jb.c[o] * jb.d[o] : jb.c[o];
-        return make_double2(re, im);
-      };
-      auto st = [&](int k, int s, double2 v) {
-        if (!last) {
-          dst[k * sn + s * sb] = v;
-          return;
-        }
-        const long o = base + (long)s * L + k;  // row y = s, column x = k
-        if (jb.outr) jb.outr[o] = A.scale * v.x;
-        else jb.out[o] = v;
-      };
-      if (!first || Ns > 1) __syncthreads();
-      fft_stage_sel<INV, NT>(R, L, Ns, pass ? px.mNs[i] : py.mNs[i], nb * L, tw, split, ld, st);
-      Ns *= R;
-      cur ^= 1;
+  auto lanes_x = [&](int e, int& s, int& j) {
+    j = udiv(e, px.mn);
+    s = e - j * L;
+  };
+  {  // along y, from memory: row y = k, column x = s
+    const int R = py.R[0], items = L / R * L;
+    auto st = [&](int k, int s, double2 v) { buf[nbuf + k * LP + s] = v; };
+    auto at = [&](int k, int s) { return base + (long)k * L + s; };
+    auto first = [&](const auto& ld) {
+      fft_first<INV, NT>(R, L, items, lanes_x, [&](int k, int s) { return ld(at(k, s)); }, st);
+    };
+    if (jb.in) first([&](long o) { return jb.in[o]; });
+    else if (jb.b && jb.c) first([&](long o) { return make_double2(jb.a[o] * jb.b[o], jb.c[o] * jb.d[o]); });
+    else if (jb.b) first([&](long o) { return make_double2(jb.a[o] * jb.b[o], 0.0); });
+    else if (jb.c) first([&](long o) { return make_double2(jb.a[o], jb.c[o]); });
+    else first([&](long o) { return make_double2(jb.a[o], 0.0); });
+  }
+  int cur = 1, Ns = py.R[0];
+  for (int t = 1; t < py.ns + px.ns - 1; ++t) {  // along y, then along x
+    const bool x = t >= py.ns;
+    const int i = x ? t - py.ns : t, sn = x ? 1 : LP, sb = x ? LP : 1;
+    const int R = x ? px.R[i] : py.R[i];
+    if (i == 0) Ns = 1;
+    const double2* src = buf + cur * nbuf;
+    double2* dst = buf + (cur ^ 1) * nbuf;
+    __syncthreads();
+    fft_stage_sel<INV, NT>(
+        R, L, Ns, x ? px.mNs[i] : py.mNs[i], L / R * L, tw, lanes_x,
+        [&](int k, int s) { return src[k * sn + s * sb]; }, [&](int k, int s, double2 v) { dst[k * sn + s * sb] = v; });
+    Ns *= R;
+    cur ^= 1;
+  }
+  {  // the last along x, to memory: row y = s, column x = k, lanes along its outputs
+    const int i = px.ns - 1, R = px.R[i], nb = L / R;
+    if (i == 0) Ns = 1;
+    const double2* src = buf + cur * nbuf;
+    auto split = [&](int e, int& s, int& j) {
+      s = udiv(e, px.mNb[i]);
+      j = e - s * nb;
+    };
+    auto ld = [&](int k, int s) { return src[k + s * LP]; };
+    auto last = [&](const auto& put) {
+      fft_stage_sel<INV, NT>(R, L, Ns, px.mNs[i], nb * L, tw, split, ld,
+                             [&](int k, int s, double2 v) { put(base + (long)s * L + k, v); });
+    };
+    __syncthreads();
+    if (jb.outr) last([&](long o, double2 v) { jb.outr[o] = A.scale * v.x; });
+    else last([&](long o, double2 v) { jb.out[o] = v; });
+  }
+}
+
+// The same by direct DFTs of length L in three phases, for short sides (the rule
+// stands with launch_xy).  A small transform is a chain of phases (a barrier, an
+// LDS round trip, the fetch of the stage's instructions: 0.5 to 0.8 us), and a
+// side of 2 p is two stages per axis with a direct sum over p in it anyway.  One
+// grid of 40 slices, L = 6 and 22: 3.6 and 5.2 us; as FFTs 5.6 and 7.9.
+template <bool INV, int NT>
+__global__ void __launch_bounds__(NT)
+k_dft_xy(int L, int N, XyArgs A, const double2* __restrict__ twL) {
+  extern __shared__ double2 sh[];
+  double2* tw = sh;
+  double2* U = sh + L;  // [y][x]
+  double2* B = U + N;   // [y][kx]
+  const int slice = blockIdx.x / A.njob;
+  const XyJob jb = A.job[blockIdx.x - slice * A.njob];
+  const long base = (long)slice * N;
+  for (int e = threadIdx.x; e < L; e += NT) tw[e] = INV ? conjd(twL[e]) : twL[e];
+  auto fill = [&](const auto& ld) {
+    for (int e = threadIdx.x; e < N; e += NT) U[e] = ld(base + e);
+  };
+  if (jb.in) fill([&](long o) { return jb.in[o]; });
+  else if (jb.b) fill([&](long o) { return make_double2(jb.a[o] * jb.b[o], jb.c ? jb.c[o] * jb.d[o] : 0.0); });
+  else fill([&](long o) { return make_double2(jb.a[o], jb.c ? jb.c[o] : 0.0); });
+  __syncthreads();
+  // Entries x and L - x of a line meet outputs k and L - k with the same cosine
+  // and sine (w = c + i t): with p, q their sum and difference,
+  // X_k, X_{L-k} = v_0 + (-1)^k v_{L/2} + sum c p +- i sum t q, odd and even x
+  // summed apart (a shorter chain, and as small an error as the FFT's).
+  const int h = L / 2;
+  auto pair = [&](const double2* v, int stride, int k, double2& lo, double2& hi) {
+    double2 C[2], S[2];
+    C[0] = C[1] = S[0] = S[1] = make_double2(0.0, 0.0);
+    int m = 0;
+    for (int x = 1; x < h; x += 2) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (x + i == h) break;
+        m += k;
+        if (m >= L) m -= L;
+        const double2 w = tw[m], f = v[(x + i) * stride], g = v[(L - x - i) * stride];
+        const double2 p = cadd(f, g), q = csub(f, g);
+        C[i] = make_double2(fma(w.x, p.x, C[i].x), fma(w.x, p.y, C[i].y));
+        S[i] = make_double2(fma(w.y, q.x, S[i].x), fma(w.y, q.y, S[i].y));
+      }
+    }
+    const double2 v0 = v[0], vh = v[h * stride];
+    const double2 c = cadd(k & 1 ? csub(v0, vh) : cadd(v0, vh), cadd(C[0], C[1])), t = cadd(S[0], S[1]);
+    lo = make_double2(c.x - t.y, c.y + t.x);
+    hi = make_double2(c.x + t.y, c.y - t.x);
+  };
+  for (int e = threadIdx.x; e < (h + 1) * L; e += NT) {  // along x
+    const int y = e / (h + 1), k = e - y * (h + 1);
+    double2 lo, hi;
+    pair(U + y * L, 1, k, lo, hi);
+    B[y * L + k] = lo;
+    if (k > 0) B[y * L + L - k] = hi;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < (h + 1) * L; e += NT) {  // along y
+    const int ky = e / L, k = e - ky * L;
+    double2 lo, hi;
+    pair(B + k, L, ky, lo, hi);
+    const long o = base + (long)ky * L + k, o2 = base + (long)(L - ky) * L + k;
+    if (jb.outr) {
+      jb.outr[o] = A.scale * lo.x;
+      if (ky > 0) jb.outr[o2] = A.scale * hi.x;
+    } else {
+      jb.out[o] = lo;
+      if (ky > 0) jb.out[o2] = hi;
     }
   }
 }
@@ -375,17 +466,22 @@ k_fft_t(int N, int ls, FftPlan pl, TArgs A, const double2* __restrict__ tw2) {
   };
   // Transform of `in`; returns the buffer that holds it ([tau][s]), after a barrier.
   auto transform = [&](const double2* in) {
-    int cur = 0, Ns = 1;
-    for (int i = 0; i < pl.ns; ++i) {
+    int cur = 1, Ns = pl.R[0];
+    {
+      const int items = (T / Ns) << ls;
+      auto put = [&](int k, int s, double2 v) { buf[nel + (k << ls) + s] = v; };
+      auto get = [&](int k, int s) { return in[(long)k * N + site0 + s]; };
+      if (!INV && A.twist)
+        fft_first<INV, kTNT>(Ns, T, items, split, [&](int k, int s) { return cmul(get(k, s), tw2[k]); }, put);
+      else
+        fft_first<INV, kTNT>(Ns, T, items, split, get, put);
+      __syncthreads();
+    }
+    for (int i = 1; i < pl.ns; ++i) {
       const int R = pl.R[i];
       const double2* src = buf + cur * nel;
       double2* dst = buf + (cur ^ 1) * nel;
-      auto ld = [&](int k, int s) {
-        if (i > 0) return src[(k << ls) + s];
-        double2 v = in[(long)k * N + site0 + s];
-        if (!INV && A.twist) v = cmul(v, tw2[k]);
-        return v;
-      };
+      auto ld = [&](int k, int s) { return src[(k << ls) + s]; };
       auto st = [&](int k, int s, double2 v) { dst[(k << ls) + s] = v; };
       fft_stage_sel<INV, kTNT>(R, T, Ns, pl.mNs[i], (T / R) << ls, tw, split, ld, st);
       __syncthreads();
@@ -469,7 +565,17 @@ namespace {
 // Threads of a space workgroup: one radix-4 or two radix-8 butterflies each.
 hipError_t launch_xy(const fph_meas_s* m, bool inv, const XyArgs& A, hipStream_t s) {
   const dim3 g(m->T * A.njob);
-  if (m->N <= 1024) {
+  // Direct sides: up to 22, and up to 38 where a prime factor above 5 is a stage of
+  // direct sums (us, direct / FFT, one grid of 40 and of 400 slices: L = 12 4.0 / 5.7
+  // and 4.5 / 5.6; 22 5.2 / 7.9 and 6.9 / 10.0; 38 10.5 / 13.5 and 16.7 / 23.3; but 24
+  // 5.4 / 5.9 and 7.5 / 7.3, eight grids of 400 18 / 17; 32 8.6 / 6.4 and 14.5 / 9.9).
+  // 512 threads where 256 would take the lines in two rounds.
+  if (m->L <= 22 || (m->L <= 38 && m->pX.R[m->pX.ns - 1] > 5)) {
+    const int nt = (m->L / 2 + 1) * m->L <= 256 ? 256 : 512;
+    auto k = nt == 256 ? (inv ? k_dft_xy<true, 256> : k_dft_xy<false, 256>)
+                       : (inv ? k_dft_xy<true, 512> : k_dft_xy<false, 512>);
+    hipLaunchKernelGGL(k, g, dim3(nt), m->lds_xy, s, m->L, m->N, A, (const double2*)m->twL);
+  } else if (m->N <= 1024) {
     auto k = inv ? k_fft_xy<true, 256> : k_fft_xy<false, 256>;
     hipLaunchKernelGGL(k, g, dim3(256), m->lds_xy, s, m->L, m->N, m->pY, m->pX, A, (const double2*)m->twL);
   } else {
@@ -585,6 +691,8 @@ int fph_meas_create(fph_meas_t* out, fph_handle_t h, void* stream) {
   {
     const void* fns[] = {(const void*)k_fft_xy<false, 256>,    (const void*)k_fft_xy<true, 256>,
                          (const void*)k_fft_xy<false, 512>,    (const void*)k_fft_xy<true, 512>,
+                         (const void*)k_dft_xy<false, 256>,    (const void*)k_dft_xy<true, 256>,
+                         (const void*)k_dft_xy<false, 512>,    (const void*)k_dft_xy<true, 512>,
                          (const void*)k_fft_t<false, T_PLAIN>, (const void*)k_fft_t<true, T_PLAIN>,
                          (const void*)k_fft_t<false, T_CROSS>, (const void*)k_fft_t<false, T_PREFIX>};
     for (const void* f : fns)

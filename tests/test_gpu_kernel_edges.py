@@ -322,3 +322,25 @@ def test_slot_edge_cases(L, Ltau, prec, precond):
         assert not v[0].any() and st[0]["status"] == 1
         for r in (1, 3):
             solved(v, st, r)
+
+
+# Sides on either line of the direct form (up to 22; 26, 28, 34 and 38 for their prime factors, not 24, 30,
+# 36 and 40), lines of one and two rounds of threads, every kind of input of a launch.
+@pytest.mark.parametrize("L,Ltau", [(4, 6), (6, 4), (12, 2), (16, 6), (20, 2), (22, 6), (24, 2), (26, 4), (28, 2),
+                                    (30, 4), (34, 2), (36, 2), (38, 4), (40, 2)])
+def test_direct_sides(L, Ltau):
+    from oracle import measure as OM
+    from paper_2203_01291_amd.measure import GreenMeasurement
+    lat = OL.Lattice(L, Ltau, 0.1, 1.0, 0.0, 1.0)
+    rng = np.random.default_rng(3 * L + Ltau)
+    m = GreenMeasurement(_solver(lat, 1))
+    z = rng.standard_normal((Ltau, L, L)) + 1j * rng.standard_normal((Ltau, L, L))
+    zg = torch.from_numpy(z.reshape(Ltau, -1)).cuda()
+    for inverse, ref in ((False, np.fft.fftn(z)), (True, np.fft.ifftn(z) * z.size)):
+        got = m.fft(zg, inverse=inverse).cpu().numpy().reshape(z.shape)
+        assert _relmax(got, ref) < 7e-15  # some 60 roundings on the way of a value
+    xi = rng.choice([-1.0, 1.0], size=(3, Ltau, lat.N))
+    gx = 0.5 * xi + 0.3 * rng.standard_normal(xi.shape)
+    a, b = torch.from_numpy(xi).cuda(), torch.from_numpy(gx).cuda()
+    assert _relmax(m.green_average(a, b).cpu().numpy(), OM.green_average_estimate(lat, xi, gx)) < 1e-12
+    assert _relmax(m.pair_products(a, b).cpu().numpy(), OM.pair_products_estimate(lat, xi, gx)) < 1e-12
