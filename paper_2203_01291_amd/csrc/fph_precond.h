@@ -108,8 +108,8 @@ __global__ void k_pc_twiddles(int H, int H1, int H2, int Ltau, double2* tw64, do
 
 // How many blocks of F F^T, longest series first, to apply as N x N matrices
 // (k_pc_dense, k_kpm_split) to n vectors.  A block's series is a chain of
-// 2 (N_P - 1) exchanges of 0.2 us each (0.3 in FP64 with more than 100
-// plaquettes), and the longest one left sets the kernel's time; the rows of the
+// 2 (N_P - 1) exchanges of 0.2 us each (0.3 in FP64 with more than 100 plaquettes),
+// and the longest one left sets the kernel's time; the rows of the
 // matrices run beside the series, one vector after the other, about 1 us each
 // and what reading the matrices takes at 6.7 MB per us.  N_P(0) is
 // large only at the lowest frequencies (its a1/phi term), so a few matrices
@@ -1861,7 +1861,9 @@ inline hipError_t pc_set_field(PcTables* pc, const Geom& g, const double* dbar64
 // Whether the series kernel is k_kpm_split (its rule stands with pc_kpm).
 template <typename T>
 bool pc_split(const PcTables* pc, const Geom& g, int nrhs) {
-  return g.Q <= 256 && (sizeof(T) == 8 || g.hL != 16 || (long)pc->H * nrhs <= 512);
+  const long blocks = (long)pc->H * nrhs;
+  if (g.hL == 16) return sizeof(T) == 8 || blocks <= 512;
+  return g.Q <= 128 || (g.Q <= 256 && blocks <= (sizeof(T) == 8 ? 512 : 256));
 }
 
 // The class whose matrices an apply of F F^T to nrhs vectors takes, or -1 where
@@ -2065,14 +2067,23 @@ hipError_t pc_kpm(const PcTables* pc, const Geom& g, const T* dbar, int op, int 
   // Split parts up to 256 plaquettes (8 waves); with 16 waves per block
   // (L = 40) the barrier costs more than the shorter steps give (26.2
   // against 24.2 us per FP32 F F^T at Ltau = 100, 30.7 against 28.7 in FP64).
-  // L = 32: each plaquette row is one 16-lane row of a wave (row form).  There
-  // the FP32 blocks of several right-hand sides fill the compute units, so
-  // past two blocks each, where issue and not the chain sets the time, the
-  // unsplit form needs fewer instructions (Ltau = 400: split 19.1 against
-  // 20.8 us for one right-hand side, 23.2 / 24.1 for two, 33.2 / 32.2 for
-  // four, 49.1 / 46.5 for ten); FP64 gains or ties throughout.
+  // The blocks of several right-hand sides fill the compute units: past one or
+  // two blocks each, where issue and not the chain sets the time, the unsplit
+  // form needs fewer instructions and, above 128 plaquettes, half the waves.
+  // L = 32 (each plaquette row one 16-lane row of a wave: row form), FP32, Ltau
+  // 400: split 19.1 against 20.8 us for one right-hand side, 23.2 / 24.1 for two,
+  // 33.2 / 32.2 for four, 49.1 / 46.5 for ten; FP64 gains or ties throughout.
+  // Solver iteration at L = 24, Ltau 100, series of 11 to 14 terms, split / unsplit,
+  // FP64: 200 blocks 37.3 / 36.7 us, 400 51.0 / 44.6, 800 79.5 / 63.4, 2 000 149 / 111;
+  // of up to 29 terms 47.3 / 47.6, 52.8 / 53.9, 60.9 / 61.7, 102 / 83 (and below 512
+  // blocks the split form has its matrices); FP32 23.9 / 23.8, 28.8 / 26.9, 37.2 /
+  // 31.1, 55.2 / 43.1 and 28.7 / 29.0, 32.5 / 32.4, 36.7 / 35.2, 47.8 / 43.8.  Up to
+  // 128 plaquettes the split form wins or ties but for short series (12 terms, L =
+  // 12, 1 280 blocks, FP64: 44.9 / 41.0; of 45 terms 47.0 / 52.8).
   if (!pc_split<T>(pc, g, nrhs)) {
     if (g.hL == 16) return pc_launch_kpm<T, 256, true>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
+    if (g.Q <= 192) return pc_launch_kpm<T, 192>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
+    if (g.Q <= 256) return pc_launch_kpm<T, 256>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
     if (g.Q <= 512) return pc_launch_kpm<T, 512>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
     return pc_launch_kpm<T, 1024>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
   }

@@ -177,3 +177,25 @@ def test_apply_does_not_depend_on_solves(L, Ltau):
         s.solve(v, tol=1e-2, precond=True, prec=prec)
     for w, ref in zip((v, v.float()), before):
         assert torch.equal(s.precond(w, "FFT"), ref)
+
+
+# Many vectors, on either side of the split series kernel's line (blocks: Ltau / 2 per vector), as applies
+# and inside a solve.
+@pytest.mark.parametrize("L,Ltau,nrhs", [(24, 20, 26), (24, 20, 52), (26, 20, 52), (28, 20, 52), (30, 20, 26),
+                                         (30, 20, 52)])
+@pytest.mark.parametrize("prec", ["f64", "f32_refined"])
+def test_series_of_many_vectors(L, Ltau, nrhs, prec):
+    lat = OL.Lattice(L, Ltau, 0.1, 1.0, 0.1, 1.0)
+    rng = np.random.default_rng(5 * L + nrhs)
+    x = rng.standard_normal((Ltau, lat.N))
+    b = rng.standard_normal((nrhs, Ltau, lat.N))
+    s = _solver(lat, nrhs)
+    s.set_field(torch.from_numpy(x).cuda())
+    pc = OP.Preconditioner(lat, x, 1.0, 1.0, C=OL.sparse_C(lat).tocsr())
+    some = [0, 1, nrhs // 2, nrhs - 1]
+    bg = torch.from_numpy(b).cuda()
+    got = s.precond(bg if prec == "f64" else bg.float(), "FFT").double().cpu().numpy()
+    for r in some:
+        ref = pc.apply_FFt(b[r])
+        assert np.max(np.abs(got[r] - ref)) < (1e-12 if prec == "f64" else 1e-5) * np.max(np.abs(ref)), r
+    _close(_direction(s, bg, prec)[some], b[some], [pc] * len(some), prec)

@@ -135,3 +135,29 @@ out["uneven"] = threads((4, 40, 700), (16, 40, 20))
     assert out == {"few small": [512, 512], "many small": [256, 256], "largest of the small": [256, 256],
                    "above": [512, 256], "large": [512, 1024], "many large": [512, 256], "wide": [512, 1024],
                    "many wide": [512, 256], "uneven": [512, 1024]}
+
+
+# The series kernel: real and imaginary parts on separate lanes while the blocks of all right-hand sides
+# leave the compute units room, from 129 plaquettes on and for FP32 at L = 32.
+def test_series_kernel_by_blocks(record):
+    out = record("""
+def kernel(L, Ltau, prec, n):
+    h = handle(L, Ltau, n)
+    lib.fph_set_field(h, P, 1.0, 1.0, None)
+    names()
+    assert lib.fph_precond_apply(h, _lib.FPH_PC_FFT, prec, n, P, P, None) == 0
+    k = [(rec.rec_name(i).decode(), rec.rec_threads(i)) for i in range(rec.rec_count())]
+    k = [("split" if "split" in name else "whole", t) for name, t in k if "k_kpm" in name]
+    lib.fph_destroy(h)
+    return k[0]
+F64, F32 = _lib.FPH_F64, _lib.FPH_F32
+out["L=22"] = [kernel(22, 40, p, 40) for p in (F64, F32)]
+out["L=24"] = [kernel(24, 32, F64, 32), kernel(24, 32, F64, 33), kernel(24, 32, F32, 16), kernel(24, 32, F32, 17)]
+out["L=30"] = [kernel(30, 32, F64, 32), kernel(30, 32, F64, 33), kernel(30, 32, F32, 16), kernel(30, 32, F32, 17)]
+out["L=32"] = [kernel(32, 32, F64, 33), kernel(32, 32, F32, 32), kernel(32, 32, F32, 33)]
+out["L=34"] = [kernel(34, 4, F64, 1), kernel(34, 4, F32, 1)]
+""")
+    s, w = "split", "whole"
+    assert out == {"L=22": [[s, 256], [s, 256]], "L=24": [[s, 512], [w, 192], [s, 512], [w, 192]],
+                   "L=30": [[s, 512], [w, 256], [s, 512], [w, 256]], "L=32": [[s, 512], [s, 512], [w, 256]],
+                   "L=34": [[w, 512], [w, 512]]}
