@@ -108,7 +108,7 @@ __global__ void k_pc_twiddles(int H, int H1, int H2, int Ltau, double2* tw64, do
 
 // How many blocks of F F^T, longest series first, to apply as N x N matrices
 // (k_pc_dense, k_kpm_split) to n vectors.  A block's series is a chain of
-// 2 (N_P - 1) exchanges of 0.2 us each (0.3 in FP64 with more than 100 plaquettes),
+// 2 (N_P - 1) exchanges of 0.2 us each (0.3 in FP64 from 100 plaquettes on),
 // and the longest one left sets the kernel's time; the rows of the
 // matrices run beside the series, one vector after the other, about 1 us each
 // and what reading the matrices takes at 6.7 MB per us.  N_P(0) is
@@ -121,7 +121,7 @@ __global__ void k_pc_twiddles(int H, int H1, int H2, int Ltau, double2* tw64, do
 // Ltau 400, FP32 (N_P 110) 1: 68.3 / 30.8.  Over 100 such cases (L 8 to 32, N_P 12
 // to 110) the rule is never slower than the series by more than 0.4 %.
 FPH_DEVINL int dense_count(const int* np, int N, int kdmax, int elem, int n) {
-  const double step = elem == 16 && N > 400 ? 0.6 : 0.4;
+  const double step = elem == 16 && N >= 400 ? 0.6 : 0.4;
   double best = step * (np[0] - 1) - 1.0;
   int kd = 0;
   for (int k = 1; k <= kdmax; ++k) {
