@@ -712,7 +712,7 @@ struct SolveRun {
   }
 
   hipError_t start(hipStream_t s) {
-    hipLaunchKernelGGL(k_solve_init, dim3(1), dim3(64), 0, s, nrhs, init, sq.latest());
+    hipLaunchKernelGGL(k_solve_init, dim3((nrhs + 63) / 64), dim3(64), 0, s, nrhs, init, sq.latest());
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !zero) return e;
     const long n = (long)nrhs * h->g.d;

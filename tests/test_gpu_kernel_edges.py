@@ -344,3 +344,23 @@ def test_direct_sides(L, Ltau):
     a, b = torch.from_numpy(xi).cuda(), torch.from_numpy(gx).cuda()
     assert _relmax(m.green_average(a, b).cpu().numpy(), OM.green_average_estimate(lat, xi, gx)) < 1e-12
     assert _relmax(m.pair_products(a, b).cpu().numpy(), OM.pair_products_estimate(lat, xi, gx)) < 1e-12
+
+
+# More right-hand sides than a wave has lanes: every one is started, solved and reported.
+@pytest.mark.parametrize("nrhs", [64, 65, 130])
+@pytest.mark.parametrize("prec", ["f64", "f32_refined"])
+@pytest.mark.parametrize("precond", [False, True])
+def test_many_right_hand_sides(nrhs, prec, precond):
+    lat = OL.Lattice(16, 20, 0.1, 1.0, 0.1, 1.0)
+    rng = np.random.default_rng(nrhs)
+    x = rng.standard_normal((lat.Ltau, lat.N))
+    b = rng.standard_normal((nrhs, lat.Ltau, lat.N))
+    s = _solver(lat, nrhs)
+    s.set_field(torch.from_numpy(x).cuda())
+    u, st = s.solve(torch.from_numpy(b).cuda(), tol=1e-11, prec=prec, precond=precond, maxiter=2000)
+    C = OL.sparse_C(lat).tocsr()
+    un = u.cpu().numpy()
+    res = b - OL.apply_MT(lat, x, OL.apply_M(lat, x, un, C), C)
+    for r in range(nrhs):
+        assert st[r]["status"] == 1 and np.linalg.norm(res[r]) <= 1.1e-11 * np.linalg.norm(b[r]), r
+        assert st[r]["action"] == pytest.approx(float(np.sum(b[r] * un[r])), rel=1e-12)

@@ -16,7 +16,8 @@ PRELUDE = """
 import ctypes, json, sys
 sys.path.insert(0, {root!r})
 rec = ctypes.CDLL({so!r}, mode=ctypes.RTLD_GLOBAL)
-rec.rec_name.restype, rec.rec_threads.restype = ctypes.c_char_p, ctypes.c_long
+rec.rec_name.restype = ctypes.c_char_p
+rec.rec_threads.restype = rec.rec_blocks.restype = ctypes.c_long
 from paper_2203_01291_amd import _lib
 lib = ctypes.CDLL(_lib.LIB_PATH)
 for name, (res, args) in _lib.EXPORTS.items():
@@ -161,3 +162,17 @@ out["L=34"] = [kernel(34, 4, F64, 1), kernel(34, 4, F32, 1)]
     assert out == {"L=22": [[s, 256], [s, 256]], "L=24": [[s, 512], [w, 192], [s, 512], [w, 192]],
                    "L=30": [[s, 512], [w, 256], [s, 512], [w, 256]], "L=32": [[s, 512], [s, 512], [w, 256]],
                    "L=34": [[w, 512], [w, 512]]}
+
+
+# Every right-hand side's state is set before a solve.
+def test_every_state_is_initialised(record):
+    out = record("""
+h = handle(16, 32, 200)
+lib.fph_set_field(h, P, 1.0, 1.0, None)
+for n in (1, 64, 65, 200):
+    rec.rec_reset()
+    assert lib.pcg_solve(h, n, P, P, opts(_lib.FPH_F64, 0), P, None) == 0
+    k = [i for i in range(rec.rec_count()) if b"k_solve_init" in rec.rec_name(i)]
+    out[n] = len(k) == 1 and rec.rec_blocks(k[0]) * rec.rec_threads(k[0]) >= n
+""")
+    assert out == {"1": True, "64": True, "65": True, "200": True}
