@@ -23,6 +23,7 @@
 // (A^T = s C^T diag(dbar) - c, C^T = P_B P_A).
 #pragma once
 
+#include <cmath>
 #include <cstring>
 #include <type_traits>
 
@@ -54,6 +55,7 @@ struct PcTables {
   int dense_cls[2];  // least class whose matrices are enqueued for the field set last (pc_dense), FP64 and FP32
   void* Z;         // complex workspace, max_rhs * H * N (double2)
   void* Z2;
+  double a1, a2;   // series orders of the field set last (k_pc_bounds)
   double th, c4;   // tanh(dtau t) and cosh(dtau t)^4: P_A P_B = c4 P'_A P'_B, C2' = [[1, th], [th, 1]]
 };
 
@@ -1855,15 +1857,26 @@ inline hipError_t pc_set_field(PcTables* pc, const Geom& g, const double* dbar64
                      (const int*)np, pc->coef64 + (long)f * pc->H * kNPMax,
                      pc->coef32 + (long)f * pc->H * kNPMax);
   pc->dense_cls[0] = pc->dense_cls[1] = kDenseCls;
+  pc->a1 = a1;
+  pc->a2 = a2;
   return hipGetLastError();
+}
+
+// Steps of the blocks of nrhs vectors per compute unit (256 of them) over those
+// of the longest block: the mean of N_P ~ a1 / phi + a2 over the frequencies
+// against its value at the lowest.  Small: the longest chain sets the time of a
+// series kernel; large: how fast the units issue.
+inline double pc_load(const PcTables* pc, const Geom& g, int nrhs) {
+  const double inv_phi = (std::log(2.0 * g.Ltau) + 0.5772) / M_PI;  // mean of 1 / phi
+  return pc->H * (double)nrhs / 256.0 * (pc->a2 + pc->a1 * inv_phi) / (pc->a2 + pc->a1 * g.Ltau / M_PI);
 }
 
 // Whether the series kernel is k_kpm_split (its rule stands with pc_kpm).
 template <typename T>
 bool pc_split(const PcTables* pc, const Geom& g, int nrhs) {
-  const long blocks = (long)pc->H * nrhs;
-  if (g.hL == 16) return sizeof(T) == 8 || blocks <= 512;
-  return g.Q <= 128 || (g.Q <= 256 && blocks <= (sizeof(T) == 8 ? 512 : 256));
+  if (g.hL == 16) return sizeof(T) == 8 || (long)pc->H * nrhs <= 512;
+  if (g.Q <= 32 || (g.Q > 64 && g.Q <= 128)) return true;
+  return g.Q <= 256 && pc_load(pc, g, nrhs) <= (g.Q <= 64 ? 1.8 : 0.5);
 }
 
 // The class whose matrices an apply of F F^T to nrhs vectors takes, or -1 where
@@ -2067,21 +2080,21 @@ hipError_t pc_kpm(const PcTables* pc, const Geom& g, const T* dbar, int op, int 
   // Split parts up to 256 plaquettes (8 waves); with 16 waves per block
   // (L = 40) the barrier costs more than the shorter steps give (26.2
   // against 24.2 us per FP32 F F^T at Ltau = 100, 30.7 against 28.7 in FP64).
-  // The blocks of several right-hand sides fill the compute units: past one or
-  // two blocks each, where issue and not the chain sets the time, the unsplit
-  // form needs fewer instructions and, above 128 plaquettes, half the waves.
-  // L = 32 (each plaquette row one 16-lane row of a wave: row form), FP32, Ltau
-  // 400: split 19.1 against 20.8 us for one right-hand side, 23.2 / 24.1 for two,
-  // 33.2 / 32.2 for four, 49.1 / 46.5 for ten; FP64 gains or ties throughout.
-  // Solver iteration at L = 24, Ltau 100, series of 11 to 14 terms, split / unsplit,
-  // FP64: 200 blocks 37.3 / 36.7 us, 400 51.0 / 44.6, 800 79.5 / 63.4, 2 000 149 / 111;
-  // of up to 29 terms 47.3 / 47.6, 52.8 / 53.9, 60.9 / 61.7, 102 / 83 (and below 512
-  // blocks the split form has its matrices); FP32 23.9 / 23.8, 28.8 / 26.9, 37.2 /
-  // 31.1, 55.2 / 43.1 and 28.7 / 29.0, 32.5 / 32.4, 36.7 / 35.2, 47.8 / 43.8.  Up to
-  // 128 plaquettes the split form wins or ties but for short series (12 terms, L =
-  // 12, 1 280 blocks, FP64: 44.9 / 41.0; of 45 terms 47.0 / 52.8).
+  // The blocks of several right-hand sides fill the compute units, and then
+  // issue and not the chain sets the time: the unsplit form needs fewer
+  // instructions and, but for 32 plaquettes and fewer or 65 to 128, half the
+  // waves.  L = 32 (each plaquette row one 16-lane row of a wave: row form), FP32,
+  // Ltau 400: split 19.1 against 20.8 us for one right-hand side, 23.2 / 24.1 for
+  // two, 33.2 / 32.2 for four, 49.1 / 46.5 for ten; FP64 gains or ties throughout.
+  // Elsewhere the line is a load (pc_load); solver iteration, us, split / unsplit, at
+  // loads of 0.6, 1.1, 2.3 and 5.7 (L = 24, Ltau 100, N_P 11 to 14) FP64 37.3 / 36.7,
+  // 51.0 / 44.6, 79.5 / 63.4, 149 / 111, FP32 23.9 / 23.8, 28.8 / 26.9, 37.2 / 31.1, 55.2 /
+  // 43.1; at 0.1, 0.3 and 0.7 (N_P 2 to 29) FP64 52.8 / 53.9, 60.9 / 61.7, 102 / 83, FP32
+  // 32.5 / 32.4, 36.7 / 35.2, 47.8 / 43.8.  33 to 64 plaquettes (L = 16, Ltau 160) at 1.6,
+  // 2.4 and 8 FP64 35.2 / 36.4, 43.0 / 39.7, 83.6 / 79.7; at 1.0 99 / 94, FP32 63.1 / 68.4.
   if (!pc_split<T>(pc, g, nrhs)) {
     if (g.hL == 16) return pc_launch_kpm<T, 256, true>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
+    if (g.Q <= 64) return pc_launch_kpm<T, 64>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
     if (g.Q <= 192) return pc_launch_kpm<T, 192>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
     if (g.Q <= 256) return pc_launch_kpm<T, 256>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);
     if (g.Q <= 512) return pc_launch_kpm<T, 512>(pc, g, dbar, op, nrhs, Z, Zo, U, sq, th, c4, s);

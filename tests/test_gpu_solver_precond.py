@@ -179,10 +179,9 @@ def test_apply_does_not_depend_on_solves(L, Ltau):
         assert torch.equal(s.precond(w, "FFT"), ref)
 
 
-# Many vectors, on either side of the split series kernel's line (blocks: Ltau / 2 per vector), as applies
-# and inside a solve.
-@pytest.mark.parametrize("L,Ltau,nrhs", [(24, 20, 26), (24, 20, 52), (26, 20, 52), (28, 20, 52), (30, 20, 26),
-                                         (30, 20, 52)])
+# Many vectors, on either side of the split series kernel's line, as applies and inside a solve.
+@pytest.mark.parametrize("L,Ltau,nrhs", [(14, 20, 200), (16, 20, 140), (16, 20, 200), (24, 20, 26), (24, 20, 52),
+                                         (26, 20, 52), (28, 20, 52), (30, 20, 26), (30, 20, 52)])
 @pytest.mark.parametrize("prec", ["f64", "f32_refined"])
 def test_series_of_many_vectors(L, Ltau, nrhs, prec):
     lat = OL.Lattice(L, Ltau, 0.1, 1.0, 0.1, 1.0)

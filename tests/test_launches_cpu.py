@@ -138,13 +138,13 @@ out["uneven"] = threads((4, 40, 700), (16, 40, 20))
                    "many wide": [512, 256], "uneven": [512, 1024]}
 
 
-# The series kernel: real and imaginary parts on separate lanes while the blocks of all right-hand sides
-# leave the compute units room, from 129 plaquettes on and for FP32 at L = 32.
-def test_series_kernel_by_blocks(record):
+# The series kernel: real and imaginary parts on separate lanes while the longest block sets the time; at
+# 33 to 64 and 129 to 256 plaquettes by the load, at L = 32 in FP32 by the blocks.
+def test_series_kernel_by_load(record):
     out = record("""
-def kernel(L, Ltau, prec, n):
+def kernel(L, Ltau, prec, n, a=(1.0, 1.0)):
     h = handle(L, Ltau, n)
-    lib.fph_set_field(h, P, 1.0, 1.0, None)
+    lib.fph_set_field(h, P, *a, None)
     names()
     assert lib.fph_precond_apply(h, _lib.FPH_PC_FFT, prec, n, P, P, None) == 0
     k = [(rec.rec_name(i).decode(), rec.rec_threads(i)) for i in range(rec.rec_count())]
@@ -152,16 +152,19 @@ def kernel(L, Ltau, prec, n):
     lib.fph_destroy(h)
     return k[0]
 F64, F32 = _lib.FPH_F64, _lib.FPH_F32
-out["L=22"] = [kernel(22, 40, p, 40) for p in (F64, F32)]
-out["L=24"] = [kernel(24, 32, F64, 32), kernel(24, 32, F64, 33), kernel(24, 32, F32, 16), kernel(24, 32, F32, 17)]
-out["L=30"] = [kernel(30, 32, F64, 32), kernel(30, 32, F64, 33), kernel(30, 32, F32, 16), kernel(30, 32, F32, 17)]
+S = (0.15, 12.0)  # short series, about as long at every frequency
+out["L=10"] = [kernel(10, 32, p, 256, S) for p in (F64, F32)]
+out["L=16"] = [kernel(16, 32, F64, 60), kernel(16, 32, F64, 31, S), kernel(16, 32, F64, 32, S)]
+out["L=22"] = [kernel(22, 32, p, 64, S) for p in (F64, F32)]
+out["L=24"] = [kernel(24, 32, F64, 35), kernel(24, 32, F64, 36), kernel(24, 32, F32, 8, S), kernel(24, 32, F32, 9, S)]
+out["L=30"] = [kernel(30, 32, F64, 8, S), kernel(30, 32, F64, 9, S)]
 out["L=32"] = [kernel(32, 32, F64, 33), kernel(32, 32, F32, 32), kernel(32, 32, F32, 33)]
 out["L=34"] = [kernel(34, 4, F64, 1), kernel(34, 4, F32, 1)]
 """)
     s, w = "split", "whole"
-    assert out == {"L=22": [[s, 256], [s, 256]], "L=24": [[s, 512], [w, 192], [s, 512], [w, 192]],
-                   "L=30": [[s, 512], [w, 256], [s, 512], [w, 256]], "L=32": [[s, 512], [s, 512], [w, 256]],
-                   "L=34": [[w, 512], [w, 512]]}
+    assert out == {"L=10": [[s, 64], [s, 64]], "L=16": [[s, 128], [s, 128], [w, 64]], "L=22": [[s, 256], [s, 256]],
+                   "L=24": [[s, 512], [w, 192], [s, 512], [w, 192]], "L=30": [[s, 512], [w, 256]],
+                   "L=32": [[s, 512], [s, 512], [w, 256]], "L=34": [[w, 512], [w, 512]]}
 
 
 # Every right-hand side's state is set before a solve.
