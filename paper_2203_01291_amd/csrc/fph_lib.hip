@@ -744,14 +744,17 @@ struct SolveRun {
 };
 
 // Whether a solve runs in one launch, a workgroup per right-hand side
-// (fph_small.h).  The line lies where a workgroup's time per iteration, which
-// grows with the unknowns, meets that of the two or four launches of a slot,
-// which hardly does (one right-hand side to 1e-13, launches / one workgroup, ms;
-// preconditioned FP64 L = 4, Ltau 40: 1.46 / 0.91, Ltau 100: 4.0 / 3.7, Ltau 160:
-// 8.1 / 8.9; L = 6, Ltau 60: 2.7 / 2.5; L = 10, Ltau 60: 3.0 / 4.0; plain FP64
-// L = 4, Ltau 160: 14.1 / 10.3, L = 8, Ltau 60: 8.1 / 6.3, L = 12, Ltau 40: 5.8 /
-// 6.0; plain FP32-refined L = 10, Ltau 60: 8.3 / 7.1, L = 16, Ltau 40: 5.9 / 6.9).
-// More right-hand sides than compute units would queue.
+// (fph_small.h).  A workgroup's time per iteration grows with the unknowns, that
+// of the two or four launches of a slot hardly does (one right-hand side to
+// 1e-13, launches / one workgroup, ms; preconditioned FP64 L = 4, Ltau 40: 1.41 /
+// 0.81, Ltau 100: 3.43 / 2.71, Ltau 128: 4.19 / 3.93, Ltau 160: 5.29 / 6.07; L = 6,
+// Ltau 56: 2.43 / 2.08, Ltau 80: 2.97 / 3.51; plain FP64 L = 4, Ltau 160: 12.6 / 9.9,
+// L = 8, Ltau 60: 8.9 / 6.1, L = 16, Ltau 40: 6.5 / 7.8; plain FP32-refined L = 10,
+// Ltau 60: 9.6 / 6.9, L = 16, Ltau 40: 6.8 / 6.5).  Up to the line one launch wins for
+// every shape measured, by 7 % at least, and by more with more right-hand sides
+// (64 of L = 4, Ltau 128: 7.5 / 4.1); some shapes above it would gain too
+// (preconditioned FP32-refined up to 4 000 unknowns, plain FP64 up to 6 000).  More
+// right-hand sides than compute units would queue.
 bool small_route(const SolveRun& run) {
   const PcTables& pc = run.h->pc;
   const long most = run.pre ? 2048 : run.mixed ? 6144 : 4096;

@@ -1664,12 +1664,13 @@ k_kpm(Geom g, int H, int nrhs, int op, const PcInfo* __restrict__ info,
   const int i0 = w.x0 + w.row[1], iL = i0 + g.L;
 
   // The series depends on no scalar of the CG, so inside a solve only one
-  // block per right-hand side reads the solver state: the one with the
-  // shortest series (the last of the longest-first order), which folds the
+  // block per right-hand side folds the solver state: the one with the
+  // shortest series (the last of the longest-first order), which adds the
   // pending |r|^2 and writes the state for the next kernel.  The other
-  // blocks never wait for the state; for a right-hand side that has
-  // finished or paused they compute a transform the next kernel ignores.
-  // The reading block issues the state loads first and folds them between
+  // blocks read one word of it beside their tables, whether the right-hand
+  // side has finished or paused, and return at once if so (a right-hand side
+  // that finishes with this very |r|^2 is transformed for nothing).
+  // The folding block issues the state loads first and folds them between
   // the conjugate series and the series of F F^T, where they have long
   // arrived (a right-hand side found finished or paused there skips the
   // second series); only F or F^T alone folds before the series.  (The

@@ -8,8 +8,8 @@
 // vectors stay in the compute unit's caches.  Every decision is taken by the
 // functions of fph_common.h on a state of the same form, so a solve takes the
 // same path as the launch sequence up to the order of its sums.  Bound by its
-// chain of phases: L = 4, Ltau = 40, preconditioned FP64 takes 16 us per
-// iteration against 28 us in four launches (without: 5 against 10 us).
+// chain of phases: L = 4, Ltau = 40, preconditioned FP64 takes 15 us per
+// iteration against 26 us in four launches (without: 4.4 against 11 us).
 #pragma once
 
 #include "fph_batch.h"
