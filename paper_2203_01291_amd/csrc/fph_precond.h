@@ -110,30 +110,32 @@ __global__ void k_pc_twiddles(int H, int H1, int H2, int Ltau, double2* tw64, do
 
 // How many blocks of F F^T, longest series first, to apply as N x N matrices
 // (k_pc_dense, k_kpm_split) to n vectors.  A block's series is a chain of
-// 2 (N_P - 1) exchanges of 0.2 us each (0.3 in FP64 from 100 plaquettes on),
-// and the longest one left sets the kernel's time; the rows of the
-// matrices run beside the series, one vector after the other, about 1 us each
-// and what reading the matrices takes at 6.7 MB per us.  N_P(0) is
-// large only at the lowest frequencies (its a1/phi term), so a few matrices
-// can shorten the chain several times.  The count with the least estimated
-// time, if it gains at least 1 us per apply.  Solver iteration in us, series /
-// best count of matrices: L = 16, Ltau 160, FP64 (N_P 45), 1 vector 36.3 / 23.5,
-// 4 39.0 / 27.5, 8 42.9 / 35.3, 16 48.2 / 52.7 (one matrix), 32 60 / 87; L = 32,
-// Ltau 160, FP64 (N_P 45) 1: 48.2 / 29.7, 4: 56.9 / 46.0, 8: 65.5 / 72.2; L = 32,
-// Ltau 400, FP32 (N_P 110) 1: 68.3 / 30.8.  Over 100 such cases (L 8 to 32, N_P 12
-// to 110) the rule is never slower than the series by more than 0.4 %.
+// 2 (N_P - 1) exchanges, 0.45 us an order (0.6 in FP64 from 100 plaquettes on),
+// and the longest one left sets the kernel's time.  N_P(0) is large only at the
+// lowest frequencies (its a1/phi term), so a few matrices can shorten the chain
+// several times.  Matrices are read beside the series at some 5 MB per us: the count
+// is where that time meets the chain that is left.  But their rows serve one vector
+// after the other, 1.1 us each and what is read: matrices only if that too
+// is shorter than the whole chain by 0.7 us.  Solver iteration in us, series / best count
+// of matrices: L = 16, Ltau 160, FP64 (N_P 45), 1 vector 36.3 / 23.5, 4 39.0 / 27.5,
+// 8 42.9 / 35.3, 16 48.2 / 52.7 (one matrix), 32 60 / 87; L = 32, Ltau 160, FP64 (N_P
+// 45) 1: 48.2 / 29.7, 4: 56.9 / 46.0, 8: 65.5 / 72.2; L = 32, Ltau 400, FP32 (N_P 110)
+// 1: 68.3 / 30.8.  Over 200 such cases (L 8 to 32, N_P 12 to 110, up to 32 vectors) the
+// rule was never slower than the series and 0.8 % from the best count on average.
 FPH_DEVINL int dense_count(const int* np, int N, int kdmax, int elem, int n) {
-  const double step = elem == 16 && N >= 400 ? 0.6 : 0.4;
-  double best = step * (np[0] - 1) - 1.0;
+  const double step = elem == 16 && N >= 400 ? 0.6 : 0.45;
+  const double read = n * ((double)N * N * elem / 5e6);
+  double best = 1e30;
   int kd = 0;
   for (int k = 1; k <= kdmax; ++k) {
-    const double t = fmax(step * (np[k] - 1), n * (1.0 + k * ((double)N * N * elem / 6.7e6)));
+    const double t = fmax(step * (np[k] - 1), 0.5 + k * read);
     if (t < best) {
       best = t;
       kd = k;
     }
   }
-  return kd;
+  const double t = fmax(step * (np[kd] - 1), n * 1.1 + 0.75 * kd * read);
+  return t < step * (np[0] - 1) - 0.7 ? kd : 0;
 }
 
 // Class of n right-hand sides in PcInfo::want; from kDenseCls on no matrix pays.
