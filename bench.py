@@ -598,12 +598,12 @@ def blas_threads():
 # WRITE_SIZE runs of `bench.py --profile-roofline`, each scaled by the same
 # counter read for a copy kernel of known size.  Valid only while the
 # kernel sources hash to `source_sha1`; otherwise reported as null.
-# FETCH_SIZE scale 518400 / 259212.53 = 1.99990 (a copy of 518 400 KiB reads
+# FETCH_SIZE scale 518400 / 259212.58 = 1.99990 (a copy of 518 400 KiB reads
 # that much), WRITE_SIZE scale 1.0; bytes per launch = (FETCH * 1.99990 +
 # WRITE) KiB * 1024, means over 10 launches.
-TRAFFIC = {"f64_bytes_per_launch": 1091089002, "f32_bytes_per_launch": 1088261336,
+TRAFFIC = {"f64_bytes_per_launch": 1091023728, "f32_bytes_per_launch": 1088579241,
            "fetch_scale": 1.99990, "write_scale": 1.0,
-           "source_sha1": "01cc514bbb45de89220a178dc083dd46ac74a522",
+           "source_sha1": "58d3177457d4507cb69687650c28c53c1313301a",
            "profile": "profiles/mtm_L64_Ltau400_roofline_counters.md"}
 KERNEL_SOURCES = ["paper_2203_01291_amd/csrc/fph_matvec.h", "paper_2203_01291_amd/csrc/fph_common.h",
                   "paper_2203_01291_amd/csrc/fph_lib.hip"]
